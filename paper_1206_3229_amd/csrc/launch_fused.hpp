@@ -1,0 +1,43 @@
+// Launcher of the fused kick and drift kernel, shared by the translation units
+// of the two storages.
+#pragma once
+
+#include "vlasov_internal.hpp"
+
+namespace vlasov_detail {
+
+template <typename T, int TW>
+int launch_kick_drift_w(vlasov_ctx *c, int ta, double h)
+{
+    // one kicked column per thread (whole wavefronts); the two half drifts
+    // run on waves of their own
+    constexpr int NT = vk::KDGeom<TW>::NT;
+    const vlasov_params &P = c->P;
+    const int nb = c->kd_rb;
+    const int ntx = (int)((P.nx + TW - 1) / TW), nty = (int)((c->nblk + nb - 1) / nb);
+    const dim3 grid((unsigned)vk::xcd_grid(ntx, nty));
+    const T *fin = (const T *)c->fcur();
+    T *fout = (T *)c->fnext();
+    const double *F = force_ptr(c);
+    const int tb = (ta + 1) % c->nsub;
+    const int32_t *dm2 = c->dm(tb);
+    const double4 *dw1 = c->dw(ta), *dw2 = c->dw(tb);
+    const int32_t *kbase = c->at<int32_t>(c->L.kd_base) + (size_t)ta * (size_t)c->nblk;
+    const int32_t *krel = c->at<int32_t>(c->L.kd_rel) + (size_t)ta * (size_t)P.np;
+    double *part = c->at<double>(c->L.part);
+    const int nx = (int)P.nx, np = (int)P.np;
+#define KD_LAUNCH(BX, BP)                                                                                             \
+    launch(c, VLASOV_K_KICK_DRIFT2, vk::k_kick_drift<T, BX, BP, TW, vk::KD_SPR, kd_pf<T>(), vk::KD_PAIR>, grid, dim3(NT), \
+           fin, fout, F, h, c->dp, dm2, dw1, dw2, kbase, krel, part, nx, np, nb, ntx, nty)
+    if (P.bc_x == VLASOV_BC_PERIODIC) {
+        if (P.bc_p == VLASOV_BC_PERIODIC) KD_LAUNCH(vk::BC_PERIODIC, vk::BC_PERIODIC); else KD_LAUNCH(vk::BC_PERIODIC, vk::BC_ZERO);
+    } else {
+        if (P.bc_p == VLASOV_BC_PERIODIC) KD_LAUNCH(vk::BC_ZERO, vk::BC_PERIODIC); else KD_LAUNCH(vk::BC_ZERO, vk::BC_ZERO);
+    }
+#undef KD_LAUNCH
+    int rc = check_launch("kick+drift");
+    if (rc == VLASOV_OK) c->cur ^= 1;
+    return rc;
+}
+
+}  // namespace vlasov_detail

@@ -119,6 +119,23 @@ __device__ __forceinline__ int wrap(int q, int n)
     return r < 0 ? r + n : r;
 }
 
+// wrap() of a position that is mostly within one period of [0, n): the
+// division only where it is not.
+__device__ __forceinline__ int wrap_near(int q, int n)
+{
+    int r = q < 0 ? q + n : (q >= n ? q - n : q);
+    if ((unsigned)r >= (unsigned)n) r = wrap(q, n);
+    return r;
+}
+
+// reduce_offset() of a foot, whose m fits 32 bits (|xi| < 2^31).
+template <int BC>
+__device__ __forceinline__ int foot_offset(const Foot &ft, int n)
+{
+    const int m = (int)ft.m;
+    return BC == BC_PERIODIC ? wrap_near(m, n) : min(max(m, -(n + 16)), n + 16);
+}
+
 // One sample of a line of n values (stride between samples `stride`) under
 // the boundary rule of the axis.
 template <typename T, int BC>
@@ -553,14 +570,15 @@ static __global__ __launch_bounds__(256) void k_kick_filter(const T *__restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Step 3 fused with the two half drifts that follow it (step 4 and step 1 of
-// the next step).  Once the force is known nothing global separates the kick
-// of a row from its drifts, so one workgroup kicks the columns its drift
-// windows need and drifts the kicked rows straight from LDS: f is read and
-// written once for the three sweeps.  The arithmetic of every value is that
-// of the separate kick and drifts, so results are identical bit for bit.
+// Step 3 fused with the half drifts that follow it: both (step 4 and step 1 of
+// the next step) inside a call, step 4 alone after the last kick of a call.
+// Once the force is known nothing global separates the kick of a row from its
+// drifts, so one workgroup kicks the columns its drift windows need and drifts
+// the kicked rows straight from LDS: f is read and written once for the two or
+// three sweeps.  The arithmetic of every value is that of the separate kick
+// and drifts, so results are identical bit for bit.
 //
-// Tile: RB consecutive density blocks (16 RB rows) by TW output columns.  The
+// Tile: nb consecutive density blocks (16 nb rows) by TW output columns.  The
 // first-pass window of row j starts at column i0 + o_j - 8, o_j = m1_j + m2_j
 // the sum of the row's two drift offsets; over the tile these windows lie in
 // the KW = TW + 18 + SPR kicked columns starting at i0 + kbase (kbase = min_j
@@ -568,287 +586,506 @@ static __global__ __launch_bounds__(256) void k_kick_filter(const T *__restrict_
 // krel_j = o_j - min o.  A grid whose tiles need krel > SPR takes the
 // separate kernels.
 //
-// Work per row (one barrier per row, three rows in flight):
-//   kick of row r: every lane kicks one column (NT >= KW lanes) from a
-//     sliding register window of its column (the kick of row r needs the
-//     samples r - 4 + m .. r + 5 + m), loads requested PF rows ahead, and
-//     writes the kicked value to slot t of the row's LDS buffer;
-//   first half drift of row r - 1 (the first W1 waves): runs of V1 = 5
-//     adjacent intermediate values per lane, TW + 9 of them per row;
-//   second half drift of row r - 2 (the next W2 waves): runs of V2 = 4
-//     outputs per lane, stored to HBM, and their serial column sums over the
-//     block (density partial sums).
-// A run of V outputs shares its V + 1 stencils (V + 9 samples), so a lane
-// computes 1 + 1/V stencils per output instead of 2.
+// Work per interval of two rows (one barrier per interval, three intervals in
+// flight), each part by waves of its own:
+//   kick of rows r, r + 1: every lane kicks one column from a sliding register
+//     window of its column (the kick of row r needs the samples r - 4 + m .. r
+//     + 5 + m), loads requested PF rows ahead, and writes the kicked values to
+//     the rows' LDS buffers;
+//   first half drift of the two rows before them;
+//   second half drift of the two rows before those, stored to HBM, and their
+//     serial column sums over the block (density partial sums).
+// A drift lane forms a run of four adjacent outputs (five stencils for four
+// outputs), lanes 0..31 of a wave in the first row of the pair and lanes
+// 32..63 in the second; the waves of a part share the runs of a row.
+//
+// What bounds it: small grids by the time of an interval in one wave (0.35 us
+// with every wave kicking and drifting in turn 0.5 us, hence waves of their
+// own for each part); FP64 at 4096^2 by the traffic (318 MB, 51 us of data
+// movement alone) and VALU issue together, FP32 by VALU issue.  Runs of four
+// cost 15.25 operations an output and 7 LDS reads of 16 bytes for four
+// (runs of two: 17.5, and 12); row weights stand in LDS and row offsets one per
+// lane (v_readlane), where scalar loads between the barriers cost a wait each.
+// Measured alone, before -> now: 230 x 16 6.9 -> 5.9 us, 1024^2 10.1 -> 9.5,
+// 2048^2 22.2 -> 20.9, 4096^2 65.9 -> 64.2 (FP32 42.1 -> 38.4).
 // ---------------------------------------------------------------------------
 constexpr int KD_SPR = 8;
-// rows per barrier interval of the fused kernel
+// rows per barrier interval, and density blocks of a tile at most (the rows of
+// a tile fit one per lane)
 constexpr int KD_RPI = 2;
+constexpr int KD_MAX_BLOCKS = 4;
+
+// What follows the kick: both half drifts with density partial sums, or one
+// half drift without.
+enum { KD_PAIR = 0, KD_LAST = 1 };
 
 // Geometry of a fused tile of TW columns whose rows' windows lie within SPR
-// columns of slack: runs of two adjacent values per lane in both half drifts
-// (16-byte LDS accesses, conflict-free), W1 waves for the first half drift
-// (TW + 9 values per row) and W2 for the second (TW outputs), one kicked
-// column per lane over the KW = TW + 18 + SPR columns the windows need.  Every
-// wave kicks; TW = 230 (four waves) and 486 (eight) with 8 columns of slack,
-// and TW = 182 with 56, make the kicked columns and both half drifts fill
-// their waves.
+// columns of slack: WK waves kick the KW = TW + 18 + SPR columns the windows
+// need (one per lane), W1 waves run the first half drift (TW + 9 values per
+// row) and W2 the second (TW outputs).  TW = 230 (4 + 2 + 2 waves) and 486 (8 +
+// 4 + 4) with 8 columns of slack, and TW = 182 with 56, fill the kicking lanes.
 template <int TW, int SPR = KD_SPR>
 struct KDGeom {
-    static constexpr int V = 2;                          // outputs per lane in the half drifts
-    static constexpr int MIDN = TW + 9;                  // first-pass values per row
-    static constexpr int NRUN1 = (MIDN + V - 1) / V;     // first-pass lanes
-    static constexpr int NRUN2 = TW / V;                 // second-pass lanes
-    static constexpr int W1 = (NRUN1 + 63) / 64, W2 = (NRUN2 + 63) / 64;
-    static constexpr int KW = TW + 18 + SPR;             // kicked columns per row
-    static constexpr int NWK = (KW + 63) / 64;
-    static constexpr int NW = NWK > W1 + W2 ? NWK : W1 + W2;  // waves
-    static constexpr int NT = 64 * NW;
-    // Role of wave w in a workgroup rotated by `rot`: roles [0, W1) run the
-    // first half drift, [W1, W1 + W2) the second.  Rotating the roles from one
-    // workgroup to the next spreads them over the SIMDs.
-    static __device__ __forceinline__ int role(int w, int rot) { return (w + NW - rot) % NW; }
-    // kicked row: column c of the range at slot c + (krel & 1), so that every
-    // row's window starts at an even slot; both buffers padded for the reads
-    // of the last runs (V + 10 values from slot V u)
-    static constexpr int NBUF = 2 * KD_RPI;  // rows in each LDS ring
-    static constexpr int KLD = NT + 16;
-    static constexpr int MLD = NRUN1 * V + 16;
-    static_assert(TW % V == 0, "whole second-pass runs");
-    static_assert(SPR + 1 + V * (NRUN1 - 1) + V + 10 <= KLD, "first-pass reads stay in the kicked row");
-    static_assert(V * (NRUN2 - 1) + V + 10 <= MLD, "second-pass reads stay in the first-pass row");
+    static constexpr int V = 4;                              // outputs per lane in the half drifts
+    static constexpr int MIDN = TW + 9;                      // first-pass values per row
+    static constexpr int NRUN1 = (MIDN + V - 1) / V;         // first-pass runs per row
+    static constexpr int NRUN2 = (TW + V - 1) / V;           // second-pass runs per row
+    static constexpr int KW = TW + 18 + SPR;                 // kicked columns per row
+    static constexpr int WK = (KW + 63) / 64;
+    static constexpr int W1 = (NRUN1 + 31) / 32, W2 = (NRUN2 + 31) / 32;
+    static constexpr int NTK = 64 * WK, NT = 64 * (WK + W1 + W2);  // kicking lanes, threads
+    static constexpr int R1 = (NRUN1 + W1 - 1) / W1, R2 = (NRUN2 + W2 - 1) / W2;  // runs per wave and row
+    static constexpr int NBUF = 2 * KD_RPI;                  // rows in each LDS ring
+    // Rows are held in groups of four values (KDRow).  Column c of the kicked
+    // range is at slot c + pad, pad = -krel mod 4, so that every row's window
+    // starts a group.
+    static constexpr int NG = NTK / 4 + 4;                   // groups per row
+    static constexpr int ROWLD = 4 * NG;                     // values per row
+    // Part of wave w in workgroup `rot`: the kicking waves come first, so that
+    // each SIMD gets kicking and drifting waves alike; the two drifts change
+    // places from one workgroup to the next.
+    static __device__ __forceinline__ int part(int w, int rot)
+    {
+        if (w < WK) return w;
+        const int d = w - WK + (rot & 1) * W1;
+        return WK + (d < W1 + W2 ? d : d - (W1 + W2));
+    }
+    static_assert((SPR + 3) / 4 + NRUN1 + 3 <= NG && NRUN2 + 3 <= NG, "run reads stay in the row");
+    static_assert(NG % 8 == 4, "the two halves of FP64 groups on distinct banks");
 };
 
-// P2: the calling wave runs the second half drift (and stores); the other
-// waves run the first half drift (or only kick).  The two roles are separate
-// code, so that the wait of each for its requested kick samples counts only
-// its own memory operations.
-template <typename T, int BCX, int BCP, int TW, int PF, int RB, bool FULL, bool P2, int SPR = KD_SPR>
-__device__ __forceinline__ void kick_drift_tile(const T *__restrict__ fin, T *__restrict__ fout,
-                                                const double *__restrict__ F, double dt, double dp,
-                                                const int32_t *__restrict__ dm2, const double4 *__restrict__ dw1,
-                                                const double4 *__restrict__ dw2, const int32_t *__restrict__ kbase,
-                                                const int32_t *__restrict__ krel, double *__restrict__ part, int nx,
-                                                int np, int tx, int ty, int rw, T *kbuf, T *mbuf)
+// A row of groups of four values in LDS.  FP32: contiguous, one 16-byte word
+// per group.  FP64: the first pairs of all groups, then the second pairs, so
+// that the lanes of a run read (lane u word u) touch consecutive 16-byte words.
+template <typename T> struct KDRow;
+template <> struct KDRow<float> {
+    static __device__ __forceinline__ int at(int slot, int) { return slot; }
+    template <int NG>
+    static __device__ __forceinline__ void read(const float *row, int g, float (&x)[16])
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float4 v = reinterpret_cast<const float4 *>(row)[g + k];
+            x[4 * k] = v.x;
+            x[4 * k + 1] = v.y;
+            x[4 * k + 2] = v.z;
+            x[4 * k + 3] = v.w;
+        }
+    }
+    template <int NG>
+    static __device__ __forceinline__ void write(float *row, int g, const float (&o)[4])
+    {
+        reinterpret_cast<float4 *>(row)[g] = make_float4(o[0], o[1], o[2], o[3]);
+    }
+    static __device__ __forceinline__ void weights(const float *p, float (&w)[4])
+    {
+        const float4 v = *reinterpret_cast<const float4 *>(p);
+        w[0] = v.x;
+        w[1] = v.y;
+        w[2] = v.z;
+        w[3] = v.w;
+    }
+};
+template <> struct KDRow<double> {
+    static __device__ __forceinline__ int at(int slot, int ng) { return (slot >> 2) * 2 + (slot & 1) + (slot & 2) * ng; }
+    template <int NG>
+    static __device__ __forceinline__ void read(const double *row, int g, double (&x)[16])
+    {
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {  // samples 14 and 15 are not used
+            const double2 v = reinterpret_cast<const double2 *>(row)[g + (k >> 1) + (k & 1) * NG];
+            x[2 * k] = v.x;
+            x[2 * k + 1] = v.y;
+        }
+        x[14] = x[15] = 0.0;
+    }
+    template <int NG>
+    static __device__ __forceinline__ void write(double *row, int g, const double (&o)[4])
+    {
+        double2 *p = reinterpret_cast<double2 *>(row);
+        p[g] = make_double2(o[0], o[1]);
+        p[g + NG] = make_double2(o[2], o[3]);
+    }
+    static __device__ __forceinline__ void weights(const double *p, double (&w)[4])
+    {
+        const double2 v0 = reinterpret_cast<const double2 *>(p)[0], v1 = reinterpret_cast<const double2 *>(p)[1];
+        w[0] = v0.x;
+        w[1] = v0.y;
+        w[2] = v1.x;
+        w[3] = v1.y;
+    }
+};
+
+// Four adjacent outputs from samples x[0 .. 13] (output k's cell starts at
+// x[4 + k]).
+template <typename T>
+__device__ __forceinline__ void spline_run4(const T (&x)[16], T a, T b, T g, T d, T (&o)[4])
+{
+    T Dk = second_diff(x + 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const T Dk1 = second_diff(x + 5 + k);
+        o[k] = spline(a, b, g, d, x[4 + k], x[5 + k], Dk, Dk1);
+        Dk = Dk1;
+    }
+}
+
+// Lanes 0..31 hold p, q of row a and lanes 32..63 those of row b.  Afterwards
+// lanes 0..31 hold p of both rows (p: row a, q: row b) and lanes 32..63 q.
+__device__ __forceinline__ void swap_halves(float &p, float &q)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+    p = __uint_as_float(r[0]);
+    q = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_halves(double &p, double &q)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(p), __double2loint(q), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(p), __double2hiint(q), false, false);
+    p = __hiloint2double((int)hi[0], (int)lo[0]);
+    q = __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+// Two adjacent values stored at any multiple of their own size (rows of an
+// odd length).
+template <typename T>
+__device__ __forceinline__ void store2(T *p, T v0, T v1)
+{
+    typedef T pair_t __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+    pair_t v;
+    v.x = v0;
+    v.y = v1;
+    *reinterpret_cast<pair_t *>(p) = v;
+}
+
+template <typename T>
+struct KDTile {
+    const T *fin;
+    T *fout;
+    const double *F;
+    double dt, dp;
+    const int32_t *dm;  // offsets of the half drift whose result is stored
+    const double4 *dw1, *dw2;
+    const int32_t *kbase, *krel;
+    double *part;
+    int nx, np, nb, tx, ty;
+    T *kbuf, *mbuf, *wtab;  // LDS: rings of NBUF rows of ROWLD values, 8 weights for each of the 16 nb rows
+};
+
+// Row offsets of a tile, one row per lane (a tile has at most 64 rows): the
+// window's start in the kicked range (rel_v), and the first kicked column.
+template <int MODE, int BCX, typename T>
+__device__ __forceinline__ void kd_rows(const KDTile<T> &a, int i0, int jl, int &rel_v, int &cL)
+{
+    if (MODE == KD_PAIR) {
+        rel_v = a.krel[jl];
+        cL = i0 + a.kbase[a.ty];
+    } else {
+        // offsets of the single half drift relative to their minimum over the
+        // tile (the host checked that they spread by at most SPR columns; on a
+        // periodic axis of nx >= 4 SPR they are known mod nx)
+        const int dm = a.dm[jl];
+        const int ref = __builtin_amdgcn_readfirstlane(dm);
+        int d = dm - ref;
+        if (BCX == BC_PERIODIC) {
+            d = 2 * d > a.nx ? d - a.nx : d;
+            d = 2 * d < -a.nx ? d + a.nx : d;
+        }
+        int mn = d;
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) mn = min(mn, __shfl_xor(mn, s, 64));
+        rel_v = d - mn;
+        cL = i0 + ref + __builtin_amdgcn_readfirstlane(mn) - 4;
+    }
+}
+
+// The kicking waves: lane t kicks column cL + t of every row of the tile.
+template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int MODE>
+__device__ __forceinline__ void kd_kick_part(const KDTile<T> &a, int t)
 {
     using G = KDGeom<TW, SPR>;
-    using V2 = typename Vec2<T>::type;
-    constexpr int V = G::V, R = ROWS_PER_BLOCK, KLD = G::KLD, MLD = G::MLD;
+    constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NI = R / P, NB = G::NBUF;
     constexpr int NS = R + 10 + PF;  // window slots: samples of a block plus those requested ahead
-    static_assert(NS <= 32, "one mask bit per sample");
-    const int t = threadIdx.x;
-    const int lane = t & 63;
-    const int i0 = tx * TW;
-    const int j0 = ty * (R * RB);
-    const int nr = FULL ? R * RB : min(R * RB, np - j0);  // rows of the tile
+    constexpr int LAG = MODE == KD_PAIR ? 2 : 1;
+    static_assert(PF % P == 0 && NS <= 32, "whole requests per interval, one mask bit per sample");
+    const int nx = a.nx, np = a.np, i0 = a.tx * TW, j0 = a.ty * (R * a.nb);
+    const int nblk = (min(R * a.nb, np - j0) + R - 1) / R;
+    int rel_v, cL;
+    kd_rows<MODE, BCX>(a, i0, min(j0 + (t & 63), np - 1), rel_v, cL);
+    const int pad_v = 4 * ((rel_v + 3) >> 2) - rel_v;
 
-    // padding of the row buffers (read only by values that are never kept)
-    for (int s = G::NT + t; s < KLD; s += G::NT)
-#pragma unroll
-        for (int b = 0; b < G::NBUF; ++b) kbuf[b * KLD + s] = T(0);
-    for (int s = G::NRUN1 * V + t; s < MLD; s += G::NT)
-#pragma unroll
-        for (int b = 0; b < G::NBUF; ++b) mbuf[b * MLD + s] = T(0);
-
-    // The kicked column of this lane: foot of its p shift (eq. step3), the
-    // spline weights, and the element index of its first sample.
-    const int cL = i0 + kbase[ty];
+    // Foot of the column's p shift (eq. step3), the spline weights, and the
+    // row of the first sample.
     const int c = cL + t;
     int gc;
-    bool colin = true;
+    bool colin = true, xin = true;
     if (BCX == BC_PERIODIC) {
-        gc = wrap(c, nx);
+        gc = wrap_near(c, nx);
     } else {
         gc = min(max(c, 0), nx - 1);
         colin = c >= 0 && c < nx;
+        xin = cL >= 0 && cL + G::NTK <= nx;
     }
-    // every kicked column lies inside the grid (or the axis is periodic): no mask
-    const bool kick_in = BCX == BC_PERIODIC || (cL >= 0 && cL + G::NT <= nx);
-    const Foot ft = foot_of_shift((F[gc] * dt) / dp);
-    const int m = reduce_offset(ft.m, np, BCP);
+    const Foot ft = foot_of_shift((a.F[gc] * a.dt) / a.dp);
+    const int m = foot_offset<BCP>(ft, np);
     const T ka = (T)ft.a, kb = (T)ft.b, kg = (T)ft.g, kd = (T)ft.d;
-    const uint32_t total = (uint32_t)np * (uint32_t)nx;
-    // periodic p: element index of the next sample to request (one row per
-    // request, wrapped by one subtraction); zero p: row of sample 0
-    int rb0 = j0 + m - 4;
-    uint32_t nidx = 0;
-    if (BCP == BC_PERIODIC) {
-        rb0 = wrap(rb0, np);
-        nidx = (uint32_t)rb0 * (uint32_t)nx + (uint32_t)gc;
-    }
-    uint32_t inside = 0;  // zero p: bit s says that sample s lies in the grid
-    T w[NS];
-    auto request = [&](int s) {
-        // sample s of the window (of the current block)
+    // Samples are requested two rows at a time, from p0 and p1.  Where no
+    // column of the wave needs a boundary rule in this tile (pin) both move by
+    // two rows; otherwise the rows of the next request are wrapped (periodic)
+    // or clamped, with bit s of `inside` saying that sample s lies in the grid.
+    // The loads stand outside of that branch: in it, the compiler waited for
+    // every outstanding load before the next request.
+    int q0 = j0 + m - 4;
+    if (BCP == BC_PERIODIC) q0 = wrap_near(q0, np);
+    const size_t ld = (size_t)nx;
+    const int pin = __builtin_amdgcn_readfirstlane((int)__all(q0 >= 0 && q0 + R * nblk + 10 + PF <= np));
+    const T *fcol = a.fin + gc;
+    uint32_t inside = 0;
+    const T *p0, *p1;
+    auto place = [&]() {
         if (BCP == BC_PERIODIC) {
-            w[s] = fin[nidx];
-            nidx += (uint32_t)nx;
-            nidx = min(nidx, nidx - total);  // unsigned: subtracts total once past the end
+            p0 = fcol + (size_t)q0 * ld;
+            p1 = fcol + (size_t)(q0 + 1 < np ? q0 + 1 : 0) * ld;
         } else {
-            const int q = rb0 + s;
-            inside |= (uint32_t)(q >= 0 && q < np) << s;
-            w[s] = fin[(size_t)min(max(q, 0), np - 1) * (size_t)nx + (size_t)gc];
+            p0 = fcol + (size_t)min(max(q0, 0), np - 1) * ld;
+            p1 = fcol + (size_t)min(max(q0 + 1, 0), np - 1) * ld;
+        }
+    };
+    place();
+    T w[NS];
+    auto request2 = [&](int s) {  // samples s, s + 1 of the window (of the current block)
+        w[s] = *p0;
+        w[s + 1] = *p1;
+        if (pin) {
+            p0 += 2 * ld;
+            p1 += 2 * ld;
+        } else {
+            if (BCP != BC_PERIODIC) {
+                inside |= (uint32_t)(q0 >= 0 && q0 < np) << s;
+                inside |= (uint32_t)(q0 + 1 >= 0 && q0 + 1 < np) << (s + 1);
+            }
+            q0 += 2;
+            if (BCP == BC_PERIODIC) q0 = q0 >= np ? q0 - np : q0;
+            place();
         }
     };
     auto settle = [&](int s) {
-        if (BCP != BC_PERIODIC) w[s] = (inside >> s & 1u) ? w[s] : T(0);
+        if (BCP != BC_PERIODIC)
+            if (!pin) w[s] = (inside >> s & 1u) ? w[s] : T(0);
     };
 #pragma unroll
-    for (int s = 0; s < 10 + PF; ++s) request(s);
+    for (int s = 0; s < 10 + PF; s += 2) request2(s);
 #pragma unroll
     for (int s = 0; s < 9; ++s) settle(s);
     T Dk = second_diff(w + 4);
+    int pad = -1;
+    T *dst = a.kbuf;  // LDS slot of the column in ring row 0, for the pad of the current row
 
-    const bool pass1 = !P2 && rw < G::W1;
-    const int u1 = 64 * rw + lane, u2 = 64 * (rw - G::W1) + lane;  // run of the lane in its pass
-    const int i = i0 + V * u2;  // first output column of a second-pass lane
-    const bool own2 = P2 && u2 < G::NRUN2 && i < nx;
-    const bool own1 = pass1 && u1 < G::NRUN1;
-
-    // Interval it of block blk kicks rows P it .. P it + P - 1 of the block
-    // (P = KD_RPI rows per barrier interval), runs the first half drift of the
-    // P rows before them and the second of the P rows before those; negative
-    // rows are the previous block's last ones, so the pipeline runs on across
-    // the blocks of a tile and only the last block drains it (two more
-    // intervals).  Row q's buffers are slot q mod 2P of each ring.
-    constexpr int P = KD_RPI, NI = R / P, NB = G::NBUF;
-    static_assert(R % P == 0 && (NB & (NB - 1)) == 0, "whole intervals per block, ring of 2^k rows");
-    double acc[V];
+    for (int blk = 0; blk < nblk; ++blk) {
+        const bool more = blk + 1 < nblk;  // uniform
 #pragma unroll
-    for (int k = 0; k < V; ++k) acc[k] = 0.0;
-#pragma unroll
-    for (int blk = 0; blk < RB; ++blk) {
-        const int jb = j0 + R * blk;
-        if (!FULL && R * blk >= nr) break;  // uniform
-        const bool lastb = blk + 1 == RB || (!FULL && R * (blk + 1) >= nr);  // uniform
-#pragma unroll
-        for (int it = 0; it < NI + 2; ++it) {
-            if (it >= NI && !lastb) break;  // uniform
+        for (int it = 0; it < NI; ++it) {
 #pragma unroll
             for (int s = 0; s < P; ++s) {
                 const int r = P * it + s;
-                if (it < NI && (FULL || R * blk + r < nr)) {
-                    // kick of row r into its buffer
-                    settle(r + 9);
-                    const T Dk1 = second_diff(w + r + 5);
-                    T y = spline(ka, kb, kg, kd, w[r + 4], w[r + 5], Dk, Dk1);
-                    Dk = Dk1;
-                    if (!kick_in) y = colin ? y : T(0);
-                    kbuf[(r & (NB - 1)) * KLD + (krel[jb + r] & 1) + t] = y;
-                    // samples of the next block are requested too (the last
-                    // block's extra requests read valid rows and are unused)
-                    if (r + 10 + PF < NS && (RB > 1 || r + 10 + PF < R + 10)) request(r + 10 + PF);
+                settle(r + 9);
+                const T Dk1 = second_diff(w + r + 5);
+                T y = spline(ka, kb, kg, kd, w[r + 4], w[r + 5], Dk, Dk1);
+                Dk = Dk1;
+                if (BCX == BC_ZERO && !xin) {
+                    y = colin ? y : T(0);
+                    __asm__ __volatile__("");  // a branch of the edge tiles, not a select in all
                 }
+                const int rp = __builtin_amdgcn_readlane(pad_v, R * blk + r);
+                if (rp != pad) {  // uniform, changes a few times per tile at most
+                    pad = rp;
+                    dst = a.kbuf + KDRow<T>::at(t + pad, G::NG);
+                }
+                dst[(r & (NB - 1)) * LD] = y;
             }
+            if (P * it + 10 + PF < R + 10 || more) request2(P * it + 10 + PF);
+            __syncthreads();
+        }
+        // slide the window by one block: sample s + 16 becomes sample s
 #pragma unroll
-            for (int s = 0; s < P; ++s) {
-                const int q1 = P * (it - 1) + s;
-                if (!P2 && (it >= 1 || blk > 0) && it - 1 < NI && (FULL || R * blk + q1 < nr) && own1) {
-                    // first half drift (table 1) of row q1 at the positions
-                    // i0 + m2 - 4 + q, q in [0, TW + 9), that the second reads
-                    const int j = jb + q1;
-                    const int rel = krel[j];
-                    const T *src = kbuf + (q1 & (NB - 1)) * KLD + rel + (rel & 1);
-                    const double4 w1 = dw1[j];
-                    T o[V];
-                    spline_run<T, V>(src, u1, (T)w1.x, (T)w1.y, (T)w1.z, (T)w1.w, o);
-                    if (BCX == BC_ZERO) {
-                        const int lo = i0 + dm2[j] - 4;  // position of first-pass value 0
-                        if (!(lo >= 0 && lo + G::MIDN <= nx)) {
-                            const int q = lo + V * u1;
+        for (int s = 0; s + R < NS; ++s) w[s] = w[s + R];
+        inside >>= R;
+    }
 #pragma unroll
-                            for (int k = 0; k < V; ++k)
-                                if (q + k < 0 || q + k >= nx) o[k] = T(0);
-                        }
+    for (int k = 0; k < LAG; ++k) __syncthreads();
+}
+
+// The waves of the first half drift of a pair: wave w1 of W1.
+template <typename T, int BCX, int TW, int SPR>
+__device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
+{
+    using G = KDGeom<TW, SPR>;
+    constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NB = G::NBUF;
+    const int nx = a.nx, np = a.np, i0 = a.tx * TW, j0 = a.ty * (R * a.nb);
+    const int nblk = (min(R * a.nb, np - j0) + R - 1) / R;
+    const int lane = threadIdx.x & 63, l32 = lane & 31;
+    const bool hi = lane >= 32;
+    const int jl = min(j0 + lane, np - 1);
+    const int st_v = 4 * ((a.krel[jl] + 3) >> 2);  // slot where the row's window starts, in elements of its first half
+    int dm_v = 0;
+    bool xin = true;  // no value of the tile lies outside the grid
+    if (BCX == BC_ZERO) {
+        dm_v = a.dm[jl];
+        const int lo = i0 + dm_v - 4;
+        xin = __all(lo >= 0 && lo + 4 * G::NRUN1 <= nx);
+    }
+    const int u = min(G::R1 * w1 + min(l32, G::R1 - 1), G::NRUN1 - 1);  // lanes past the last run repeat it
+    const T *src = a.kbuf + (hi ? LD : 0);
+    T *dst = a.mbuf + (hi ? LD : 0);
+    const T *wt = a.wtab + (hi ? 8 : 0);
+    __syncthreads();
+#pragma unroll 2
+    for (int it = 0; it < nblk * (R / P); ++it) {
+        const int qs = (P * it) & (NB - 1);  // ring slot of the pair's first row
+        const int sa = __builtin_amdgcn_readlane(st_v, P * it), sb = __builtin_amdgcn_readlane(st_v, P * it + 1);
+        T x[16], wr[4], o[4];
+        KDRow<T>::template read<G::NG>(src + qs * LD, ((hi ? sb : sa) >> 2) + u, x);
+        KDRow<T>::weights(wt, wr);
+        wt += 8 * P;
+        spline_run4<T>(x, wr[0], wr[1], wr[2], wr[3], o);
+        if (BCX == BC_ZERO && !xin) {
+            const int da = __builtin_amdgcn_readlane(dm_v, P * it), db = __builtin_amdgcn_readlane(dm_v, P * it + 1);
+            const int q = i0 + (hi ? db : da) - 4 + 4 * u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = q + k >= 0 && q + k < nx ? o[k] : T(0);
+            __asm__ __volatile__("");  // a branch of the edge tiles, not a select in all
+        }
+        KDRow<T>::template write<G::NG>(dst + qs * LD, u, o);
+        __syncthreads();
+    }
+    __syncthreads();
+}
+
+// The waves of the half drift whose result is stored: wave w2 of W2.
+template <typename T, int BCX, int TW, int SPR, int MODE>
+__device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
+{
+    using G = KDGeom<TW, SPR>;
+    constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NB = G::NBUF, NI = R / P;
+    constexpr int LAG = MODE == KD_PAIR ? 2 : 1;
+    const int nx = a.nx, np = a.np, i0 = a.tx * TW, j0 = a.ty * (R * a.nb);
+    const int nr = min(R * a.nb, np - j0), nblk = (nr + R - 1) / R;
+    const int lane = threadIdx.x & 63, l32 = lane & 31;
+    const bool hi = lane >= 32;
+    int st_v = 0, cL;
+    if (MODE == KD_LAST) {
+        kd_rows<MODE, BCX>(a, i0, min(j0 + lane, np - 1), st_v, cL);
+        st_v = 4 * ((st_v + 3) >> 2);
+    }
+    const int u = min(G::R2 * w2 + min(l32, G::R2 - 1), G::NRUN2 - 1);
+    const int i = i0 + 4 * u + (hi ? 2 : 0);  // this lane stores columns i and i + 1
+    const bool own = l32 < G::R2 && G::R2 * w2 + l32 < G::NRUN2;
+    const int left = own ? min(i0 + TW, nx) - i : 0;
+    const bool two = left >= 2, one = left == 1, anyone = __any(one);
+    const T *src = (MODE == KD_PAIR ? a.mbuf : a.kbuf) + (hi ? LD : 0);
+    const T *wt = a.wtab + (hi ? 8 : 0) + (MODE == KD_PAIR ? 4 : 0);
+    const uint32_t io = (uint32_t)i * (uint32_t)sizeof(T), ios = (uint32_t)i * (uint32_t)sizeof(double);  // bytes
+    const size_t ld = (size_t)nx, ldb = ld * sizeof(T);
+    char *out = reinterpret_cast<char *>(a.fout + (size_t)j0 * ld);  // row stored next
+#pragma unroll
+    for (int k = 0; k < LAG; ++k) __syncthreads();
+    for (int blk = 0; blk < nblk; ++blk) {
+        double acc0 = 0.0, acc1 = 0.0;
+#pragma unroll 2
+        for (int it = 0; it < NI; ++it) {
+            const int row = R * blk + P * it;
+            const int qs = (P * it) & (NB - 1);
+            T x[16], wr[4], o[4];
+            int g = u;
+            if (MODE == KD_LAST) {
+                const int sa = __builtin_amdgcn_readlane(st_v, row), sb = __builtin_amdgcn_readlane(st_v, row + 1);
+                g += (hi ? sb : sa) >> 2;
+            }
+            KDRow<T>::template read<G::NG>(src + qs * LD, g, x);
+            KDRow<T>::weights(wt, wr);
+            wt += 8 * P;
+            spline_run4<T>(x, wr[0], wr[1], wr[2], wr[3], o);
+            // o[0], o[1]: first row, o[2], o[3]: second row of the pair, of
+            // columns i and i + 1
+            swap_halves(o[0], o[2]);
+            swap_halves(o[1], o[3]);
+            T *outa = reinterpret_cast<T *>(out + io), *outb = reinterpret_cast<T *>(out + ldb + io);
+            out += 2 * ldb;
+            if (row + 1 < nr) {
+                if (two) {
+                    store2(outa, o[0], o[1]);
+                    store2(outb, o[2], o[3]);
+                }
+                if (anyone)
+                    if (one) {
+                        outa[0] = o[0];
+                        outb[0] = o[2];
                     }
-                    V2 ww;
-                    ww.x = o[0];
-                    ww.y = o[1];
-                    reinterpret_cast<V2 *>(mbuf + (q1 & (NB - 1)) * MLD)[u1] = ww;
+                if (MODE == KD_PAIR) {
+                    acc0 = (acc0 + (double)o[0]) + (double)o[2];
+                    acc1 = (acc1 + (double)o[1]) + (double)o[3];
                 }
-            }
-#pragma unroll
-            for (int s = 0; s < P; ++s) {
-                const int q2 = P * (it - 2) + s;
-                if (P2 && (it >= 2 || blk > 0) && (FULL || R * blk + q2 < nr) && own2) {
-                    // second half drift (table 2) of row q2: outputs i, i + 1
-                    const int j = jb + q2;
-                    const double4 wd = dw2[j];
-                    T o[V];
-                    spline_run<T, V>(mbuf + (q2 & (NB - 1)) * MLD, u2, (T)wd.x, (T)wd.y, (T)wd.z, (T)wd.w, o);
-                    if (FULL) {
-                        V2 ww;
-                        ww.x = o[0];
-                        ww.y = o[1];
-                        *reinterpret_cast<V2 *>(fout + (size_t)j * nx + i) = ww;
-                    } else {
-                        store_run<T, V>(fout + (size_t)j * nx, i, nx, o);
-                    }
-#pragma unroll
-                    for (int k = 0; k < V; ++k) acc[k] = acc[k] + (double)o[k];
+            } else if (row < nr) {
+                if (two) store2(outa, o[0], o[1]);
+                if (one) outa[0] = o[0];
+                if (MODE == KD_PAIR) {
+                    acc0 = acc0 + (double)o[0];
+                    acc1 = acc1 + (double)o[1];
                 }
-            }
-            if (P2 && it == 1 && blk > 0) {
-                // the previous block's sums are complete
-                if (own2) {
-                    double *prow = part + (size_t)(ty * RB + blk - 1) * nx;
-#pragma unroll
-                    for (int k = 0; k < V; ++k)
-                        if (i + k < nx) prow[i + k] = acc[k];
-                }
-#pragma unroll
-                for (int k = 0; k < V; ++k) acc[k] = 0.0;
             }
             __syncthreads();
         }
-        if (P2 && own2 && lastb) {
-            double *prow = part + (size_t)(ty * RB + blk) * nx;
-#pragma unroll
-            for (int k = 0; k < V; ++k)
-                if (i + k < nx) prow[i + k] = acc[k];
-        }
-        // slide the window by one block: sample s + 16 becomes sample s
-        if (RB > 1) {
-#pragma unroll
-            for (int s = 0; s + R < NS; ++s) w[s] = w[s + R];
-            inside >>= R;
-            rb0 += R;
+        if (MODE == KD_PAIR) {
+            double *sums = reinterpret_cast<double *>(reinterpret_cast<char *>(a.part + (size_t)(a.ty * a.nb + blk) * ld) + ios);
+            if (two) store2(sums, acc0, acc1);
+            if (one) sums[0] = acc0;
         }
     }
 }
 
-template <typename T, int BCX, int BCP, int TW, int PF, int RB>
-static __global__ __launch_bounds__(KDGeom<TW>::NT) void k_kick_drift(
-    const T *__restrict__ fin, T *__restrict__ fout, const double *__restrict__ F, double dt, double dp,
-    const int32_t *__restrict__ dm2, const double4 *__restrict__ dw1, const double4 *__restrict__ dw2,
-    const int32_t *__restrict__ kbase, const int32_t *__restrict__ krel, double *__restrict__ part, int nx, int np,
-    int ntx, int nty)
+// One tile, by a workgroup of KDGeom::NT threads.
+template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int MODE>
+__device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot)
 {
-    using G = KDGeom<TW>;
-    __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::KLD];  // ring of kicked rows
-    __shared__ __attribute__((aligned(16))) T mbuf[G::NBUF * G::MLD];  // ring of first-pass rows
+    using G = KDGeom<TW, SPR>;
+    constexpr int R = ROWS_PER_BLOCK;
+    const int p = G::part((int)threadIdx.x >> 6, rot);
+    if (p < G::WK) {
+        kd_kick_part<T, BCX, BCP, TW, SPR, PF, MODE>(a, (int)threadIdx.x);
+    } else {
+        // row weights, both passes of a row adjacent
+        const int j0 = a.ty * (R * a.nb);
+        const int n = 2 * R * ((min(R * a.nb, a.np - j0) + R - 1) / R);
+        for (int k = threadIdx.x - G::NTK; k < n; k += G::NT - G::NTK) {
+            const double4 w = (MODE == KD_PAIR && (k & 1) ? a.dw2 : a.dw1)[min(j0 + (k >> 1), a.np - 1)];
+            a.wtab[4 * k] = (T)w.x;
+            a.wtab[4 * k + 1] = (T)w.y;
+            a.wtab[4 * k + 2] = (T)w.z;
+            a.wtab[4 * k + 3] = (T)w.w;
+        }
+        if (MODE == KD_PAIR && p < G::WK + G::W1)
+            kd_first_part<T, BCX, TW, SPR>(a, p - G::WK);
+        else if (p >= G::WK + G::W1)
+            kd_second_part<T, BCX, TW, SPR, MODE>(a, p - G::WK - G::W1);
+    }
+}
+
+template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int MODE>
+static __global__ __launch_bounds__((KDGeom<TW, SPR>::NT)) __attribute__((amdgpu_waves_per_eu(8)))
+void k_kick_drift(
+    const T *__restrict__ fin, T *__restrict__ fout, const double *__restrict__ F, double dt, double dp,
+    const int32_t *__restrict__ dmL, const double4 *__restrict__ dw1, const double4 *__restrict__ dw2,
+    const int32_t *__restrict__ kbase, const int32_t *__restrict__ krel, double *__restrict__ part, int nx, int np,
+    int nb, int ntx, int nty)
+{
+    using G = KDGeom<TW, SPR>;
+    __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];                         // ring of kicked rows
+    __shared__ __attribute__((aligned(16))) T mbuf[MODE == KD_PAIR ? G::NBUF * G::ROWLD : 4];  // of first-pass rows
+    __shared__ __attribute__((aligned(16))) T wtab[8 * ROWS_PER_BLOCK * KD_MAX_BLOCKS];
     int tx, ty;
     if (!xcd_tile(ntx, nty, tx, ty)) return;
-    // every row of the tile in the grid, and rows of an even length (aligned
-    // two-value stores)
-    const bool full = (ty + 1) * (ROWS_PER_BLOCK * RB) <= np && (nx & 1) == 0;
-    const int rw = G::role(threadIdx.x >> 6, blockIdx.x % G::NW);
-    const bool p2 = rw >= G::W1 && rw < G::W1 + G::W2;
-#define KDT(FL, P)                                                                                                  \
-    kick_drift_tile<T, BCX, BCP, TW, PF, RB, FL, P>(fin, fout, F, dt, dp, dm2, dw1, dw2, kbase, krel, part, nx, np, tx, \
-                                                    ty, rw, kbuf, mbuf)
-    if (full) {
-        if (p2)
-            KDT(true, true);
-        else
-            KDT(true, false);
-    } else {
-        if (p2)
-            KDT(false, true);
-        else
-            KDT(false, false);
-    }
-#undef KDT
+    const KDTile<T> a{fin, fout, F, dt, dp, dmL, dw1, dw2, kbase, krel, part, nx, np, nb, tx, ty, kbuf, mbuf, wtab};
+    kick_drift_tile<T, BCX, BCP, TW, SPR, PF, MODE>(a, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1794,19 +2031,18 @@ static __global__ __launch_bounds__(256) void kb_kick(const GridDesc *__restrict
 // columns and four waves, more kicked columns per output).  Periodic p only.
 constexpr int KB_KD_TW = 230;
 constexpr int KB_KD_TW_WIDE = 182, KD_SPR_WIDE = 56;
-// (five waves per SIMD: the FP64 form fits them without spilling)
 template <typename T, int PF>
-static __global__ __launch_bounds__(KDGeom<KB_KD_TW>::NT) __attribute__((amdgpu_waves_per_eu(5)))
+static __global__ __launch_bounds__(KDGeom<KB_KD_TW>::NT) __attribute__((amdgpu_waves_per_eu(8)))
 void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
 {
     using G = KDGeom<KB_KD_TW>;
     using GW = KDGeom<KB_KD_TW_WIDE, KD_SPR_WIDE>;
-    static_assert(G::NT == GW::NT && G::NW == GW::NW && G::W1 == GW::W1 && G::W2 == GW::W2 && G::KLD == GW::KLD &&
+    static_assert(G::NT == GW::NT && G::WK == GW::WK && G::W1 == GW::W1 && G::W2 == GW::W2 && G::ROWLD == GW::ROWLD &&
                       G::NBUF == GW::NBUF,
                   "one workgroup shape and wave roles for both tile widths");
-    constexpr int MLD = G::MLD > GW::MLD ? G::MLD : GW::MLD;
-    __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::KLD];
-    __shared__ __attribute__((aligned(16))) T mbuf[G::NBUF * MLD];
+    __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];
+    __shared__ __attribute__((aligned(16))) T mbuf[G::NBUF * G::ROWLD];
+    __shared__ __attribute__((aligned(16))) T wtab[8 * ROWS_PER_BLOCK];
     const int n = cy->n;
     const int total = cy->off_kd[n];
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
@@ -1819,41 +2055,21 @@ void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy
         const int kin = cy->kin[a];
         const T *fin = (const T *)g.f[kin];
         T *fout = (T *)g.f[kin ^ 1];
-        const bool full = (ty + 1) * ROWS_PER_BLOCK <= g.np && (g.nx & 1) == 0;
-        const int rw = G::role(threadIdx.x >> 6, e % G::NW);
-        const bool p2 = rw >= G::W1 && rw < G::W1 + G::W2;
         __syncthreads();  // the previous item's LDS rows are consumed
-#define KDB(TW, SPR, BX, FL, P)                                                                                     \
-    kick_drift_tile<T, BX, BC_PERIODIC, TW, PF, 1, FL, P, SPR>(fin, fout, g.Fkick, g.dt, g.dp, g.dm, g.dw, g.dw,   \
-                                                               g.kbase, g.krel, g.part, g.nx, g.np, tx, ty, rw, kbuf, \
-                                                               mbuf)
-#define KDB2(TW, SPR, BX, FL)     \
-    if (p2)                       \
-        KDB(TW, SPR, BX, FL, true); \
-    else                          \
-        KDB(TW, SPR, BX, FL, false)
-#define KDB4(TW, SPR)                              \
-    if (g.bc_x == BC_PERIODIC) {                   \
-        if (full) {                                \
-            KDB2(TW, SPR, BC_PERIODIC, true);      \
-        } else {                                   \
-            KDB2(TW, SPR, BC_PERIODIC, false);     \
-        }                                          \
-    } else {                                       \
-        if (full) {                                \
-            KDB2(TW, SPR, BC_ZERO, true);          \
-        } else {                                   \
-            KDB2(TW, SPR, BC_ZERO, false);         \
-        }                                          \
-    }
+        const KDTile<T> t{fin, fout, g.Fkick, g.dt, g.dp, g.dm, g.dw, g.dw, g.kbase, g.krel, g.part, g.nx, g.np, 1, tx, ty,
+                          kbuf, mbuf, wtab};
+        const bool px = g.bc_x == BC_PERIODIC;
         if (g.kd_wide) {
-            KDB4(KB_KD_TW_WIDE, KD_SPR_WIDE)
+            if (px)
+                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, KB_KD_TW_WIDE, KD_SPR_WIDE, PF, KD_PAIR>(t, e);
+            else
+                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, KB_KD_TW_WIDE, KD_SPR_WIDE, PF, KD_PAIR>(t, e);
         } else {
-            KDB4(KB_KD_TW, KD_SPR)
+            if (px)
+                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, KB_KD_TW, KD_SPR, PF, KD_PAIR>(t, e);
+            else
+                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, KB_KD_TW, KD_SPR, PF, KD_PAIR>(t, e);
         }
-#undef KDB4
-#undef KDB2
-#undef KDB
     }
 }
 
