@@ -274,17 +274,16 @@ const char *vlasov_last_error(void);
  * ------------------------------------------------------------------------- */
 
 typedef struct {
-    int32_t drift_threads;     /* threads per drift workgroup: 64, 128 or 256 (2 columns each) */
+    int32_t drift_threads;     /* 64, 128 or 256: accepted and kept, without effect (the drift
+                                  kernel has one shape, tiles of 230 columns) */
     int32_t kick_rows;         /* rows per thread of the kick: 8, 16 or 32 */
-    int32_t kick_drift_width;  /* 0: the kick (step 3) and the two half drifts after it (step 4
-                                  and the next step 1) run as separate kernels; 230 or 486: one
-                                  fused kernel on tiles of that many columns (four or eight
-                                  wavefronts: the 256 or 512 columns a tile kicks, one per
-                                  thread), which reads and writes f once for the three sweeps.
-                                  It is used where the combined drift offsets of the rows of
-                                  every tile differ by at most 8 columns, else the separate
-                                  kernels run.  The last step of a call (kick and one half
-                                  drift) always uses the separate kernels. */
+    int32_t kick_drift_width;  /* 0: the kick (step 3) and the half drifts after it (step 4 and
+                                  the next step 1; step 4 alone after the last kick of a call)
+                                  run as separate kernels; 230 or 486: one fused kernel on tiles
+                                  of that many columns, which reads and writes f once for the
+                                  sweeps.  Where the combined drift offsets of the rows of a
+                                  tile differ by 9 to 56 columns its tiles are 182 columns wide,
+                                  where by more the separate kernels run. */
     int32_t kick_drift_blocks; /* rows of a fused tile in 16-row density blocks: 1 to 4 */
 } vlasov_tuning;
 
@@ -415,7 +414,8 @@ enum {
     VLASOV_K_DRIFT2 = 1,   /* two fused half drifts + density partial sums */
     VLASOV_K_DENSITY = 2,  /* density from the partial sums */
     VLASOV_K_FORCE = 3,    /* model force (and magnetization) */
-    VLASOV_K_KICK = 4,     /* momentum advection */
+    VLASOV_K_KICK = 4,     /* momentum advection, alone, or fused with the half drift after
+                              the last kick of a call, or with two on 182-column tiles */
     VLASOV_K_MOMENTS = 5,  /* diagnostics */
     VLASOV_K_KICK_DRIFT2 = 6,  /* kick fused with two half drifts + density partial sums */
     VLASOV_K_FILTER = 7,   /* the filter along p (fused with the kick of a filtered step) */

@@ -6,12 +6,11 @@
 
 namespace vlasov_detail {
 
-template <typename T, int TW>
-int launch_kick_drift_w(vlasov_ctx *c, int ta, double h)
+template <typename T, int TW, int SPR, int NPASS>
+int launch_kick_drift_w(vlasov_ctx *c, int kid, int ta, double h)
 {
-    // one kicked column per thread (whole wavefronts); the two half drifts
-    // run on waves of their own
-    constexpr int NT = vk::KDGeom<TW>::NT;
+    using G = vk::KDGeom<TW, SPR>;
+    constexpr int NT = NPASS == 2 ? G::NT : G::NT1;
     const vlasov_params &P = c->P;
     const int nb = c->kd_rb;
     const int ntx = (int)((P.nx + TW - 1) / TW), nty = (int)((c->nblk + nb - 1) / nb);
@@ -20,15 +19,15 @@ int launch_kick_drift_w(vlasov_ctx *c, int ta, double h)
     T *fout = (T *)c->fnext();
     const double *F = force_ptr(c);
     const int tb = (ta + 1) % c->nsub;
-    const int32_t *dm2 = c->dm(tb);
+    const int32_t *dm1 = c->dm(ta), *dm2 = c->dm(tb);
     const double4 *dw1 = c->dw(ta), *dw2 = c->dw(tb);
     const int32_t *kbase = c->at<int32_t>(c->L.kd_base) + (size_t)ta * (size_t)c->nblk;
     const int32_t *krel = c->at<int32_t>(c->L.kd_rel) + (size_t)ta * (size_t)P.np;
-    double *part = c->at<double>(c->L.part);
+    double *part = NPASS == 2 ? c->at<double>(c->L.part) : nullptr;
     const int nx = (int)P.nx, np = (int)P.np;
-#define KD_LAUNCH(BX, BP)                                                                                             \
-    launch(c, VLASOV_K_KICK_DRIFT2, vk::k_kick_drift<T, BX, BP, TW, vk::KD_SPR, kd_pf<T>(), vk::KD_PAIR>, grid, dim3(NT), \
-           fin, fout, F, h, c->dp, dm2, dw1, dw2, kbase, krel, part, nx, np, nb, ntx, nty)
+#define KD_LAUNCH(BX, BP)                                                                                      \
+    launch(c, kid, vk::k_kick_drift<T, BX, BP, TW, SPR, kd_pf<T>(), NPASS>, grid, dim3(NT), fin, fout, F, h, c->dp, \
+           dm1, dm2, dw1, dw2, kbase, krel, part, nx, np, nb, ntx, nty)
     if (P.bc_x == VLASOV_BC_PERIODIC) {
         if (P.bc_p == VLASOV_BC_PERIODIC) KD_LAUNCH(vk::BC_PERIODIC, vk::BC_PERIODIC); else KD_LAUNCH(vk::BC_PERIODIC, vk::BC_ZERO);
     } else {
@@ -38,6 +37,19 @@ int launch_kick_drift_w(vlasov_ctx *c, int ta, double h)
     int rc = check_launch("kick+drift");
     if (rc == VLASOV_OK) c->cur ^= 1;
     return rc;
+}
+
+template <typename T>
+int launch_kick_drift(vlasov_ctx *c, int ta, bool pair, int64_t spread, double h)
+{
+    if (pair) {
+        if (spread > vk::KD_SPR)
+            return launch_kick_drift_w<T, vk::KD_TW_WIDE, vk::KD_SPR_WIDE, 2>(c, VLASOV_K_KICK, ta, h);
+        if (c->tune.kick_drift_width == 486) return launch_kick_drift_w<T, 486, vk::KD_SPR, 2>(c, VLASOV_K_KICK_DRIFT2, ta, h);
+        return launch_kick_drift_w<T, KD_TW, vk::KD_SPR, 2>(c, VLASOV_K_KICK_DRIFT2, ta, h);
+    }
+    if (spread > vk::KD_SPR) return launch_kick_drift_w<T, vk::KD_TW_WIDE, vk::KD_SPR_WIDE, 1>(c, VLASOV_K_KICK, ta, h);
+    return launch_kick_drift_w<T, KD_TW, vk::KD_SPR, 1>(c, VLASOV_K_KICK, ta, h);
 }
 
 }  // namespace vlasov_detail

@@ -4,7 +4,6 @@
 
 namespace vlasov_detail {
 
-template int launch_kick_drift_w<float, 230>(vlasov_ctx *, int, double);
-template int launch_kick_drift_w<float, 486>(vlasov_ctx *, int, double);
+template int launch_kick_drift<float>(vlasov_ctx *, int, bool, int64_t, double);
 
 }  // namespace vlasov_detail

@@ -220,15 +220,21 @@ int gs_kick(vlasov_ctx *c, double h)
     return c->P.storage == VLASOV_F32 ? gs_kick_t<float>(c, h) : gs_kick_t<double>(c, h);
 }
 
-// Fused kick and two half drifts (+ density partial sums) on tiles of TW
-// columns by RB density blocks.
+// Kick of substep k, then (with the filter in between if filt) the half drift
+// of table k and, tb >= 0, that of table tb: in one kernel where the offsets of
+// the rows of every tile lie close enough together, else in separate ones.
+// Measured, a call's last kick and half drift apart -> in one kernel: 4096^2
+// sheet 106 -> 57.6 us (FP32 46 -> 30), 2048^2 27 -> 18, 64^2 17 -> 6.7.
 int kick_then_drift(vlasov_ctx *c, int k, int tb, double h, bool filt)
 {
-    const int w = c->tune.kick_drift_width;
-    if (tb >= 0 && !filt && w != 0 && c->kd_ok[k] && c->P.spline == VLASOV_SPLINE_FD) {
-        const bool f32 = c->P.storage == VLASOV_F32;
-        if (w == 230) return f32 ? launch_kick_drift_w<float, 230>(c, k, h) : launch_kick_drift_w<double, 230>(c, k, h);
-        return f32 ? launch_kick_drift_w<float, 486>(c, k, h) : launch_kick_drift_w<double, 486>(c, k, h);
+    if (!filt && c->tune.kick_drift_width != 0 && c->P.spline == VLASOV_SPLINE_FD) {
+        const int64_t spread = tb >= 0 ? c->kd_spread[k] : c->kd_spread1[k];
+        // with one half drift the kernel takes the offsets mod nx, which are
+        // apart by less than half a period on lines of four spreads
+        const bool known = tb >= 0 || c->P.bc_x == VLASOV_BC_ZERO || c->P.nx >= 4 * spread + 16;
+        if (spread <= vk::KD_SPR_WIDE && known)
+            return c->P.storage == VLASOV_F32 ? launch_kick_drift<float>(c, k, tb >= 0, spread, h)
+                                              : launch_kick_drift<double>(c, k, tb >= 0, spread, h);
     }
     int rc = filt ? kick_filter(c, h) : kick(c, h);
     if (rc == VLASOV_OK) rc = drift(c, k, tb, tb >= 0);
@@ -239,9 +245,8 @@ int kick_then_drift(vlasov_ctx *c, int k, int tb, double h, bool filt)
 // per pair (k, k + 1 mod nsub) of drift tables: row j's two half drifts move
 // its window by o_j = m_k,j + m_k+1,j columns; per tile the start of its
 // kicked column range relative to the tile, per row the offset of its window
-// in that range.  Sets kd_ok[k] (the single-grid kernels' slack) and
-// kd_spread[k]; the tables are filled for spreads up to the batched kernel's
-// wider slack.
+// in that range.  Sets kd_spread[k] and kd_spread1[k]; the tables are filled
+// for spreads up to the slack of the narrower tiles.
 void build_kd_tables(vlasov_ctx *c, int rb)
 {
     const vlasov_params &P = c->P;
@@ -253,15 +258,18 @@ void build_kd_tables(vlasov_ctx *c, int rb)
         const int64_t *mb = c->h_mfull.data() + (size_t)((k + 1) % c->nsub) * (size_t)P.np;
         int32_t *base = c->h_kd_base.data() + (size_t)k * (size_t)c->nblk;
         int32_t *rel = c->h_kd_rel.data() + (size_t)k * (size_t)P.np;
-        int64_t spread = 0;
+        int64_t spread = 0, spread1 = 0;
         for (int64_t b = 0; b < ntile; ++b) {
             const int64_t j0 = b * rows, j1 = std::min<int64_t>(P.np, j0 + rows);
-            int64_t lo = ma[j0] + mb[j0], hi = lo;
+            int64_t lo = ma[j0] + mb[j0], hi = lo, lo1 = ma[j0], hi1 = lo1;
             for (int64_t j = j0; j < j1; ++j) {
                 lo = std::min(lo, ma[j] + mb[j]);
                 hi = std::max(hi, ma[j] + mb[j]);
+                lo1 = std::min(lo1, ma[j]);
+                hi1 = std::max(hi1, ma[j]);
             }
             spread = std::max(spread, hi - lo);
+            spread1 = std::max(spread1, hi1 - lo1);
             if (hi - lo > vk::KD_SPR_WIDE) continue;  // not fusable; the tables are unused
             for (int64_t j = j0; j < j1; ++j) rel[j] = (int32_t)(ma[j] + mb[j] - lo);
             int64_t s0 = lo - 8;
@@ -271,8 +279,8 @@ void build_kd_tables(vlasov_ctx *c, int rb)
             }
             base[b] = (int32_t)s0;
         }
-        c->kd_ok[k] = spread <= vk::KD_SPR;
         c->kd_spread[k] = spread;
+        c->kd_spread1[k] = spread1;
     }
     c->kd_rb = rb;
 }

@@ -61,14 +61,13 @@ int one_block_tiles(vlasov_ctx *c)
 
 int kd_tiles(const vlasov_ctx *c)
 {
-    const int tw = kd_wide(c) ? vk::KB_KD_TW_WIDE : vk::KB_KD_TW;
+    const int tw = kd_wide(c) ? vk::KD_TW_WIDE : vk::KB_KD_TW;
     return (int)((c->P.nx + tw - 1) / tw) * (int)c->nblk;
 }
 
 int drift_tiles(const vlasov_ctx *c)
 {
-    constexpr int TW = vk::DriftGeom<1, DRIFT_NT, DRIFT_V, 0>::TW;
-    return (int)((c->P.nx + TW - 1) / TW) * (int)c->nblk;
+    return (int)((c->P.nx + vk::DR_TW - 1) / vk::DR_TW) * (int)c->nblk;
 }
 
 int kick_tiles(const vlasov_ctx *c)
@@ -275,7 +274,7 @@ class Engine {
     template <typename T>
     hipError_t size_grids(int ncu)
     {
-        hipError_t e = resident(vk::kb_drift<T, DRIFT_NT, DRIFT_V, DRIFT_PF>, DRIFT_NT, ncu, wg_drift_);
+        hipError_t e = resident(vk::kb_drift<T>, vk::KDGeom<vk::DR_TW>::NT, ncu, wg_drift_);
         if (e == hipSuccess) e = resident(vk::kb_density, 256, ncu, wg_dens_);
         if (e == hipSuccess) e = resident(vk::kb_force, KB_FORCE_NT, ncu, wg_force_);
         if (e == hipSuccess) e = resident(vk::kb_kick<T, kick_rows<T>()>, 256, ncu, wg_kick_);
@@ -290,7 +289,7 @@ class Engine {
         const vk::GridDesc *gd = reinterpret_cast<const vk::GridDesc *>(dset);
         const vk::Cycle *cy = reinterpret_cast<const vk::Cycle *>(dset + sizeof(vk::GridDesc) * vk::BATCH_MAX);
         for (int k = 0; k < K_; ++k) {
-            vk::kb_drift<T, DRIFT_NT, DRIFT_V, DRIFT_PF><<<wg_drift_, DRIFT_NT, 0, st>>>(gd, cy + k);
+            vk::kb_drift<T><<<wg_drift_, vk::KDGeom<vk::DR_TW>::NT, 0, st>>>(gd, cy + k);
             vk::kb_density<<<wg_dens_, 256, 0, st>>>(gd, cy + k);
             vk::kb_force<<<wg_force_, KB_FORCE_NT, 0, st>>>(gd, cy + k);
             vk::kb_kick<T, kick_rows<T>()><<<wg_kick_, 256, 0, st>>>(gd, cy + k);

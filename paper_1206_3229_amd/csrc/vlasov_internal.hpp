@@ -29,8 +29,8 @@ int fail(int code, const std::string &msg);
 constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
-// drift launch shape: NT threads, runs of V columns, no trim, rows requested PF ahead
-constexpr int DRIFT_NT = 128, DRIFT_V = 2, DRIFT_PF = 4;
+// drift_threads of the default launch shape
+constexpr int DRIFT_NT = 128;
 // kick rows per thread (measured best on 4096^2: 16 for FP64, 32 for FP32)
 template <typename T> constexpr int kick_rows() { return sizeof(T) == 8 ? 16 : 32; }
 // fused kick and drift: default tile width and blocks; rows requested ahead by
@@ -105,13 +105,11 @@ struct vlasov_ctx {
     int nsub;
     double wsub[vlasov_detail::MAX_SUB];
     int64_t steps_done;
-    // kick k and the two half drifts after it (tables k, k+1 mod nsub) can run
-    // fused on tiles of kd_rb blocks (drift shifts of every tile within the
-    // kicked halo)
-    bool kd_ok[vlasov_detail::MAX_SUB];
-    // largest spread of the drift offsets o_j inside one such tile (the
-    // batched fused kernel has a wider-slack tile for spreads up to 56)
-    int64_t kd_spread[vlasov_detail::MAX_SUB];
+    // largest spread of the drift offsets inside one tile of kd_rb blocks: of
+    // the two half drifts after kick k (tables k, k+1 mod nsub; the fused
+    // kernel runs up to 8 columns, on narrower tiles 56), and of the half
+    // drift of table k alone (after the last kick of a call)
+    int64_t kd_spread[vlasov_detail::MAX_SUB], kd_spread1[vlasov_detail::MAX_SUB];
     int kd_rb;
     // profiling
     bool prof;
@@ -189,8 +187,9 @@ template <typename T> int launch_kick_filter(vlasov_ctx *c, double h);
 // Global spline: half drift of table `table` (and its partial sums); kick.
 template <typename T> int gs_drift_t(vlasov_ctx *c, int table, bool partials);
 template <typename T> int gs_kick_t(vlasov_ctx *c, double h);
-// Kick of substep ta (step size h) fused with the half drifts of tables ta
-// and ta + 1 mod nsub, on tiles of TW columns.
-template <typename T, int TW> int launch_kick_drift_w(vlasov_ctx *c, int ta, double h);
+// Kick of substep ta (step size h) fused with the half drifts of tables ta and
+// ta + 1 mod nsub (pair), or with that of table ta alone; `spread` (at most
+// KD_SPR_WIDE) is that of their offsets inside a tile.
+template <typename T> int launch_kick_drift(vlasov_ctx *c, int ta, bool pair, int64_t spread, double h);
 }  // namespace vlasov_detail
 

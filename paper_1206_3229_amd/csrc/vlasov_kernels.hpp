@@ -170,278 +170,6 @@ __device__ __forceinline__ bool xcd_tile(int ntx, int nty, int &tx, int &ty)
     return ty < nty;
 }
 
-// Two adjacent values as one 8- or 16-byte vector.
-template <typename T> struct Vec2;
-template <> struct Vec2<double> { using type = double2; };
-template <> struct Vec2<float> { using type = float2; };
-template <typename T> struct Vec4;
-template <> struct Vec4<double> { using type = double4; };
-template <> struct Vec4<float> { using type = float4; };
-
-// Interpolates the V adjacent outputs q = V u .. V u + V - 1 of a row from an
-// LDS window `src` (the sample at the start of output q's cell is src[q + 4]):
-// V + 1 stencils shared by the run, read as V/2 + 5 aligned pairs
-// src[V u .. V u + V + 9].
-template <typename T, int V>
-__device__ __forceinline__ void spline_run(const T *src, int u, T a, T b, T g, T d, T (&o)[V])
-{
-    using V2 = typename Vec2<T>::type;
-    static_assert(V % 2 == 0, "runs of even length");
-    const V2 *p = reinterpret_cast<const V2 *>(src) + (V / 2) * u;
-    T x[V + 10];
-#pragma unroll
-    for (int k = 0; k < V / 2 + 5; ++k) {
-        const V2 v = p[k];
-        x[2 * k] = v.x;
-        x[2 * k + 1] = v.y;
-    }
-    T D[V + 1];
-#pragma unroll
-    for (int k = 0; k <= V; ++k) D[k] = second_diff(x + 4 + k);
-#pragma unroll
-    for (int k = 0; k < V; ++k) o[k] = spline(a, b, g, d, x[4 + k], x[5 + k], D[k], D[k + 1]);
-}
-
-// Stores V adjacent outputs at row[i .. i + V), vectorised when aligned.
-template <typename T, int V>
-__device__ __forceinline__ void store_run(T *row, int i, int nx, const T (&o)[V])
-{
-    using V2 = typename Vec2<T>::type;
-    if (i + V <= nx && (nx & 1) == 0) {
-#pragma unroll
-        for (int k = 0; k < V; k += 2) {
-            V2 w;
-            w.x = o[k];
-            w.y = o[k + 1];
-            *reinterpret_cast<V2 *>(row + i + k) = w;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < V; ++k)
-            if (i + k < nx) row[i + k] = o[k];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Steps 1 and 4 (eqs. step1, step4): drift along x, row j shifted by the
-// constant p_j tau/dx cells.  NPASS = 2 applies two half drifts in turn (the
-// second half drift of one (sub)step and the first of the next, tables 1 and
-// 2: equal for the Strang splitting), keeping the intermediate row in LDS.
-// One workgroup of NT threads: TW consecutive columns of a block of 16
-// consecutive rows, runs of V adjacent columns per thread; TW = V NT - TRIM
-// (a trim keeps the TW + 9 intermediate values of the two-pass form within
-// one run per thread).  Rows stream through two LDS window
-// buffers; the window of each row (TW columns plus the stencil and shift halo,
-// periodic wrap or zeros) is requested PF rows ahead of its use and held in
-// registers meanwhile.  With PARTIALS, also writes the serial column sum of the
-// 16 output rows (density partial sums).
-// ---------------------------------------------------------------------------
-template <typename T, int BC, int NPASS, int TW, int NT, int NLD>
-__device__ __forceinline__ void load_window(const T *__restrict__ fin, const int32_t *__restrict__ dm1,
-                                            const int32_t *__restrict__ dm2, int j, int i0, int nx, T (&v)[NLD],
-                                            uint32_t &inside)
-{
-    // Branch-free: every thread issues NLD loads at valid addresses (periodic
-    // positions wrapped, zero-extended ones clamped; slots past the window
-    // load a duplicate that is never used). For zero extension bit k of
-    // `inside` says whether slot k lies in the grid; the zero is applied when
-    // the value is written to LDS, not here, so that no use of a loaded value
-    // sits next to its load and the loads of the rows requested ahead stay in
-    // flight.
-    const T *row = fin + (size_t)j * nx;
-    int base = i0 + (NPASS == 2 ? dm1[j] + dm2[j] : dm1[j]) - 4 * NPASS;
-    if (BC == BC_PERIODIC) base = wrap(base, nx);
-    inside = 0;
-#pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-        const int s = threadIdx.x + k * NT;
-        int q = base + s;
-        if (BC == BC_PERIODIC) {
-            q = q >= nx ? q - nx : q;
-            q = q >= nx ? wrap(q, nx) : q;
-            v[k] = row[q];
-        } else {
-            v[k] = row[min(max(q, 0), nx - 1)];
-            inside |= (uint32_t)(q >= 0 && q < nx) << k;
-        }
-    }
-}
-
-// Geometry of a drift tile: NT threads, runs of V columns, TW = V NT - TRIM
-// columns; buffer sizes of the row window and of the first-pass row.
-template <int NPASS, int NT, int V, int TRIM>
-struct DriftGeom {
-    static constexpr int TW = V * NT - TRIM;
-    static constexpr int WIN = TW + 9 * NPASS;        // window samples per row
-    static constexpr int MIDN = TW + 9;               // first-pass outputs per row (NPASS = 2)
-    static constexpr int NRUN1 = (MIDN + V - 1) / V;  // first-pass runs per row
-    static constexpr int NLD = (WIN + NT - 1) / NT;   // loads per thread per row
-    // runs read V + 10 samples from V u: pad the buffers past the last run
-    static constexpr int LDW = ((NPASS == 2 ? NRUN1 * V : TW) + 10 + 1) & ~1;
-    static constexpr int MIDW = NRUN1 * V > TW + 10 ? NRUN1 * V : TW + 10;
-    static constexpr int LDM = NPASS == 2 ? (MIDW + 1) & ~1 : 2;
-    // allocation pitch of a window buffer: slot LDW takes the writes of lanes
-    // past the window, so that the LDS write (the only use of a prefetched
-    // value) is unconditional and the compiler cannot sink the load into a
-    // branch next to it
-    static constexpr int LDA = LDW + 2;
-    static_assert(TRIM % V == 0 && TW > 0, "tile width a positive multiple of the run");
-    static_assert(LDW >= WIN, "window buffer");
-};
-
-template <int NT, int V, int TRIM>
-struct DriftShape {
-    static constexpr int TW = V * NT - TRIM;
-};
-
-// One drift tile (columns [tx TW, (tx+1) TW) of rows [16 ty, 16 ty + 16)).
-// win: two LDS row buffers of at least LDA entries each, mid: LDS row of LDM
-// (NPASS = 2).
-// FULL: the tile has all 16 rows and all TW columns inside the grid and nx is
-// even; then the row loop is straight-line code (no branch around a memory
-// access), which lets the loads requested ahead stay in flight.
-template <typename T, int NPASS, int BC, bool PARTIALS, int NT, int V, int TRIM, int PF, bool FULL>
-__device__ __forceinline__ void drift_tile(const T *__restrict__ fin, T *__restrict__ fout,
-                                           const int32_t *__restrict__ dm1, const double4 *__restrict__ dw1,
-                                           const int32_t *__restrict__ dm2, const double4 *__restrict__ dw2,
-                                           double *__restrict__ part, int nx, int np, int tx, int ty, T *win0,
-                                           T *win1, T *mid)
-{
-    using G = DriftGeom<NPASS, NT, V, TRIM>;
-    constexpr int R = ROWS_PER_BLOCK;
-    constexpr int TW = G::TW, WIN = G::WIN, MIDN = G::MIDN, NRUN1 = G::NRUN1, NLD = G::NLD, LDW = G::LDW,
-                  LDM = G::LDM;
-    const int t = threadIdx.x;
-    const int i0 = tx * TW;
-    const int j0 = ty * R;
-    const int nr = FULL ? R : min(R, np - j0);
-
-    for (int s = WIN + t; s < LDW; s += NT) {
-        win0[s] = T(0);
-        win1[s] = T(0);
-    }
-    if (NPASS == 2)
-        for (int s = MIDN + t; s < LDM; s += NT) mid[s] = T(0);
-
-    T v[PF][NLD];
-    uint32_t inside[PF];
-    static_assert(NLD <= 32, "one bit per loaded slot");
-#pragma unroll
-    for (int r = 0; r < PF; ++r)
-        if (FULL || r < nr) load_window<T, BC, NPASS, TW, NT, NLD>(fin, dm1, dm2, j0 + r, i0, nx, v[r], inside[r]);
-
-    const int i = i0 + V * t;                // first of this thread's V columns
-    const bool own = FULL || V * t < TW;     // trailing threads own no output when TRIM > 0
-    double acc[V];
-#pragma unroll
-    for (int k = 0; k < V; ++k) acc[k] = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (FULL || r < nr) {
-            T *wrow = (r & 1) ? win1 : win0;
-#pragma unroll
-            for (int k = 0; k < NLD; ++k) {
-                // slots k < NLD - 1 always lie in the window (t < NT)
-                const int s = t + k * NT;
-                const T x = v[r % PF][k];
-                wrow[k < NLD - 1 || s < WIN ? s : LDW] = BC == BC_PERIODIC || (inside[r % PF] >> k & 1u) ? x : T(0);
-            }
-            if (FULL ? r + PF < R : r + PF < nr)
-                load_window<T, BC, NPASS, TW, NT, NLD>(fin, dm1, dm2, j0 + r + PF, i0, nx, v[r % PF],
-                                                       inside[r % PF]);
-            __syncthreads();
-            const int j = j0 + r;
-            const double4 w = (NPASS == 2 ? dw2 : dw1)[j];
-            const T a = (T)w.x, b = (T)w.y, g = (T)w.z, d = (T)w.w;
-            const T *src = wrow;
-            if (NPASS == 2) {
-                // first half drift (table 1) at the positions i0 + m - 4 + q,
-                // q in [0, TW + 9), that the second (table 2, offset m) reads
-                const int m = dm2[j];
-                const double4 w1 = dw1[j];
-                const T a1 = (T)w1.x, b1 = (T)w1.y, g1 = (T)w1.z, d1 = (T)w1.w;
-                for (int u = t; u < NRUN1; u += NT) {
-                    T o[V];
-                    spline_run<T, V>(src, u, a1, b1, g1, d1, o);
-                    if (BC == BC_ZERO) {
-                        const int q = i0 + m - 4 + V * u;
-#pragma unroll
-                        for (int k = 0; k < V; ++k)
-                            if (q + k < 0 || q + k >= nx) o[k] = T(0);
-                    }
-#pragma unroll
-                    for (int k = 0; k < V; k += 2) {
-                        typename Vec2<T>::type ww;
-                        ww.x = o[k];
-                        ww.y = o[k + 1];
-                        reinterpret_cast<typename Vec2<T>::type *>(mid + V * u)[k / 2] = ww;
-                    }
-                }
-                __syncthreads();
-                src = mid;
-            }
-            if (own) {
-                T o[V];
-                spline_run<T, V>(src, t, a, b, g, d, o);
-                if (FULL) {
-#pragma unroll
-                    for (int k = 0; k < V; k += 2) {
-                        typename Vec2<T>::type ww;
-                        ww.x = o[k];
-                        ww.y = o[k + 1];
-                        *reinterpret_cast<typename Vec2<T>::type *>(fout + (size_t)j * nx + i + k) = ww;
-                    }
-                } else {
-                    store_run<T, V>(fout + (size_t)j * nx, i, nx, o);
-                }
-                if (PARTIALS) {
-#pragma unroll
-                    for (int k = 0; k < V; ++k) acc[k] = acc[k] + (double)o[k];
-                }
-            }
-        }
-    }
-    if (PARTIALS && own) {
-        double *prow = part + (size_t)ty * nx;
-#pragma unroll
-        for (int k = 0; k < V; ++k)
-            if (FULL || i + k < nx) prow[i + k] = acc[k];
-    }
-}
-
-// Full tiles take the straight-line form, edge tiles the guarded one.
-template <typename T, int NPASS, int BC, bool PARTIALS, int NT, int V, int TRIM, int PF>
-__device__ __forceinline__ void drift_tile_any(const T *__restrict__ fin, T *__restrict__ fout,
-                                               const int32_t *__restrict__ dm1, const double4 *__restrict__ dw1,
-                                               const int32_t *__restrict__ dm2, const double4 *__restrict__ dw2,
-                                               double *__restrict__ part, int nx, int np, int tx, int ty, T *win0,
-                                               T *win1, T *mid)
-{
-    constexpr int TW = DriftGeom<NPASS, NT, V, TRIM>::TW;
-    const bool full = (ty + 1) * ROWS_PER_BLOCK <= np && (tx + 1) * TW <= nx && (nx & 1) == 0;
-    if (full)
-        drift_tile<T, NPASS, BC, PARTIALS, NT, V, TRIM, PF, true>(fin, fout, dm1, dw1, dm2, dw2, part, nx, np, tx, ty,
-                                                                  win0, win1, mid);
-    else
-        drift_tile<T, NPASS, BC, PARTIALS, NT, V, TRIM, PF, false>(fin, fout, dm1, dw1, dm2, dw2, part, nx, np, tx, ty,
-                                                                   win0, win1, mid);
-}
-
-template <typename T, int NPASS, int BC, bool PARTIALS, int NT, int V, int TRIM, int PF>
-static __global__ __launch_bounds__(NT) void k_drift(const T *__restrict__ fin, T *__restrict__ fout,
-                                              const int32_t *__restrict__ dm1, const double4 *__restrict__ dw1,
-                                              const int32_t *__restrict__ dm2, const double4 *__restrict__ dw2,
-                                              double *__restrict__ part, int nx, int np, int ntx, int nty)
-{
-    using G = DriftGeom<NPASS, NT, V, TRIM>;
-    __shared__ __attribute__((aligned(16))) T win[2][G::LDA];
-    __shared__ __attribute__((aligned(16))) T mid[G::LDM];
-    int tx, ty;
-    if (!xcd_tile(ntx, nty, tx, ty)) return;
-    drift_tile_any<T, NPASS, BC, PARTIALS, NT, V, TRIM, PF>(fin, fout, dm1, dw1, dm2, dw2, part, nx, np, tx, ty, win[0],
-                                                            win[1], mid);
-}
-
 // ---------------------------------------------------------------------------
 // Step 3 (eq. step3): kick along p, column i shifted by F_i dt/dp cells.  One
 // thread per column and R consecutive output rows; the R + 9 samples of the
@@ -610,14 +338,16 @@ static __global__ __launch_bounds__(256) void k_kick_filter(const T *__restrict_
 // 2048^2 22.2 -> 20.9, 4096^2 65.9 -> 64.2 (FP32 42.1 -> 38.4).
 // ---------------------------------------------------------------------------
 constexpr int KD_SPR = 8;
+// tiles for offsets that spread more (coarse p, fine x, long steps): the same
+// kicked columns for fewer outputs
+constexpr int KD_TW_WIDE = 182, KD_SPR_WIDE = 56;
 // rows per barrier interval, and density blocks of a tile at most (the rows of
 // a tile fit one per lane)
 constexpr int KD_RPI = 2;
 constexpr int KD_MAX_BLOCKS = 4;
 
-// What follows the kick: both half drifts with density partial sums, or one
-// half drift without.
-enum { KD_PAIR = 0, KD_LAST = 1 };
+// Where the drifted rows come from: kicked from f, or f itself.
+enum { KD_KICK = 0, KD_LOAD = 1 };
 
 // Geometry of a fused tile of TW columns whose rows' windows lie within SPR
 // columns of slack: WK waves kick the KW = TW + 18 + SPR columns the windows
@@ -634,6 +364,7 @@ struct KDGeom {
     static constexpr int WK = (KW + 63) / 64;
     static constexpr int W1 = (NRUN1 + 31) / 32, W2 = (NRUN2 + 31) / 32;
     static constexpr int NTK = 64 * WK, NT = 64 * (WK + W1 + W2);  // kicking lanes, threads
+    static constexpr int NT1 = 64 * (WK + W2);                     // threads with one half drift
     static constexpr int R1 = (NRUN1 + W1 - 1) / W1, R2 = (NRUN2 + W2 - 1) / W2;  // runs per wave and row
     static constexpr int NBUF = 2 * KD_RPI;                  // rows in each LDS ring
     // Rows are held in groups of four values (KDRow).  Column c of the kicked
@@ -643,10 +374,12 @@ struct KDGeom {
     static constexpr int ROWLD = 4 * NG;                     // values per row
     // Part of wave w in workgroup `rot`: the kicking waves come first, so that
     // each SIMD gets kicking and drifting waves alike; the two drifts change
-    // places from one workgroup to the next.
-    static __device__ __forceinline__ int part(int w, int rot)
+    // places from one workgroup to the next.  With one half drift the waves
+    // past the kicking ones run it (those of a larger workgroup idle).
+    template <int NPASS> static __device__ __forceinline__ int part(int w, int rot)
     {
         if (w < WK) return w;
+        if (NPASS == 1) return w + W1 < WK + W1 + W2 ? w + W1 : WK;
         const int d = w - WK + (rot & 1) * W1;
         return WK + (d < W1 + W2 ? d : d - (W1 + W2));
     }
@@ -764,27 +497,36 @@ struct KDTile {
     T *fout;
     const double *F;
     double dt, dp;
-    const int32_t *dm;  // offsets of the half drift whose result is stored
+    const int32_t *dm1, *dm2;  // offsets of the half drifts in turn (the first one only with one pass)
     const double4 *dw1, *dw2;
     const int32_t *kbase, *krel;
-    double *part;
+    double *part;  // density partial sums of the result (NULL: none)
     int nx, np, nb, tx, ty;
     T *kbuf, *mbuf, *wtab;  // LDS: rings of NBUF rows of ROWLD values, 8 weights for each of the 16 nb rows
 };
 
-// Row offsets of a tile, one row per lane (a tile has at most 64 rows): the
-// window's start in the kicked range (rel_v), and the first kicked column.
-template <int MODE, int BCX, typename T>
+// Row of a tile that lane `lane` holds the offsets of (a tile has at most 64
+// rows; lanes past the last one repeat it).
+template <typename T>
+__device__ __forceinline__ int kd_row(const KDTile<T> &a, int lane)
+{
+    const int j0 = a.ty * (ROWS_PER_BLOCK * a.nb);
+    return min(j0 + lane, min(j0 + ROWS_PER_BLOCK * a.nb, a.np) - 1);
+}
+
+// Row offsets of a tile, one row per lane: the window's start in the kicked
+// range (rel_v), and the first kicked column.
+template <int NPASS, int BCX, typename T>
 __device__ __forceinline__ void kd_rows(const KDTile<T> &a, int i0, int jl, int &rel_v, int &cL)
 {
-    if (MODE == KD_PAIR) {
+    if (NPASS == 2) {
         rel_v = a.krel[jl];
         cL = i0 + a.kbase[a.ty];
     } else {
         // offsets of the single half drift relative to their minimum over the
         // tile (the host checked that they spread by at most SPR columns; on a
         // periodic axis of nx >= 4 SPR they are known mod nx)
-        const int dm = a.dm[jl];
+        const int dm = a.dm1[jl];
         const int ref = __builtin_amdgcn_readfirstlane(dm);
         int d = dm - ref;
         if (BCX == BC_PERIODIC) {
@@ -800,18 +542,18 @@ __device__ __forceinline__ void kd_rows(const KDTile<T> &a, int i0, int jl, int 
 }
 
 // The kicking waves: lane t kicks column cL + t of every row of the tile.
-template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int MODE>
+template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int NPASS>
 __device__ __forceinline__ void kd_kick_part(const KDTile<T> &a, int t)
 {
     using G = KDGeom<TW, SPR>;
     constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NI = R / P, NB = G::NBUF;
     constexpr int NS = R + 10 + PF;  // window slots: samples of a block plus those requested ahead
-    constexpr int LAG = MODE == KD_PAIR ? 2 : 1;
+    constexpr int LAG = NPASS;
     static_assert(PF % P == 0 && NS <= 32, "whole requests per interval, one mask bit per sample");
     const int nx = a.nx, np = a.np, i0 = a.tx * TW, j0 = a.ty * (R * a.nb);
     const int nblk = (min(R * a.nb, np - j0) + R - 1) / R;
     int rel_v, cL;
-    kd_rows<MODE, BCX>(a, i0, min(j0 + (t & 63), np - 1), rel_v, cL);
+    kd_rows<NPASS, BCX>(a, i0, kd_row(a, t & 63), rel_v, cL);
     const int pad_v = 4 * ((rel_v + 3) >> 2) - rel_v;
 
     // Foot of the column's p shift (eq. step3), the spline weights, and the
@@ -915,8 +657,68 @@ __device__ __forceinline__ void kd_kick_part(const KDTile<T> &a, int t)
     for (int k = 0; k < LAG; ++k) __syncthreads();
 }
 
+// The loading waves of the drifts alone: lane t loads sample t of every row's
+// own window, which starts at column i0 + o_j - 4 NPASS, PF rows ahead.
+template <typename T, int BCX, int TW, int SPR, int NPASS>
+__device__ __forceinline__ void kd_load_part(const KDTile<T> &a, int t)
+{
+    using G = KDGeom<TW, SPR>;
+    constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NI = R / P, NB = G::NBUF, PF = 8;
+    static_assert(R % PF == 0 && PF % P == 0, "requested rows in the same registers block after block");
+    const int nx = a.nx, np = a.np, i0 = a.tx * TW, j0 = a.ty * (R * a.nb);
+    const int nblk = (min(R * a.nb, np - j0) + R - 1) / R;
+    const int jl = kd_row(a, t & 63);
+    int b_v = i0 + a.dm1[jl] + (NPASS == 2 ? a.dm2[jl] : 0) - 4 * NPASS;
+    bool xin = true;
+    int tm = t;  // periodic: sample t of a window that starts at b in [0, nx) is b + tm, less nx once past the end
+    if (BCX == BC_PERIODIC) {
+        b_v = wrap(b_v, nx);
+        tm = t < nx ? t : wrap(t, nx);
+    } else {
+        xin = __all(b_v >= 0 && b_v + G::NTK <= nx);
+    }
+    const size_t ld = (size_t)nx;
+    T v[PF];
+    auto column = [&](int r) { return __builtin_amdgcn_readlane(b_v, r) + tm; };
+    auto request = [&](int r, int slot) {
+        int c = column(r);
+        if (BCX == BC_PERIODIC)
+            c = (int)min((unsigned)c, (unsigned)(c - nx));
+        else
+            c = min(max(c, 0), nx - 1);
+        v[slot] = a.fin[(size_t)min(j0 + r, np - 1) * ld + (size_t)(unsigned)c];
+    };
+#pragma unroll
+    for (int r = 0; r < PF; ++r) request(r, r);
+    T *dst = a.kbuf + KDRow<T>::at(t, G::NG);
+    for (int blk = 0; blk < nblk; ++blk) {
+        const bool more = blk + 1 < nblk;  // uniform
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+#pragma unroll
+            for (int s = 0; s < P; ++s) {
+                const int r = P * it + s;
+                T y = v[r % PF];
+                if (BCX == BC_ZERO && !xin) {
+                    const int c = column(R * blk + r);
+                    y = c >= 0 && c < nx ? y : T(0);
+                    __asm__ __volatile__("");  // a branch of the edge tiles, not a select in all
+                }
+                dst[(r & (NB - 1)) * LD] = y;
+            }
+            if (P * it + PF < R || more) {
+#pragma unroll
+                for (int s = 0; s < P; ++s) request(R * blk + P * it + s + PF, (P * it + s) % PF);
+            }
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NPASS; ++k) __syncthreads();
+}
+
 // The waves of the first half drift of a pair: wave w1 of W1.
-template <typename T, int BCX, int TW, int SPR>
+template <typename T, int BCX, int TW, int SPR, int SRC>
 __device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
 {
     using G = KDGeom<TW, SPR>;
@@ -925,12 +727,12 @@ __device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
     const int nblk = (min(R * a.nb, np - j0) + R - 1) / R;
     const int lane = threadIdx.x & 63, l32 = lane & 31;
     const bool hi = lane >= 32;
-    const int jl = min(j0 + lane, np - 1);
-    const int st_v = 4 * ((a.krel[jl] + 3) >> 2);  // slot where the row's window starts, in elements of its first half
+    const int jl = kd_row(a, lane);
+    const int st_v = SRC == KD_KICK ? (a.krel[jl] + 3) >> 2 : 0;  // group where the row's window starts
     int dm_v = 0;
     bool xin = true;  // no value of the tile lies outside the grid
     if (BCX == BC_ZERO) {
-        dm_v = a.dm[jl];
+        dm_v = a.dm2[jl];
         const int lo = i0 + dm_v - 4;
         xin = __all(lo >= 0 && lo + 4 * G::NRUN1 <= nx);
     }
@@ -942,9 +744,13 @@ __device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
 #pragma unroll 2
     for (int it = 0; it < nblk * (R / P); ++it) {
         const int qs = (P * it) & (NB - 1);  // ring slot of the pair's first row
-        const int sa = __builtin_amdgcn_readlane(st_v, P * it), sb = __builtin_amdgcn_readlane(st_v, P * it + 1);
         T x[16], wr[4], o[4];
-        KDRow<T>::template read<G::NG>(src + qs * LD, ((hi ? sb : sa) >> 2) + u, x);
+        int g = u;
+        if (SRC == KD_KICK) {
+            const int sa = __builtin_amdgcn_readlane(st_v, P * it), sb = __builtin_amdgcn_readlane(st_v, P * it + 1);
+            g += hi ? sb : sa;
+        }
+        KDRow<T>::template read<G::NG>(src + qs * LD, g, x);
         KDRow<T>::weights(wt, wr);
         wt += 8 * P;
         spline_run4<T>(x, wr[0], wr[1], wr[2], wr[3], o);
@@ -962,28 +768,30 @@ __device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
 }
 
 // The waves of the half drift whose result is stored: wave w2 of W2.
-template <typename T, int BCX, int TW, int SPR, int MODE>
+template <typename T, int BCX, int TW, int SPR, int SRC, int NPASS>
 __device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
 {
     using G = KDGeom<TW, SPR>;
     constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NB = G::NBUF, NI = R / P;
-    constexpr int LAG = MODE == KD_PAIR ? 2 : 1;
+    constexpr int LAG = NPASS;
+    constexpr bool ROWS = SRC == KD_KICK && NPASS == 1;  // windows start at their offset in the kicked range
     const int nx = a.nx, np = a.np, i0 = a.tx * TW, j0 = a.ty * (R * a.nb);
     const int nr = min(R * a.nb, np - j0), nblk = (nr + R - 1) / R;
     const int lane = threadIdx.x & 63, l32 = lane & 31;
     const bool hi = lane >= 32;
     int st_v = 0, cL;
-    if (MODE == KD_LAST) {
-        kd_rows<MODE, BCX>(a, i0, min(j0 + lane, np - 1), st_v, cL);
-        st_v = 4 * ((st_v + 3) >> 2);
+    if (ROWS) {
+        kd_rows<NPASS, BCX>(a, i0, kd_row(a, lane), st_v, cL);
+        st_v = (st_v + 3) >> 2;
     }
     const int u = min(G::R2 * w2 + min(l32, G::R2 - 1), G::NRUN2 - 1);
     const int i = i0 + 4 * u + (hi ? 2 : 0);  // this lane stores columns i and i + 1
     const bool own = l32 < G::R2 && G::R2 * w2 + l32 < G::NRUN2;
     const int left = own ? min(i0 + TW, nx) - i : 0;
+    const bool sums = a.part != nullptr;  // uniform
     const bool two = left >= 2, one = left == 1, anyone = __any(one);
-    const T *src = (MODE == KD_PAIR ? a.mbuf : a.kbuf) + (hi ? LD : 0);
-    const T *wt = a.wtab + (hi ? 8 : 0) + (MODE == KD_PAIR ? 4 : 0);
+    const T *src = (NPASS == 2 ? a.mbuf : a.kbuf) + (hi ? LD : 0);
+    const T *wt = a.wtab + (hi ? 8 : 0) + (NPASS == 2 ? 4 : 0);
     const uint32_t io = (uint32_t)i * (uint32_t)sizeof(T), ios = (uint32_t)i * (uint32_t)sizeof(double);  // bytes
     const size_t ld = (size_t)nx, ldb = ld * sizeof(T);
     char *out = reinterpret_cast<char *>(a.fout + (size_t)j0 * ld);  // row stored next
@@ -997,9 +805,9 @@ __device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
             const int qs = (P * it) & (NB - 1);
             T x[16], wr[4], o[4];
             int g = u;
-            if (MODE == KD_LAST) {
+            if (ROWS) {
                 const int sa = __builtin_amdgcn_readlane(st_v, row), sb = __builtin_amdgcn_readlane(st_v, row + 1);
-                g += (hi ? sb : sa) >> 2;
+                g += hi ? sb : sa;
             }
             KDRow<T>::template read<G::NG>(src + qs * LD, g, x);
             KDRow<T>::weights(wt, wr);
@@ -1021,71 +829,115 @@ __device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
                         outa[0] = o[0];
                         outb[0] = o[2];
                     }
-                if (MODE == KD_PAIR) {
+                if (sums) {
                     acc0 = (acc0 + (double)o[0]) + (double)o[2];
                     acc1 = (acc1 + (double)o[1]) + (double)o[3];
                 }
             } else if (row < nr) {
                 if (two) store2(outa, o[0], o[1]);
                 if (one) outa[0] = o[0];
-                if (MODE == KD_PAIR) {
+                if (sums) {
                     acc0 = acc0 + (double)o[0];
                     acc1 = acc1 + (double)o[1];
                 }
             }
             __syncthreads();
         }
-        if (MODE == KD_PAIR) {
-            double *sums = reinterpret_cast<double *>(reinterpret_cast<char *>(a.part + (size_t)(a.ty * a.nb + blk) * ld) + ios);
-            if (two) store2(sums, acc0, acc1);
-            if (one) sums[0] = acc0;
+        if (sums) {
+            double *srow = reinterpret_cast<double *>(reinterpret_cast<char *>(a.part + (size_t)(a.ty * a.nb + blk) * ld) + ios);
+            if (two) store2(srow, acc0, acc1);
+            if (one) srow[0] = acc0;
         }
     }
 }
 
-// One tile, by a workgroup of KDGeom::NT threads.
-template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int MODE>
+// The waves without a part in a tile of one half drift.
+template <int NPASS, typename T>
+__device__ __forceinline__ void kd_no_part(const KDTile<T> &a)
+{
+    constexpr int R = ROWS_PER_BLOCK;
+    const int nblk = (min(R * a.nb, a.np - a.ty * (R * a.nb)) + R - 1) / R;
+    for (int k = 0; k < nblk * (R / KD_RPI) + NPASS; ++k) __syncthreads();
+}
+
+// One tile, by a workgroup of KDGeom::NT threads (or NT1 with one half drift).
+// SRC KD_KICK: the rows kicked, KD_LOAD: the rows of f (BCP, PF unused); then
+// NPASS half drifts.  rot: number of the workgroup.
+template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int SRC, int NPASS>
 __device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot)
 {
     using G = KDGeom<TW, SPR>;
     constexpr int R = ROWS_PER_BLOCK;
-    const int p = G::part((int)threadIdx.x >> 6, rot);
+    const int p = G::template part<NPASS>((int)threadIdx.x >> 6, rot);
     if (p < G::WK) {
-        kd_kick_part<T, BCX, BCP, TW, SPR, PF, MODE>(a, (int)threadIdx.x);
+        if (SRC == KD_KICK)
+            kd_kick_part<T, BCX, BCP, TW, SPR, PF, NPASS>(a, (int)threadIdx.x);
+        else
+            kd_load_part<T, BCX, TW, SPR, NPASS>(a, (int)threadIdx.x);
     } else {
         // row weights, both passes of a row adjacent
         const int j0 = a.ty * (R * a.nb);
         const int n = 2 * R * ((min(R * a.nb, a.np - j0) + R - 1) / R);
-        for (int k = threadIdx.x - G::NTK; k < n; k += G::NT - G::NTK) {
-            const double4 w = (MODE == KD_PAIR && (k & 1) ? a.dw2 : a.dw1)[min(j0 + (k >> 1), a.np - 1)];
+        for (int k = threadIdx.x - G::NTK; k < n; k += blockDim.x - G::NTK) {
+            const double4 w = (NPASS == 2 && (k & 1) ? a.dw2 : a.dw1)[min(j0 + (k >> 1), a.np - 1)];
             a.wtab[4 * k] = (T)w.x;
             a.wtab[4 * k + 1] = (T)w.y;
             a.wtab[4 * k + 2] = (T)w.z;
             a.wtab[4 * k + 3] = (T)w.w;
         }
-        if (MODE == KD_PAIR && p < G::WK + G::W1)
-            kd_first_part<T, BCX, TW, SPR>(a, p - G::WK);
-        else if (p >= G::WK + G::W1)
-            kd_second_part<T, BCX, TW, SPR, MODE>(a, p - G::WK - G::W1);
+        if (p >= G::WK + G::W1)
+            kd_second_part<T, BCX, TW, SPR, SRC, NPASS>(a, p - G::WK - G::W1);
+        else if (NPASS == 2)
+            kd_first_part<T, BCX, TW, SPR, SRC>(a, p - G::WK);
+        else
+            kd_no_part<NPASS>(a);
     }
 }
 
-template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int MODE>
-static __global__ __launch_bounds__((KDGeom<TW, SPR>::NT)) __attribute__((amdgpu_waves_per_eu(8)))
+template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int NPASS>
+static __global__ __launch_bounds__((NPASS == 2 ? KDGeom<TW, SPR>::NT : KDGeom<TW, SPR>::NT1))
+__attribute__((amdgpu_waves_per_eu(8)))
 void k_kick_drift(
     const T *__restrict__ fin, T *__restrict__ fout, const double *__restrict__ F, double dt, double dp,
-    const int32_t *__restrict__ dmL, const double4 *__restrict__ dw1, const double4 *__restrict__ dw2,
-    const int32_t *__restrict__ kbase, const int32_t *__restrict__ krel, double *__restrict__ part, int nx, int np,
-    int nb, int ntx, int nty)
+    const int32_t *__restrict__ dm1, const int32_t *__restrict__ dm2, const double4 *__restrict__ dw1,
+    const double4 *__restrict__ dw2, const int32_t *__restrict__ kbase, const int32_t *__restrict__ krel,
+    double *__restrict__ part, int nx, int np, int nb, int ntx, int nty)
 {
     using G = KDGeom<TW, SPR>;
-    __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];                         // ring of kicked rows
-    __shared__ __attribute__((aligned(16))) T mbuf[MODE == KD_PAIR ? G::NBUF * G::ROWLD : 4];  // of first-pass rows
+    __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];                    // ring of kicked rows
+    __shared__ __attribute__((aligned(16))) T mbuf[NPASS == 2 ? G::NBUF * G::ROWLD : 4];  // of first-pass rows
     __shared__ __attribute__((aligned(16))) T wtab[8 * ROWS_PER_BLOCK * KD_MAX_BLOCKS];
     int tx, ty;
     if (!xcd_tile(ntx, nty, tx, ty)) return;
-    const KDTile<T> a{fin, fout, F, dt, dp, dmL, dw1, dw2, kbase, krel, part, nx, np, nb, tx, ty, kbuf, mbuf, wtab};
-    kick_drift_tile<T, BCX, BCP, TW, SPR, PF, MODE>(a, (int)blockIdx.x);
+    const KDTile<T> a{fin, fout, F, dt, dp, dm1, dm2, dw1, dw2, kbase, krel, part, nx, np, nb, tx, ty, kbuf, mbuf, wtab};
+    kick_drift_tile<T, BCX, BCP, TW, SPR, PF, KD_KICK, NPASS>(a, (int)blockIdx.x);
+}
+
+// Steps 1 and 4 (eqs. step1, step4) without a kick before them: drift along x,
+// row j shifted by the constant p_j tau/dx cells, once or (NPASS = 2, tables 1
+// and 2) twice in turn; the tiles of the fused kernel with the rows' windows
+// loaded instead of kicked.  Latency-bound on small grids (64^2: 5.3 us; 12.7
+// with a workgroup of two waves that waited for each row of an edge tile),
+// near the copy rate on large ones (4096^2 FP64 48.4 us, 50.6 before; FP32
+// 27.6, 25.7 before).
+constexpr int DR_TW = 230;
+template <typename T, int BCX, int NPASS>
+static __global__ __launch_bounds__((NPASS == 2 ? KDGeom<DR_TW>::NT : KDGeom<DR_TW>::NT1))
+__attribute__((amdgpu_waves_per_eu(8)))
+void k_drift(
+    const T *__restrict__ fin, T *__restrict__ fout, const int32_t *__restrict__ dm1, const int32_t *__restrict__ dm2,
+    const double4 *__restrict__ dw1, const double4 *__restrict__ dw2, double *__restrict__ part, int nx, int np, int nb,
+    int ntx, int nty)
+{
+    using G = KDGeom<DR_TW>;
+    __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];
+    __shared__ __attribute__((aligned(16))) T mbuf[NPASS == 2 ? G::NBUF * G::ROWLD : 4];
+    __shared__ __attribute__((aligned(16))) T wtab[8 * ROWS_PER_BLOCK * KD_MAX_BLOCKS];
+    int tx, ty;
+    if (!xcd_tile(ntx, nty, tx, ty)) return;
+    const KDTile<T> a{fin, fout, nullptr, 0.0, 0.0, dm1, dm2, dw1, dw2, nullptr, nullptr, part, nx, np, nb, tx, ty, kbuf,
+                      mbuf, wtab};
+    kick_drift_tile<T, BCX, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, NPASS>(a, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1900,14 +1752,14 @@ __device__ __forceinline__ int find_member(const int32_t *off, int n, int e)
     return lo;
 }
 
-template <typename T, int NT, int V, int PF>
-static __global__ __launch_bounds__(NT) void kb_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
+template <typename T>
+static __global__ __launch_bounds__(KDGeom<DR_TW>::NT) __attribute__((amdgpu_waves_per_eu(8)))
+void kb_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
 {
-    using G1 = DriftGeom<1, NT, V, 0>;
-    using G2 = DriftGeom<2, NT, V, 0>;
-    constexpr int LDA = G1::LDA > G2::LDA ? G1::LDA : G2::LDA;
-    __shared__ __attribute__((aligned(16))) T win[2][LDA];
-    __shared__ __attribute__((aligned(16))) T mid[G2::LDM];
+    using G = KDGeom<DR_TW>;
+    __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];
+    __shared__ __attribute__((aligned(16))) T mbuf[G::NBUF * G::ROWLD];
+    __shared__ __attribute__((aligned(16))) T wtab[8 * ROWS_PER_BLOCK];
     const int n = cy->n;
     const int total = cy->off_drift[n];
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
@@ -1915,30 +1767,22 @@ static __global__ __launch_bounds__(NT) void kb_drift(const GridDesc *__restrict
         const GridDesc &g = gd[cy->slot[a]];
         const int kind = cy->drift[a], cur = cy->cur[a];
         const int li = e - cy->off_drift[a];
-        const int ntx = (g.nx + G1::TW - 1) / G1::TW;
-        const int tx = li % ntx, ty = li / ntx;
-        const T *fin = (const T *)g.f[cur];
-        T *fout = (T *)g.f[cur ^ 1];
-        __syncthreads();
-#define BD(NP, BC, PT)                                                                                               \
-    drift_tile_any<T, NP, BC, PT, NT, V, 0, PF>(fin, fout, g.dm, g.dw, g.dm, g.dw, g.part, g.nx, g.np, tx, ty, win[0],   \
-                                                win[1], mid)
+        const int ntx = (g.nx + DR_TW - 1) / DR_TW;
+        __syncthreads();  // the previous item's LDS rows are consumed
+        const KDTile<T> t{(const T *)g.f[cur], (T *)g.f[cur ^ 1], nullptr, 0.0, 0.0, g.dm, g.dm, g.dw, g.dw, nullptr,
+                          nullptr, kind == DRIFT_LAST ? nullptr : g.part, g.nx, g.np, 1, li % ntx, li / ntx, kbuf, mbuf,
+                          wtab};
         if (g.bc_x == BC_PERIODIC) {
             if (kind == DRIFT_PAIR)
-                BD(2, BC_PERIODIC, true);
-            else if (kind == DRIFT_FIRST)
-                BD(1, BC_PERIODIC, true);
+                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 2>(t, e);
             else
-                BD(1, BC_PERIODIC, false);
+                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 1>(t, e);
         } else {
             if (kind == DRIFT_PAIR)
-                BD(2, BC_ZERO, true);
-            else if (kind == DRIFT_FIRST)
-                BD(1, BC_ZERO, true);
+                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 2>(t, e);
             else
-                BD(1, BC_ZERO, false);
+                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 1>(t, e);
         }
-#undef BD
     }
 }
 
@@ -2030,13 +1874,12 @@ static __global__ __launch_bounds__(256) void kb_kick(const GridDesc *__restrict
 // x, long steps), tiles of 182 columns with 56 of slack (the same 256 kicked
 // columns and four waves, more kicked columns per output).  Periodic p only.
 constexpr int KB_KD_TW = 230;
-constexpr int KB_KD_TW_WIDE = 182, KD_SPR_WIDE = 56;
 template <typename T, int PF>
 static __global__ __launch_bounds__(KDGeom<KB_KD_TW>::NT) __attribute__((amdgpu_waves_per_eu(8)))
 void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
 {
     using G = KDGeom<KB_KD_TW>;
-    using GW = KDGeom<KB_KD_TW_WIDE, KD_SPR_WIDE>;
+    using GW = KDGeom<KD_TW_WIDE, KD_SPR_WIDE>;
     static_assert(G::NT == GW::NT && G::WK == GW::WK && G::W1 == GW::W1 && G::W2 == GW::W2 && G::ROWLD == GW::ROWLD &&
                       G::NBUF == GW::NBUF,
                   "one workgroup shape and wave roles for both tile widths");
@@ -2049,26 +1892,26 @@ void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy
         const int a = find_member(cy->off_kd, n, e);
         const GridDesc &g = gd[cy->slot[a]];
         const int li = e - cy->off_kd[a];
-        const int tw = g.kd_wide ? KB_KD_TW_WIDE : KB_KD_TW;
+        const int tw = g.kd_wide ? KD_TW_WIDE : KB_KD_TW;
         const int ntx = (g.nx + tw - 1) / tw;
         const int tx = li % ntx, ty = li / ntx;
         const int kin = cy->kin[a];
         const T *fin = (const T *)g.f[kin];
         T *fout = (T *)g.f[kin ^ 1];
         __syncthreads();  // the previous item's LDS rows are consumed
-        const KDTile<T> t{fin, fout, g.Fkick, g.dt, g.dp, g.dm, g.dw, g.dw, g.kbase, g.krel, g.part, g.nx, g.np, 1, tx, ty,
+        const KDTile<T> t{fin, fout, g.Fkick, g.dt, g.dp, g.dm, g.dm, g.dw, g.dw, g.kbase, g.krel, g.part, g.nx, g.np, 1, tx, ty,
                           kbuf, mbuf, wtab};
         const bool px = g.bc_x == BC_PERIODIC;
         if (g.kd_wide) {
             if (px)
-                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, KB_KD_TW_WIDE, KD_SPR_WIDE, PF, KD_PAIR>(t, e);
+                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, KD_TW_WIDE, KD_SPR_WIDE, PF, KD_KICK, 2>(t, e);
             else
-                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, KB_KD_TW_WIDE, KD_SPR_WIDE, PF, KD_PAIR>(t, e);
+                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, KD_TW_WIDE, KD_SPR_WIDE, PF, KD_KICK, 2>(t, e);
         } else {
             if (px)
-                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, KB_KD_TW, KD_SPR, PF, KD_PAIR>(t, e);
+                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, KB_KD_TW, KD_SPR, PF, KD_KICK, 2>(t, e);
             else
-                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, KB_KD_TW, KD_SPR, PF, KD_PAIR>(t, e);
+                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, KB_KD_TW, KD_SPR, PF, KD_KICK, 2>(t, e);
         }
     }
 }
