@@ -39,89 +39,183 @@ struct Grid {
 };
 
 struct Bag {
-    double x0, p0, amp;
+    double amp;
     uint64_t seed;
+    // support: columns [i0, i0 + nc), rows [j0, j0 + nr)
+    int i0, nc, j0, nr;
 };
 
-__device__ __forceinline__ double waterbag_raw(const Grid &g, const Bag &w, int i, int j)
+// The value of a support node.
+__device__ __forceinline__ double bag_raw(const Grid &g, const Bag &w, int i, int j)
 {
-    const double x = g.xmin + (double)i * g.dx;
-    const double v = g.pmin + (double)j * g.dp;
-    if (!(fabs(v) <= w.p0 && fabs(x) <= w.x0)) return 0.0;
     if (w.amp == 0.0) return 1.0;
     const double eta = 2.0 * uniform01(w.seed, (uint64_t)j * (uint64_t)g.nx + (uint64_t)i) - 1.0;
     return 1.0 + w.amp * eta;
 }
 
-// Raw waterbag values, FP64, into `raw` (nx np values).
-__global__ void k_ic_bag_raw(double *__restrict__ raw, Grid g, Bag w)
-{
-    const size_t n = (size_t)g.nx * (size_t)g.np;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x)
-        raw[e] = waterbag_raw(g, w, (int)(e % (size_t)g.nx), (int)(e / (size_t)g.nx));
-}
+// Serial sums of the support rows from their first column (the zeros before
+// and after it add nothing).  A workgroup sums 16 rows: four wavefronts form
+// the values of the next 64 columns in LDS while lanes 0..15 of a fifth add
+// those of the last 64, one row each in column order.  The additions of a row
+// are one chain; 16 rows side by side and the values formed beside it leave
+// that chain as the time.  Sheet waterbag on 2048^2: row sums and their sum 16 us
+// (107 with every value of the grid stored first and one thread adding a
+// row), the fill 11 us (25 with a division for the position of every value).
+constexpr int IC_ROWS = 16, IC_COLS = 64, IC_NT = 320;
 
-// s + a[0] + a[1] + ... + a[n-1], added one by one in index order; sixteen
-// terms requested at a time.
-__device__ __forceinline__ double serial_sum(const double *__restrict__ a, int n)
+static __global__ __launch_bounds__(IC_NT) void k_ic_bag_rows(double *__restrict__ rows, Grid g, Bag w)
 {
+    __shared__ double buf[2][IC_COLS][IC_ROWS + 1];
+    const int t = threadIdx.x, r = t & (IC_ROWS - 1);
+    const int row = blockIdx.x * IC_ROWS + r;  // within the support
+    const int j = w.j0 + min(row, w.nr - 1);
+    const int ntile = (w.nc + IC_COLS - 1) / IC_COLS;
     double s = 0.0;
-    int i = 0;
-    for (; i + 16 <= n; i += 16) {
-        double v[16];
+    for (int k = 0; k <= ntile; ++k) {
+        if (t < 256) {
+            if (k < ntile)
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = a[i + u];
+                for (int q = 0; q < 4; ++q) {
+                    const int c = (t >> 4) + 16 * q;
+                    buf[k & 1][c][r] = bag_raw(g, w, w.i0 + IC_COLS * k + c, j);
+                }
+        } else if (k > 0 && t < 256 + IC_ROWS) {
+            const int n = min(IC_COLS, w.nc - IC_COLS * (k - 1));
+            for (int c0 = 0; c0 < n; c0 += 16) {
+                double v[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) s = s + v[u];
+                for (int u = 0; u < 16; ++u) v[u] = buf[(k - 1) & 1][c0 + u][r];
+#pragma unroll
+                for (int u = 0; u < 16; ++u)
+                    if (c0 + u < n) s = s + v[u];
+            }
+        }
+        __syncthreads();
     }
-    for (; i < n; ++i) s = s + a[i];
-    return s;
+    if (t >= 256 && t < 256 + IC_ROWS && row < w.nr) rows[row] = s;
 }
 
-// Serial sum of each row (one thread per row, from i = 0).
-__global__ void k_ic_rows_raw(const double *__restrict__ raw, double *__restrict__ rows, Grid g)
+// Serial sums of e_j c_i over i (one thread per row), the node factors c staged
+// in LDS.
+static __global__ __launch_bounds__(64) void k_ic_gauss_rows(const double *__restrict__ e, const double *__restrict__ c,
+                                                             double *__restrict__ rows, Grid g)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= g.np) return;
-    rows[j] = serial_sum(raw + (size_t)j * (size_t)g.nx, g.nx);
-}
-
-__global__ void k_ic_rows_gauss(const double *__restrict__ e, const double *__restrict__ c,
-                                double *__restrict__ rows, Grid g)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= g.np) return;
-    const double ej = e[j];
+    constexpr int CH = 1024;
+    __shared__ double L[CH];
+    const int j = blockIdx.x * 64 + threadIdx.x;
+    const double ej = e[min(j, g.np - 1)];
     double s = 0.0;
-    for (int i = 0; i < g.nx; ++i) s = s + ej * c[i];
-    rows[j] = s;
+    for (int i0 = 0; i0 < g.nx; i0 += CH) {
+        const int n = min(CH, g.nx - i0);
+        __syncthreads();
+        for (int i = threadIdx.x; i < n; i += 64) L[i] = c[i0 + i];
+        __syncthreads();
+        int i = 0;
+        for (; i + 16 <= n; i += 16) {
+            double v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = ej * L[i + u];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) s = s + v[u];
+        }
+        for (; i < n; ++i) s = s + ej * L[i];
+    }
+    if (j < g.np) rows[j] = s;
 }
 
-// The serial sum of the row sums S and the divisor (S dx) dp.
-__global__ void k_ic_norm(const double *__restrict__ rows, double *__restrict__ norm, Grid g)
+// The serial sum S of the n row sums and the divisor (S dx) dp: the sums pass
+// through LDS, one thread adds them.
+static __global__ __launch_bounds__(256) void k_ic_norm(const double *__restrict__ rows, double *__restrict__ norm,
+                                                        Grid g, int n)
 {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    const double s = serial_sum(rows, g.np);
-    norm[0] = (s * g.dx) * g.dp;
+    constexpr int CH = 4096;
+    __shared__ double L[CH];
+    double s = 0.0;
+    for (int k0 = 0; k0 < n; k0 += CH) {
+        const int m = min(CH, n - k0);
+        __syncthreads();
+        for (int k = threadIdx.x; k < m; k += 256) L[k] = rows[k0 + k];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int k = 0;
+            for (; k + 16 <= m; k += 16) {
+                double v[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u] = L[k + u];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) s = s + v[u];
+            }
+            for (; k < m; ++k) s = s + L[k];
+        }
+    }
+    if (threadIdx.x == 0) norm[0] = (s * g.dx) * g.dp;
+}
+
+// Four adjacent columns per thread, 256 columns by four rows per workgroup.
+template <typename T>
+__device__ __forceinline__ void ic_store(T *f, const Grid &g, int i, int j, const T (&v)[4])
+{
+    typedef T quad_t __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    T *p = f + (size_t)j * (size_t)g.nx + i;
+    if (i + 4 <= g.nx) {
+        quad_t q;
+        q.x = v[0];
+        q.y = v[1];
+        q.z = v[2];
+        q.w = v[3];
+        *reinterpret_cast<quad_t *>(p) = q;
+    } else {
+        for (int u = 0; u < 4; ++u)
+            if (i + u < g.nx) p[u] = v[u];
+    }
 }
 
 template <typename T>
-__global__ void k_ic_bag_fill(T *__restrict__ f, const double *__restrict__ norm, Grid g, Bag w)
+static __global__ __launch_bounds__(256) void k_ic_bag_fill(T *__restrict__ f, const double *__restrict__ norm, Grid g,
+                                                            Bag w)
 {
+    const int i = blockIdx.x * 256 + (threadIdx.x & 63) * 4;
     const double d = norm[0];
-    const size_t n = (size_t)g.nx * (size_t)g.np;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x)
-        f[e] = (T)(waterbag_raw(g, w, (int)(e % (size_t)g.nx), (int)(e / (size_t)g.nx)) / d);
+    for (int j = blockIdx.y * 4 + (threadIdx.x >> 6); j < g.np; j += gridDim.y * 4) {
+        if (i >= g.nx) continue;
+        T v[4] = {T(0), T(0), T(0), T(0)};
+        if (j >= w.j0 && j < w.j0 + w.nr && i + 4 > w.i0 && i < w.i0 + w.nc)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i + u >= w.i0 && i + u < w.i0 + w.nc)
+                    v[u] = (T)(bag_raw(g, w, i + u, j) / d);
+        ic_store(f, g, i, j, v);
+    }
 }
 
 template <typename T>
-__global__ void k_ic_gauss_fill(T *__restrict__ f, const double *__restrict__ e, const double *__restrict__ c,
-                                const double *__restrict__ norm, Grid g)
+static __global__ __launch_bounds__(256) void k_ic_gauss_fill(T *__restrict__ f, const double *__restrict__ e,
+                                                              const double *__restrict__ c,
+                                                              const double *__restrict__ norm, Grid g)
 {
+    const int i = blockIdx.x * 256 + (threadIdx.x & 63) * 4;
     const double d = norm[0];
-    const size_t n = (size_t)g.nx * (size_t)g.np;
-    for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x)
-        f[k] = (T)((e[k / (size_t)g.nx] * c[k % (size_t)g.nx]) / d);
+    for (int j = blockIdx.y * 4 + (threadIdx.x >> 6); j < g.np; j += gridDim.y * 4) {
+        if (i >= g.nx) continue;
+        const double ej = e[j];
+        T v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = (T)((ej * c[min(i + u, g.nx - 1)]) / d);
+        ic_store(f, g, i, j, v);
+    }
+}
+
+// Nodes u_k = umin + k du with |u_k| <= half: first and count (they are
+// adjacent, u_k grows with k), by the arithmetic of the nodes' definition.
+void support(int n, double umin, double du, double half, int &first, int &count)
+{
+    first = 0;
+    count = 0;
+    for (int k = 0; k < n; ++k)
+        if (fabs(umin + (double)k * du) <= half) {
+            if (count == 0) first = k;
+            ++count;
+        }
 }
 
 // Half-widths of the HMF waterbag of magnetization M0 and energy U (Sec.
@@ -173,16 +267,6 @@ std::string validate_ic(const vlasov_ic *ic)
 
 }  // namespace vlasov_detail
 
-namespace {
-
-int launch_grid(size_t n)
-{
-    const size_t wg = (n + 255) / 256;
-    return (int)(wg < 8192 ? (wg ? wg : 1) : 8192);
-}
-
-}  // namespace
-
 extern "C" {
 
 int vlasov_generate_ic(vlasov_ctx *c, const vlasov_ic *ic)
@@ -190,31 +274,29 @@ int vlasov_generate_ic(vlasov_ctx *c, const vlasov_ic *ic)
     if (!c || !ic) return fail(VLASOV_E_INVAL, "NULL argument");
     const vlasov_params &P = c->P;
     Grid g{(int)P.nx, (int)P.np, P.xmin, c->dx, P.pmin, c->dp};
-    const size_t N = (size_t)P.nx * (size_t)P.np;
-    // scratch: raw values over the whole f pair (N doubles fit in it for both
-    // storages), row sums in the density partial sums (nblk nx >= np), the
+    // scratch: row sums in the density partial sums (nblk nx >= np), the
     // divisor in rho; the Gaussian's node factors in the second f buffer (np
     // values) and the diagnostics columns (nx values)
-    double *raw = reinterpret_cast<double *>(c->f[0]);
     double *rows = c->at<double>(c->L.part);
     double *norm = c->at<double>(c->L.rho);
     const bool f32 = P.storage == VLASOV_F32;
     void *out = c->f[0];
-    const int G = launch_grid(N);
+    const dim3 fill((unsigned)((g.nx + 255) / 256), (unsigned)std::min((g.np + 3) / 4, 65535));
     const std::string why = validate_ic(ic);
     if (!why.empty()) return fail(VLASOV_E_INVAL, why);
     if (ic->kind == VLASOV_IC_WATERBAG || ic->kind == VLASOV_IC_WATERBAG_UM) {
-        Bag w{ic->a0, ic->a1, ic->amp, ic->seed};
-        if (ic->kind == VLASOV_IC_WATERBAG_UM) (void)hmf_halfwidths(ic->a0, ic->a1, w.x0, w.p0);
-        w.x0 = std::max(w.x0, 2.0 * c->dx);
-        w.p0 = std::max(w.p0, 2.0 * c->dp);
-        k_ic_bag_raw<<<G, 256, 0, c->stream>>>(raw, g, w);
-        k_ic_rows_raw<<<(g.np + 63) / 64, 64, 0, c->stream>>>(raw, rows, g);
-        k_ic_norm<<<1, 64, 0, c->stream>>>(rows, norm, g);
+        double x0 = ic->a0, p0 = ic->a1;
+        if (ic->kind == VLASOV_IC_WATERBAG_UM) (void)hmf_halfwidths(ic->a0, ic->a1, x0, p0);
+        Bag w{ic->amp, ic->seed, 0, 0, 0, 0};
+        support(g.nx, g.xmin, g.dx, std::max(x0, 2.0 * c->dx), w.i0, w.nc);
+        support(g.np, g.pmin, g.dp, std::max(p0, 2.0 * c->dp), w.j0, w.nr);
+        if (w.nc == 0 || w.nr == 0) return fail(VLASOV_E_INVAL, "the initial condition has no mass on the grid");
+        k_ic_bag_rows<<<(w.nr + IC_ROWS - 1) / IC_ROWS, IC_NT, 0, c->stream>>>(rows, g, w);
+        k_ic_norm<<<1, 256, 0, c->stream>>>(rows, norm, g, w.nr);
         if (f32)
-            k_ic_bag_fill<float><<<G, 256, 0, c->stream>>>((float *)out, norm, g, w);
+            k_ic_bag_fill<float><<<fill, 256, 0, c->stream>>>((float *)out, norm, g, w);
         else
-            k_ic_bag_fill<double><<<G, 256, 0, c->stream>>>((double *)out, norm, g, w);
+            k_ic_bag_fill<double><<<fill, 256, 0, c->stream>>>((double *)out, norm, g, w);
     } else if (ic->kind == VLASOV_IC_GAUSSIAN) {
         const double T = ic->a0, A = ic->amp;
         const double phi = ic->seed == 0 ? 0.0 : 2.0 * M_PI * uniform01(ic->seed, 0);
@@ -231,12 +313,12 @@ int vlasov_generate_ic(vlasov_ctx *c, const vlasov_ic *ic)
         double *dc = c->at<double>(c->L.mom_col);
         HIP_TRY(hipMemcpyAsync(de, e.data(), e.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
         HIP_TRY(hipMemcpyAsync(dc, cc.data(), cc.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-        k_ic_rows_gauss<<<(g.np + 63) / 64, 64, 0, c->stream>>>(de, dc, rows, g);
-        k_ic_norm<<<1, 64, 0, c->stream>>>(rows, norm, g);
+        k_ic_gauss_rows<<<(g.np + 63) / 64, 64, 0, c->stream>>>(de, dc, rows, g);
+        k_ic_norm<<<1, 256, 0, c->stream>>>(rows, norm, g, g.np);
         if (f32)
-            k_ic_gauss_fill<float><<<G, 256, 0, c->stream>>>((float *)out, de, dc, norm, g);
+            k_ic_gauss_fill<float><<<fill, 256, 0, c->stream>>>((float *)out, de, dc, norm, g);
         else
-            k_ic_gauss_fill<double><<<G, 256, 0, c->stream>>>((double *)out, de, dc, norm, g);
+            k_ic_gauss_fill<double><<<fill, 256, 0, c->stream>>>((double *)out, de, dc, norm, g);
     }
     int rc = check_launch("initial condition");
     if (rc != VLASOV_OK) return rc;
