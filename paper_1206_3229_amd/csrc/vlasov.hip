@@ -627,20 +627,15 @@ int vlasov_drift(vlasov_ctx *c, int32_t npass)
 int vlasov_force(vlasov_ctx *c, double *F_host, double *mxmy_host)
 {
     if (!c) return fail(VLASOV_E_INVAL, "NULL context");
-    // density partial sums of the current f: reuse the diagnostic block pass
     const vlasov_params &P = c->P;
-    dim3 grid((unsigned)((P.nx + 255) / 256), (unsigned)c->nblk);
-    double *scratch = (double *)c->fnext();
+    const dim3 grid((unsigned)((P.nx + 255) / 256), (unsigned)c->nblk);
+    double *part = c->at<double>(c->L.part);
     if (P.storage == VLASOV_F32)
-        vk::k_mom_blocks<float><<<grid, 256, 0, c->stream>>>((const float *)c->fcur(), scratch, (int)P.nx, (int)P.np,
-                                                             (int)c->nblk, P.pmin, c->dp);
+        vk::k_partials<float><<<grid, 256, 0, c->stream>>>((const float *)c->fcur(), part, (int)P.nx, (int)P.np);
     else
-        vk::k_mom_blocks<double><<<grid, 256, 0, c->stream>>>((const double *)c->fcur(), scratch, (int)P.nx,
-                                                              (int)P.np, (int)c->nblk, P.pmin, c->dp);
+        vk::k_partials<double><<<grid, 256, 0, c->stream>>>((const double *)c->fcur(), part, (int)P.nx, (int)P.np);
     int rc = check_launch("force: block sums");
     if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(c->ws + c->L.part, scratch, (size_t)c->nblk * (size_t)P.nx * sizeof(double),
-                           hipMemcpyDeviceToDevice, c->stream));
     if ((rc = density_force(c)) != VLASOV_OK) return rc;
     if (F_host || mxmy_host) {
         if (F_host)
@@ -674,24 +669,28 @@ int vlasov_moments(vlasov_ctx *c, vlasov_moments_t *out)
     double *col = c->at<double>(c->L.mom_col);
     double *phi = c->at<double>(c->L.mom_phi);
     double *res = c->at<double>(c->L.mom_out);
-    const dim3 grid((unsigned)((P.nx + 255) / 256), (unsigned)c->nblk);
-    if (P.storage == VLASOV_F32)
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks<float>, grid, dim3(256), (const float *)c->fcur(), scratch, nx,
-               (int)P.np, (int)c->nblk, P.pmin, c->dp);
-    else
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks<double>, grid, dim3(256), (const double *)c->fcur(), scratch, nx,
-               (int)P.np, (int)c->nblk, P.pmin, c->dp);
-    launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols, dim3((unsigned)((nx + 3) / 4)), dim3(256), scratch, col, nx,
-           (int)c->nblk, c->dp, 4, 0);
-    // entropy density and negative mass: a second block pass over the scratch
-    if (P.storage == VLASOV_F32)
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks2<float>, grid, dim3(256), (const float *)c->fcur(), scratch, nx,
-               (int)P.np, (int)c->nblk);
-    else
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks2<double>, grid, dim3(256), (const double *)c->fcur(), scratch,
-               nx, (int)P.np, (int)c->nblk);
-    launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols, dim3((unsigned)((nx + 3) / 4)), dim3(256), scratch, col, nx,
-           (int)c->nblk, c->dp, 2, 4);
+    const dim3 grid((unsigned)((nx + 255) / 256), (unsigned)c->nblk), cgrid((unsigned)((nx + 15) / 16));
+    const int nblk = (int)c->nblk;
+#define MOM_BLOCKS(SETS)                                                                                                 \
+    if (P.storage == VLASOV_F32)                                                                                        \
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks<float, SETS>, grid, dim3(256), (const float *)c->fcur(), scratch, \
+               nx, (int)P.np, nblk, P.pmin, c->dp);                                                                     \
+    else                                                                                                                \
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks<double, SETS>, grid, dim3(256), (const double *)c->fcur(),        \
+               scratch, nx, (int)P.np, nblk, P.pmin, c->dp)
+    // six planes of block sums in one pass where the idle buffer holds them
+    // (always but for FP32 grids of 17 to 23 and 33 to 35 rows), else four
+    // and two
+    if (6 * (size_t)nblk * sizeof(double) <= (size_t)P.np * c->s) {
+        MOM_BLOCKS(3);
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<6>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 0);
+    } else {
+        MOM_BLOCKS(1);
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<4>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 0);
+        MOM_BLOCKS(2);
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<2>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 4);
+    }
+#undef MOM_BLOCKS
     double wcoef = 0.0;
     if (P.model == VLASOV_MODEL_RING) {
         launch(c, VLASOV_K_MOMENTS, vk::k_mom_phi<true>, dim3((unsigned)((nx + 3) / 4)), dim3(256), col,
@@ -702,7 +701,7 @@ int vlasov_moments(vlasov_ctx *c, vlasov_moments_t *out)
                (const double *)nullptr, phi, nx);
         wcoef = (((M_PI * P.sheet_G) * c->dx) * c->dx) * c->dx;
     }
-    launch(c, VLASOV_K_MOMENTS, vk::k_mom_final, dim3(1), dim3(64), col, phi, c->at<double>(c->L.cs),
+    launch(c, VLASOV_K_MOMENTS, vk::k_mom_final, dim3(1), dim3(576), col, phi, c->at<double>(c->L.cs),
            c->at<double>(c->L.sn), res, nx, c->dx, (int)P.model, wcoef);
     int rc = check_launch("moments");
     if (rc) return rc;
