@@ -306,9 +306,11 @@ int vlasov_get_tuning(vlasov_ctx *c, vlasov_tuning *t);
 
 /* Flags of batched stepping and of the server (the `flags` arguments):
  *   VLASOV_BATCH_GRAPH  capture the chunk's launches into a HIP graph once and
- *                       replay it;
+ *                       replay it, for full chunks of stepping after the first
+ *                       sixteen (a graph costs more host time than it saves before);
  *   VLASOV_BATCH_FUSE   run each member's kick fused with the pair of half drifts
- *                       after it (the single-grid fused kernel on 230-column
+ *                       after it, or with the one after its last kick (the
+ *                       single-grid fused kernel on 230-column
  *                       tiles, or on 182-column tiles with 56 columns of
  *                       slack for members whose drift offsets spread by 9 to
  *                       56 columns inside a 16-row tile; members with a

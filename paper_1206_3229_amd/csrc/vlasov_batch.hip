@@ -25,7 +25,7 @@ using namespace vlasov_detail;
 namespace {
 
 // Persistent launch widths (workgroups) of the four batched phases.
-constexpr int KB_FORCE_NT = 1024;
+constexpr int KB_FORCE_NT = 256;
 
 size_t set_bytes(int K) { return align_up(sizeof(vk::GridDesc) * vk::BATCH_MAX + sizeof(vk::Cycle) * (size_t)K); }
 
@@ -45,6 +45,14 @@ struct Member {
 bool fusable(const vlasov_ctx *c)
 {
     return c->kd_spread[0] <= vk::KD_SPR_WIDE && c->kd_rb == 1 && c->P.bc_p == VLASOV_BC_PERIODIC;
+}
+
+// Whether the last kick of such a member runs fused with its half drift: that
+// tile takes the drift offsets mod nx, which are known to be apart by less than
+// half a period on lines of four spreads.
+bool fusable_last(const vlasov_ctx *c)
+{
+    return fusable(c) && (c->P.bc_x == VLASOV_BC_ZERO || c->P.nx >= 4 * c->kd_spread1[0] + 16);
 }
 
 bool kd_wide(const vlasov_ctx *c) { return c->kd_spread[0] > vk::KD_SPR; }
@@ -147,13 +155,9 @@ class Engine {
         } else {
             HIP_TRY(size_grids<double>(ncu));
         }
-        for (int s = 0; s < 2; ++s) {
-            HIP_TRY(hipHostMalloc((void **)&host_[s], set_bytes(K), hipHostMallocDefault));
-            HIP_TRY(hipEventCreateWithFlags(&ev_[s], hipEventDisableTiming));
-        }
-        // graphs are captured on a private stream (the caller's may be the null
-        // stream, which cannot be captured) and launched on the caller's
-        if (graph) HIP_TRY(hipStreamCreateWithFlags(&cap_, hipStreamNonBlocking));
+        HIP_TRY(hipHostMalloc((void **)&host_[0], 2 * set_bytes(K), hipHostMallocDefault));
+        host_[1] = host_[0] + set_bytes(K);
+        for (int s = 0; s < 2; ++s) HIP_TRY(hipEventCreateWithFlags(&ev_[s], hipEventDisableTiming));
         return VLASOV_OK;
     }
 
@@ -163,11 +167,11 @@ class Engine {
         for (int s = 0; s < 2; ++s) {
             if (exec_[s]) (void)hipGraphExecDestroy(exec_[s]);
             if (ev_[s]) (void)hipEventDestroy(ev_[s]);
-            if (host_[s]) (void)hipHostFree(host_[s]);
             exec_[s] = nullptr;
             ev_[s] = nullptr;
-            host_[s] = nullptr;
         }
+        if (host_[0]) (void)hipHostFree(host_[0]);
+        host_[0] = host_[1] = nullptr;
         if (cap_) (void)hipStreamDestroy(cap_);
         cap_ = nullptr;
     }
@@ -183,6 +187,8 @@ class Engine {
         vk::Cycle *hc = reinterpret_cast<vk::Cycle *>(host_[set] + sizeof(vk::GridDesc) * vk::BATCH_MAX);
         const int n = (int)ms.size();
         for (int a = 0; a < n; ++a) hd[a] = describe(ms[a]->c);
+        int used = 0;                // cycles with work
+        bool dr_later = false, kick_alone = false;  // drifts after cycle 0, separate kicks
         for (int k = 0; k < K_; ++k) {
             vk::Cycle &cy = hc[k];
             cy.n = n;
@@ -193,33 +199,42 @@ class Engine {
                 // drift phase: the first half drift of the first step, the
                 // pair closing one step and opening the next, or the last
                 // half drift; none when the open step has its first half drift
-                int kind = vk::DRIFT_NONE, kick = 0, fused = 0;
+                int kind = vk::DRIFT_NONE, kick = vk::KICK_NONE;
                 if (!m.done()) {
                     if (m.started == m.closed) {
                         kind = vk::DRIFT_FIRST;
-                        kick = 1;
+                        kick = vk::KICK_ALONE;
                         ++m.started;
                     } else if (m.half_open) {
-                        kick = 1;
+                        kick = vk::KICK_ALONE;
                     } else if (m.started < m.total) {
                         kind = vk::DRIFT_PAIR;
-                        kick = 1;
+                        kick = vk::KICK_ALONE;
                         ++m.closed;
                         ++m.started;
                     } else {
                         kind = vk::DRIFT_LAST;
                         ++m.closed;
                     }
-                    // kick phase: with a next step to open, the fused kick and
-                    // drift pair where the member allows it
+                    // kick phase: fused with the half drifts after it where the
+                    // member allows it
+                    m.half_open = false;
                     if (kick && fuse_ && m.started < m.total && fusable(c)) {
-                        fused = 1;
+                        kick = vk::KICK_PAIR;
                         ++m.closed;
                         ++m.started;
+                        m.half_open = true;
+                    } else if (kick && fuse_ && m.started == m.total && fusable_last(c)) {
+                        kick = vk::KICK_LAST;
+                        ++m.closed;
                     }
-                    m.half_open = fused != 0;
+                    used = k + 1;
+                    dr_later = dr_later || (k > 0 && kind);
+                    kick_alone = kick_alone || kick == vk::KICK_ALONE;
+                } else {
+                    m.half_open = false;
                 }
-                cy.slot[a] = a;
+                const bool fused = kick == vk::KICK_PAIR || kick == vk::KICK_LAST;
                 cy.drift[a] = (int8_t)kind;
                 cy.kick[a] = (int8_t)kick;
                 cy.cur[a] = (int8_t)c->cur;
@@ -241,11 +256,23 @@ class Engine {
         char *dset = dev_ + (size_t)set * set_bytes(K_);
         HIP_TRY(hipMemcpyAsync(dset, host_[set], set_bytes(K_), hipMemcpyHostToDevice, st_));
         HIP_TRY(hipEventRecord(ev_[set], st_));
-        if (!graph_) return launch_cycles(dset, st_);
+        // The graph holds the phases of K cycles of stepping: density, force
+        // and the fused kick with fusion, whose members drift on their own
+        // in the first cycle only (launched before the graph); drift,
+        // density, force and kick without.  Chunks with other phases, or with
+        // fewer cycles left, launch what they have: an empty phase costs a
+        // launch of about 4 us on the device.
+        // A graph is made after GRAPH_AFTER such chunks: capturing and
+        // instantiating one takes about 410 us of host time, a launch 2.6 us.
+        const bool steady = fuse_ ? !dr_later && !kick_alone : true;
+        if (!graph_ || used < K_ || !steady || ++steady_[set] <= GRAPH_AFTER) return launch_cycles(dset, st_, hc, used);
         if (!exec_[set]) {
+            // captured on a private stream (the caller's may be the null stream,
+            // which cannot be captured) and launched on the caller's
+            if (!cap_) HIP_TRY(hipStreamCreateWithFlags(&cap_, hipStreamNonBlocking));
             hipGraph_t g = nullptr;
             HIP_TRY(hipStreamBeginCapture(cap_, hipStreamCaptureModeThreadLocal));
-            int rc = launch_cycles(dset, cap_);
+            int rc = launch_cycles(dset, cap_, nullptr, K_);
             hipError_t e = hipStreamEndCapture(cap_, &g);
             if (rc != VLASOV_OK) {
                 if (g) (void)hipGraphDestroy(g);
@@ -255,6 +282,10 @@ class Engine {
             e = hipGraphInstantiate(&exec_[set], g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             if (e != hipSuccess) return fail(VLASOV_E_HIP, std::string("graph instantiate: ") + hipGetErrorString(e));
+        }
+        if (fuse_ && hc[0].off_drift[n] > 0) {
+            const int rc = launch_first_drift(dset, n, hc[0].off_drift[n]);
+            if (rc != VLASOV_OK) return rc;
         }
         HIP_TRY(hipGraphLaunch(exec_[set], st_));
         return VLASOV_OK;
@@ -283,29 +314,55 @@ class Engine {
         return e;
     }
 
+    // The phases of `cycles` cycles: those with work, by the host tables `hc`,
+    // or (hc NULL, for the graph) those of stepping.
     template <typename T>
-    void launch_cycles_t(char *dset, hipStream_t st)
+    void launch_cycles_t(char *dset, hipStream_t st, const vk::Cycle *hc, int cycles)
     {
         const vk::GridDesc *gd = reinterpret_cast<const vk::GridDesc *>(dset);
         const vk::Cycle *cy = reinterpret_cast<const vk::Cycle *>(dset + sizeof(vk::GridDesc) * vk::BATCH_MAX);
-        for (int k = 0; k < K_; ++k) {
-            vk::kb_drift<T><<<wg_drift_, vk::KDGeom<vk::DR_TW>::NT, 0, st>>>(gd, cy + k);
-            vk::kb_density<<<wg_dens_, 256, 0, st>>>(gd, cy + k);
-            vk::kb_force<<<wg_force_, KB_FORCE_NT, 0, st>>>(gd, cy + k);
-            vk::kb_kick<T, kick_rows<T>()><<<wg_kick_, 256, 0, st>>>(gd, cy + k);
-            if (fuse_) vk::kb_kick_drift<T, kd_pf<T>()><<<wg_kd_, vk::KDGeom<vk::KB_KD_TW>::NT, 0, st>>>(gd, cy + k);
+        constexpr int NT = vk::KDGeom<vk::KB_KD_TW>::NT;
+        for (int k = 0; k < cycles; ++k) {
+            const int n = hc ? hc[k].n : 0;
+            // items of a captured launch are read from the table (-1)
+            const int drift = hc ? hc[k].off_drift[n] : (fuse_ ? 0 : -1);
+            const int dens = hc ? hc[k].off_dens[n] : -1, force = hc ? hc[k].off_force[n] : -1;
+            const int kick = hc ? hc[k].off_kick[n] : (fuse_ ? 0 : -1), kd = hc ? hc[k].off_kd[n] : (fuse_ ? -1 : 0);
+            auto grid = [](int wg, int items) { return dim3((unsigned)(items < 0 ? wg : std::min(wg, items))); };
+            if (drift) vk::kb_drift<T><<<grid(wg_drift_, drift), vk::KDGeom<vk::DR_TW>::NT, 0, st>>>(gd, cy + k, n, drift);
+            if (dens) vk::kb_density<<<grid(wg_dens_, dens), 256, 0, st>>>(gd, cy + k, n, dens);
+            if (force) vk::kb_force<<<grid(wg_force_, force), KB_FORCE_NT, 0, st>>>(gd, cy + k, n, force);
+            if (kick) vk::kb_kick<T, kick_rows<T>()><<<grid(wg_kick_, kick), 256, 0, st>>>(gd, cy + k, n, kick);
+            if (kd) vk::kb_kick_drift<T, kd_pf<T>()><<<grid(wg_kd_, kd), NT, 0, st>>>(gd, cy + k, n, kd);
         }
     }
 
-    int launch_cycles(char *dset, hipStream_t st)
+    int launched()
     {
-        if (storage_ == VLASOV_F32)
-            launch_cycles_t<float>(dset, st);
-        else
-            launch_cycles_t<double>(dset, st);
-        hipError_t e = hipGetLastError();
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(VLASOV_E_HIP, std::string("batched launch: ") + hipGetErrorString(e));
         return VLASOV_OK;
+    }
+
+    int launch_cycles(char *dset, hipStream_t st, const vk::Cycle *hc, int cycles)
+    {
+        if (storage_ == VLASOV_F32)
+            launch_cycles_t<float>(dset, st, hc, cycles);
+        else
+            launch_cycles_t<double>(dset, st, hc, cycles);
+        return launched();
+    }
+
+    int launch_first_drift(char *dset, int n, int tiles)
+    {
+        const vk::GridDesc *gd = reinterpret_cast<const vk::GridDesc *>(dset);
+        const vk::Cycle *cy = reinterpret_cast<const vk::Cycle *>(dset + sizeof(vk::GridDesc) * vk::BATCH_MAX);
+        const dim3 grid((unsigned)std::min(wg_drift_, tiles)), block(vk::KDGeom<vk::DR_TW>::NT);
+        if (storage_ == VLASOV_F32)
+            vk::kb_drift<float><<<grid, block, 0, st_>>>(gd, cy, n, tiles);
+        else
+            vk::kb_drift<double><<<grid, block, 0, st_>>>(gd, cy, n, tiles);
+        return launched();
     }
 
     char *dev_ = nullptr;
@@ -316,6 +373,8 @@ class Engine {
     hipEvent_t ev_[2] = {nullptr, nullptr};
     hipGraphExec_t exec_[2] = {nullptr, nullptr};
     hipStream_t cap_ = nullptr;
+    static constexpr int GRAPH_AFTER = 8;
+    int steady_[2] = {0, 0};  // chunks of stepping phases only, per table set
     int set_ = 0;
     bool fuse_ = false;  // the fused kick and drift pair for the members that allow it
     int wg_drift_ = 1, wg_dens_ = 1, wg_force_ = 1, wg_kick_ = 1, wg_kd_ = 1;  // persistent grid sizes

@@ -1405,6 +1405,42 @@ __device__ __forceinline__ void force_ring_output(const double *__restrict__ rho
     if (lane == 0) F[i] = -(dx * acc);
 }
 
+// Four adjacent outputs i0 .. i0 + 3 by one wavefront, their chains side by
+// side over the same density values.
+__device__ __forceinline__ void force_ring_outputs4(const double *__restrict__ rho, const double *__restrict__ K,
+                                                    double *__restrict__ F, int n, double dx, int i0)
+{
+    const int lane = threadIdx.x & 63;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = lane; k0 < n; k0 += 4 * 64) {
+        double kv[4][4], rv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = min(k0 + 64 * u, n - 1);
+            rv[u] = rho[k];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int d = min(i0 + q, n - 1) - k;
+                kv[u][q] = K[d < 0 ? d + n : d];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            keep_issued(rv[u]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) keep_issued(kv[u][q]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (k0 + 64 * u < n)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] = fma(kv[u][q], rv[u], acc[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = wave_sum(acc[q]);
+    if (lane < 4 && i0 + lane < n) F[i0 + lane] = -(dx * (lane == 0 ? acc[0] : lane == 1 ? acc[1] : lane == 2 ? acc[2] : acc[3]));
+}
+
 // Workgroup 0 forms the magnetization (M_x, M_y) for the history instead (the
 // ring force does not use it), dispatched first so that its chain overlaps
 // the outputs' workgroups.  STAGED (n <= RING_LDS_MAX): every workgroup first
@@ -1740,9 +1776,15 @@ static __global__ __launch_bounds__(576) void k_mom_final(const double *__restri
 // over the work items of all members; per-grid arithmetic is exactly that of
 // the single-grid kernels, whatever workgroup processes a tile.
 // ---------------------------------------------------------------------------
+// The counts of members and work items are arguments where the launch knows
+// them (items >= 0; two dependent loads fewer before the first item), else
+// (a captured launch) read from the table.
 constexpr int BATCH_MAX = 256;
 
 enum { DRIFT_NONE = 0, DRIFT_FIRST = 1, DRIFT_PAIR = 2, DRIFT_LAST = 3 };
+// no kick, a separate one, one fused with the two half drifts after it, or (last
+// step) with the one after it
+enum { KICK_NONE = 0, KICK_ALONE = 1, KICK_PAIR = 2, KICK_LAST = 3 };
 
 struct GridDesc {
     void *f[2];
@@ -1761,10 +1803,9 @@ struct GridDesc {
 };
 
 struct Cycle {
-    int32_t n;                   // members in this cycle
-    int32_t slot[BATCH_MAX];     // GridDesc index of member a
+    int32_t n;                   // members in this cycle (member a has GridDesc a)
     int8_t drift[BATCH_MAX];     // DRIFT_* (FIRST and PAIR also write density partial sums)
-    int8_t kick[BATCH_MAX];      // density, force and kick in this cycle
+    int8_t kick[BATCH_MAX];      // KICK_* (all but NONE with density and force)
     int8_t cur[BATCH_MAX];       // current f buffer at the start of the cycle
     int8_t kin[BATCH_MAX];       // f buffer the kick (or fused kick and drift) reads
     int8_t pad[4];
@@ -1774,33 +1815,34 @@ struct Cycle {
         off_kd[BATCH_MAX + 1];
 };
 
-// Member owning work item e: the last a with off[a] <= e (off[0] = 0 <= e < off[n]).
-__device__ __forceinline__ int find_member(const int32_t *off, int n, int e)
+// Member owning work item e: the last a with off[a] <= e (off[0] = 0 <= e <
+// off[n]).  The lanes of each wavefront look at 64 members at a time: one
+// memory latency, where a binary search had one per halving.
+__device__ __forceinline__ int find_member(const int32_t *__restrict__ off, int n, int e)
 {
-    int lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (off[mid] <= e)
-            lo = mid;
-        else
-            hi = mid;
+    const int lane = threadIdx.x & 63;
+    int count = 0;
+    for (int base = 0; base < n; base += 64) {
+        const int a = base + lane;
+        const bool below = a < n && off[min(a, n)] <= e;
+        count += __popcll(__ballot(below));
     }
-    return lo;
+    return count - 1;
 }
 
 template <typename T>
 static __global__ __launch_bounds__(KDGeom<DR_TW>::NT) __attribute__((amdgpu_waves_per_eu(8)))
-void kb_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
+void kb_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int members, int items)
 {
     using G = KDGeom<DR_TW>;
     __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];
     __shared__ __attribute__((aligned(16))) T mbuf[G::NBUF * G::ROWLD];
     __shared__ __attribute__((aligned(16))) T wtab[8 * ROWS_PER_BLOCK];
-    const int n = cy->n;
-    const int total = cy->off_drift[n];
+    const int n = items >= 0 ? members : cy->n;
+    const int total = items >= 0 ? items : cy->off_drift[n];
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
         const int a = find_member(cy->off_drift, n, e);
-        const GridDesc &g = gd[cy->slot[a]];
+        const GridDesc &g = gd[a];
         const int kind = cy->drift[a], cur = cy->cur[a];
         const int li = e - cy->off_drift[a];
         const int ntx = (g.nx + DR_TW - 1) / DR_TW;
@@ -1822,38 +1864,38 @@ void kb_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
     }
 }
 
-static __global__ __launch_bounds__(256) void kb_density(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
+static __global__ __launch_bounds__(256) void kb_density(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int members, int items)
 {
     __shared__ double S[64][17];
-    const int n = cy->n;
-    const int total = cy->off_dens[n];
+    const int n = items >= 0 ? members : cy->n;
+    const int total = items >= 0 ? items : cy->off_dens[n];
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
         const int a = find_member(cy->off_dens, n, e);
-        const GridDesc &g = gd[cy->slot[a]];
+        const GridDesc &g = gd[a];
         __syncthreads();
         density_block(g.part, g.rho, g.nx, g.nblk, g.dp, e - cy->off_dens[a], S);
     }
 }
 
 // Work items per member: HMF and sheet one workgroup; ring ceil(nx/16)
-// workgroups of 16 outputs plus one for the magnetization; EXTERNAL none.
-// Arrays are staged in LDS for grids up to BATCH_FORCE_STAGE columns (48 KB,
-// and at most 64 VGPRs: two workgroups per compute unit, so that the many
-// ring items of a cycle run two at a time on each unit).
+// workgroups of 16 outputs, four a wavefront, plus one for the magnetization;
+// EXTERNAL none.  Arrays of the others are staged in LDS for grids up to
+// BATCH_FORCE_STAGE columns.  Workgroups of four wavefronts: with sixteen (one
+// ring output each) dispatching them took longer than the work (32 grids of up
+// to 1024 columns: 9.2 us, 7.8 now).
 constexpr int BATCH_FORCE_STAGE = 2048;
 constexpr int BATCH_SHEET_WORDS = ((BATCH_FORCE_STAGE + 63) / 64) * 65;
 constexpr int BATCH_FORCE_LDS = BATCH_SHEET_WORDS > 3 * BATCH_FORCE_STAGE ? BATCH_SHEET_WORDS : 3 * BATCH_FORCE_STAGE;
 
-static __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
-void kb_force(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
+static __global__ __launch_bounds__(256) void kb_force(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int members, int items)
 {
     __shared__ double L[BATCH_FORCE_LDS];
     __shared__ double M[2];
-    const int n = cy->n;
-    const int total = cy->off_force[n];
+    const int n = items >= 0 ? members : cy->n;
+    const int total = items >= 0 ? items : cy->off_force[n];
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
         const int a = find_member(cy->off_force, n, e);
-        const GridDesc &g = gd[cy->slot[a]];
+        const GridDesc &g = gd[a];
         const int li = e - cy->off_force[a];
         __syncthreads();
         if (g.model == 0) {
@@ -1870,8 +1912,7 @@ void kb_force(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
         } else if (g.model == 1) {
             const int nb = (g.nx + 15) / 16;
             if (li < nb) {
-                const int i = li * 16 + (threadIdx.x >> 6);
-                if (i < g.nx) force_ring_output(g.rho, g.K, g.F, g.nx, g.dx, i);
+                force_ring_outputs4(g.rho, g.K, g.F, g.nx, g.dx, li * 16 + (threadIdx.x >> 6) * 4);
             } else if (g.nx <= BATCH_FORCE_STAGE) {
                 magnetization_block<true, BATCH_FORCE_STAGE>(g.rho, g.cs, g.sn, g.nx, g.dx, g.mxmy, g.hist, g.hcount,
                                                              g.hcap, L);
@@ -1883,13 +1924,13 @@ void kb_force(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
 }
 
 template <typename T, int R>
-static __global__ __launch_bounds__(256) void kb_kick(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
+static __global__ __launch_bounds__(256) void kb_kick(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int members, int items)
 {
-    const int n = cy->n;
-    const int total = cy->off_kick[n];
+    const int n = items >= 0 ? members : cy->n;
+    const int total = items >= 0 ? items : cy->off_kick[n];
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
         const int a = find_member(cy->off_kick, n, e);
-        const GridDesc &g = gd[cy->slot[a]];
+        const GridDesc &g = gd[a];
         const int li = e - cy->off_kick[a];
         const int ntx = (g.nx + 255) / 256;
         const int tx = li % ntx, ty = li / ntx;
@@ -1904,7 +1945,8 @@ static __global__ __launch_bounds__(256) void kb_kick(const GridDesc *__restrict
 }
 
 // The kick fused with the two half drifts after it (the second of one step,
-// the first of the next) for the members whose tables allow it: tiles of 230
+// the first of the next; only the former after the last kick) for the members
+// whose tables allow it: tiles of 230
 // columns by 16 rows with 8 columns of slack, as the single-grid kernel, or,
 // for a member whose drift offsets spread more inside a tile (coarse p, fine
 // x, long steps), tiles of 182 columns with 56 of slack (the same 256 kicked
@@ -1912,7 +1954,7 @@ static __global__ __launch_bounds__(256) void kb_kick(const GridDesc *__restrict
 constexpr int KB_KD_TW = 230;
 template <typename T, int PF>
 static __global__ __launch_bounds__(KDGeom<KB_KD_TW>::NT) __attribute__((amdgpu_waves_per_eu(8)))
-void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy)
+void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int members, int items)
 {
     using G = KDGeom<KB_KD_TW>;
     using GW = KDGeom<KD_TW_WIDE, KD_SPR_WIDE>;
@@ -1922,11 +1964,11 @@ void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy
     __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];
     __shared__ __attribute__((aligned(16))) T mbuf[G::NBUF * G::ROWLD];
     __shared__ __attribute__((aligned(16))) T wtab[8 * ROWS_PER_BLOCK];
-    const int n = cy->n;
-    const int total = cy->off_kd[n];
+    const int n = items >= 0 ? members : cy->n;
+    const int total = items >= 0 ? items : cy->off_kd[n];
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
         const int a = find_member(cy->off_kd, n, e);
-        const GridDesc &g = gd[cy->slot[a]];
+        const GridDesc &g = gd[a];
         const int li = e - cy->off_kd[a];
         const int tw = g.kd_wide ? KD_TW_WIDE : KB_KD_TW;
         const int ntx = (g.nx + tw - 1) / tw;
@@ -1935,20 +1977,27 @@ void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy
         const T *fin = (const T *)g.f[kin];
         T *fout = (T *)g.f[kin ^ 1];
         __syncthreads();  // the previous item's LDS rows are consumed
-        const KDTile<T> t{fin, fout, g.Fkick, g.dt, g.dp, g.dm, g.dm, g.dw, g.dw, g.kbase, g.krel, g.part, g.nx, g.np, 1, tx, ty,
+        KDTile<T> t{fin, fout, g.Fkick, g.dt, g.dp, g.dm, g.dm, g.dw, g.dw, g.kbase, g.krel, g.part, g.nx, g.np, 1, tx, ty,
                           kbuf, mbuf, wtab};
         const bool px = g.bc_x == BC_PERIODIC;
+#define KB_KD(TW, SPR)                                                                         \
+    if (cy->kick[a] == KICK_LAST) {                                                            \
+        t.part = nullptr;                                                                      \
+        if (px)                                                                                \
+            kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, TW, SPR, PF, KD_KICK, 1>(t, e);       \
+        else                                                                                   \
+            kick_drift_tile<T, BC_ZERO, BC_PERIODIC, TW, SPR, PF, KD_KICK, 1>(t, e);           \
+    } else if (px) {                                                                           \
+        kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, TW, SPR, PF, KD_KICK, 2>(t, e);           \
+    } else {                                                                                   \
+        kick_drift_tile<T, BC_ZERO, BC_PERIODIC, TW, SPR, PF, KD_KICK, 2>(t, e);               \
+    }
         if (g.kd_wide) {
-            if (px)
-                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, KD_TW_WIDE, KD_SPR_WIDE, PF, KD_KICK, 2>(t, e);
-            else
-                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, KD_TW_WIDE, KD_SPR_WIDE, PF, KD_KICK, 2>(t, e);
+            KB_KD(KD_TW_WIDE, KD_SPR_WIDE)
         } else {
-            if (px)
-                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, KB_KD_TW, KD_SPR, PF, KD_KICK, 2>(t, e);
-            else
-                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, KB_KD_TW, KD_SPR, PF, KD_KICK, 2>(t, e);
+            KB_KD(KB_KD_TW, KD_SPR)
         }
+#undef KB_KD
     }
 }
 
