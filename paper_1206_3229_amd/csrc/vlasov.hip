@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <mutex>
 
 #include "vlasov_internal.hpp"
@@ -73,27 +74,48 @@ Layout layout_of(const vlasov_params &p)
     const size_t nx = (size_t)p.nx, np = (size_t)p.np;
     double w[MAX_SUB];
     const size_t ns = (size_t)split_weights(p.splitting, w);
+    // written by the host at init, in one copy
     L.drift_m = take(ns * np * sizeof(int32_t));
     L.drift_w = take(ns * np * sizeof(double4));
     L.kd_base = take(ns * (size_t)nblocks(p.np) * sizeof(int32_t));
     L.kd_rel = take(ns * np * sizeof(int32_t));
-    L.part = take((size_t)nblocks(p.np) * nx * sizeof(double));
-    L.rho = take(nx * sizeof(double));
-    L.F = take(nx * sizeof(double));
     L.Fext = take(nx * sizeof(double));
     L.cs = take(nx * sizeof(double));
     L.sn = take(nx * sizeof(double));
     L.ringK = take(nx * sizeof(double));
     L.ringV = take(nx * sizeof(double));
     L.mxmy = take(2 * sizeof(double));
-    L.hist = take((size_t)p.hist_cap * 2 * sizeof(double));
     L.hcount = take(sizeof(int64_t));
+    L.gs_g = take(2 * sizeof(double));
+    L.part = take((size_t)nblocks(p.np) * nx * sizeof(double));  // first slice that the device writes
+    L.rho = take(nx * sizeof(double));
+    L.F = take(nx * sizeof(double));
+    L.hist = take((size_t)p.hist_cap * 2 * sizeof(double));
     L.mom_out = take(10 * sizeof(double));
     L.mom_col = take(6 * nx * sizeof(double));
     L.mom_phi = take(nx * sizeof(double));
-    L.gs_g = take(2 * sizeof(double));
     L.total = o;
     return L;
+}
+
+int read_raw(vlasov_ctx *c, std::unique_ptr<char[]> &raw)
+{
+    const size_t bytes = (size_t)c->P.nx * (size_t)c->P.np * c->s;
+    raw.reset(new char[bytes]);
+    HIP_TRY(hipMemcpyAsync(raw.get(), c->fcur(), bytes, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return VLASOV_OK;
+}
+
+void widen(const char *raw, const vlasov_params &P, double *dst)
+{
+    const size_t N = (size_t)P.nx * (size_t)P.np;
+    if (P.storage == VLASOV_F32) {
+        const float *s = reinterpret_cast<const float *>(raw);
+        for (size_t k = 0; k < N; ++k) dst[k] = (double)s[k];
+    } else {
+        memcpy(dst, raw, N * sizeof(double));
+    }
 }
 
 std::string validate(const vlasov_params *p)
@@ -295,24 +317,13 @@ int upload_kd_tables(vlasov_ctx *c)
     return VLASOV_OK;
 }
 
-void to_host_f(const vlasov_ctx *c, const void *src, double *dst)
-{
-    const size_t N = (size_t)c->P.nx * (size_t)c->P.np;
-    if (c->P.storage == VLASOV_F32) {
-        const float *s = (const float *)src;
-        for (size_t k = 0; k < N; ++k) dst[k] = (double)s[k];
-    } else {
-        memcpy(dst, src, N * sizeof(double));
-    }
-}
-
 int upload_f(vlasov_ctx *c, const double *f_host)
 {
     const size_t N = (size_t)c->P.nx * (size_t)c->P.np;
     if (c->P.storage == VLASOV_F32) {
-        std::vector<float> tmp(N);
+        const std::unique_ptr<float[]> tmp(new float[N]);
         for (size_t k = 0; k < N; ++k) tmp[k] = (float)f_host[k];
-        HIP_TRY(hipMemcpyAsync(c->fcur(), tmp.data(), N * sizeof(float), hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(hipMemcpyAsync(c->fcur(), tmp.get(), N * sizeof(float), hipMemcpyHostToDevice, c->stream));
         HIP_TRY(hipStreamSynchronize(c->stream));
     } else {
         HIP_TRY(hipMemcpyAsync(c->fcur(), f_host, N * sizeof(double), hipMemcpyHostToDevice, c->stream));
@@ -390,6 +401,75 @@ int graph_steps(vlasov_ctx *c)
 
 }  // namespace
 
+namespace vlasov_detail {
+
+int enqueue_moments(vlasov_ctx *c)
+{
+    const vlasov_params &P = c->P;
+    const int nx = (int)P.nx;
+    double *scratch = (double *)c->fnext();  // the idle buffer of the pair
+    double *col = c->at<double>(c->L.mom_col);
+    double *phi = c->at<double>(c->L.mom_phi);
+    double *res = c->at<double>(c->L.mom_out);
+    const dim3 grid((unsigned)((nx + 255) / 256), (unsigned)c->nblk), cgrid((unsigned)((nx + 15) / 16));
+    const int nblk = (int)c->nblk;
+#define MOM_BLOCKS(SETS)                                                                                                 \
+    if (P.storage == VLASOV_F32)                                                                                        \
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks<float, SETS>, grid, dim3(256), (const float *)c->fcur(), scratch, \
+               nx, (int)P.np, nblk, P.pmin, c->dp);                                                                     \
+    else                                                                                                                \
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks<double, SETS>, grid, dim3(256), (const double *)c->fcur(),        \
+               scratch, nx, (int)P.np, nblk, P.pmin, c->dp)
+    // six planes of block sums in one pass where the idle buffer holds them
+    // (always but for FP32 grids of 17 to 23 and 33 to 35 rows), else four
+    // and two
+    if (6 * (size_t)nblk * sizeof(double) <= (size_t)P.np * c->s) {
+        MOM_BLOCKS(3);
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<6>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 0);
+    } else {
+        MOM_BLOCKS(1);
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<4>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 0);
+        MOM_BLOCKS(2);
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<2>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 4);
+    }
+#undef MOM_BLOCKS
+    double wcoef = 0.0;
+    if (P.model == VLASOV_MODEL_RING) {
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_phi<true>, dim3((unsigned)((nx + 3) / 4)), dim3(256), col,
+               c->at<double>(c->L.ringV), phi, nx);
+        wcoef = (0.5 * c->dx) * c->dx;
+    } else if (P.model == VLASOV_MODEL_SHEET) {
+        launch(c, VLASOV_K_MOMENTS, vk::k_mom_phi<false>, dim3((unsigned)((nx + 3) / 4)), dim3(256), col,
+               (const double *)nullptr, phi, nx);
+        wcoef = (((M_PI * P.sheet_G) * c->dx) * c->dx) * c->dx;
+    }
+    launch(c, VLASOV_K_MOMENTS, vk::k_mom_final, dim3(1), dim3(576), col, phi, c->at<double>(c->L.cs),
+           c->at<double>(c->L.sn), res, nx, c->dx, (int)P.model, wcoef);
+    return check_launch("moments");
+}
+
+int fetch_moments(vlasov_ctx *c, vlasov_moments_t *out)
+{
+    double h[10];
+    HIP_TRY(hipMemcpyAsync(h, c->ws + c->L.mom_out, sizeof h, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    out->mass = h[0];
+    out->momentum = h[1];
+    out->kinetic = h[2];
+    out->potential = h[3];
+    out->energy = h[4];
+    out->mx = h[5];
+    out->my = h[6];
+    out->l2 = h[7];
+    out->entropy = h[8];
+    out->neg_mass = h[9];
+    for (double v : h)
+        if (!isfinite(v)) return fail(VLASOV_E_NONFINITE, "non-finite diagnostic");
+    return VLASOV_OK;
+}
+
+}  // namespace vlasov_detail
+
 extern "C" {
 
 const char *vlasov_last_error(void) { return g_err.c_str(); }
@@ -442,9 +522,13 @@ int vlasov_init(const vlasov_params *p, const double *f0_host, void *f_dev, void
     // by p_j tau_k / dx with tau_k = (w_k dt)/2 (dt/2 for the Strang step).
     c->nsub = split_weights(p->splitting, c->wsub);
     c->steps_done = 0;
-    const size_t ntab = (size_t)c->nsub * (size_t)p->np;
-    c->h_dm.resize(ntab);
-    c->h_dw.resize(ntab);
+    // All tables are written into one image of the workspace's first slices
+    // (zeros elsewhere) and uploaded by one copy.
+    const size_t ntab = (size_t)c->nsub * (size_t)p->np, image_bytes = c->L.part;
+    std::vector<double4> image(image_bytes / sizeof(double4), make_double4(0.0, 0.0, 0.0, 0.0));
+    auto slice = [&](size_t off) { return reinterpret_cast<char *>(image.data()) + off; };
+    int32_t *dm = reinterpret_cast<int32_t *>(slice(c->L.drift_m));
+    double4 *dw = reinterpret_cast<double4 *>(slice(c->L.drift_w));
     c->h_mfull.resize(ntab);
     for (int k = 0; k < c->nsub; ++k) {
         const double tau = 0.5 * (c->wsub[k] * p->dt);
@@ -452,22 +536,27 @@ int vlasov_init(const vlasov_params *p, const double *f0_host, void *f_dev, void
             const size_t e = (size_t)k * (size_t)p->np + (size_t)j;
             const double pj = p->pmin + (double)j * c->dp;
             const vk::Foot ft = vk::foot_of_shift((pj * tau) / c->dx);
-            c->h_dm[e] = vk::reduce_offset(ft.m, p->nx, p->bc_x);
-            c->h_dw[e] = make_double4(ft.a, ft.b, ft.g, ft.d);
+            dm[e] = vk::reduce_offset(ft.m, p->nx, p->bc_x);
+            dw[e] = make_double4(ft.a, ft.b, ft.g, ft.d);
             // offsets as the drift uses them: the exact foot on a periodic axis
             // (the windows of a tile are then one contiguous range mod nx), the
             // clamped one with zero extension
-            c->h_mfull[e] = p->bc_x == VLASOV_BC_PERIODIC ? ft.m : (int64_t)c->h_dm[e];
+            c->h_mfull[e] = p->bc_x == VLASOV_BC_PERIODIC ? ft.m : (int64_t)dm[e];
         }
     }
     build_kd_tables(c, c->tune.kick_drift_blocks);
-    // Model tables.
-    std::vector<double> cs((size_t)p->nx), sn((size_t)p->nx), K((size_t)p->nx, 0.0), V((size_t)p->nx, 0.0);
-    for (int64_t i = 0; i < p->nx; ++i) {
-        const double th = p->xmin + (double)i * c->dx;
-        cs[i] = cos(th);
-        sn[i] = sin(th);
-    }
+    memcpy(slice(c->L.kd_base), c->h_kd_base.data(), c->h_kd_base.size() * sizeof(int32_t));
+    memcpy(slice(c->L.kd_rel), c->h_kd_rel.data(), c->h_kd_rel.size() * sizeof(int32_t));
+    // Model tables: cos and sin of the nodes for the models with a
+    // magnetization.
+    double *cs = reinterpret_cast<double *>(slice(c->L.cs)), *sn = reinterpret_cast<double *>(slice(c->L.sn));
+    double *K = reinterpret_cast<double *>(slice(c->L.ringK)), *V = reinterpret_cast<double *>(slice(c->L.ringV));
+    if (p->model == VLASOV_MODEL_HMF || p->model == VLASOV_MODEL_RING)
+        for (int64_t i = 0; i < p->nx; ++i) {
+            const double th = p->xmin + (double)i * c->dx;
+            cs[i] = cos(th);
+            sn[i] = sin(th);
+        }
     if (p->model == VLASOV_MODEL_RING) {
         // eq. (ringpot): V(d) = -1/sqrt(q), V'(d) = sin d / (q sqrt q),
         // q = 2 (1 + eps - cos d); V' made exactly odd, V exactly even.
@@ -493,39 +582,19 @@ int vlasov_init(const vlasov_params *p, const double *f0_host, void *f_dev, void
     }
     // Recursion coefficients of the (1, 4, 1) operator of eq. (tridiagsys):
     // its root r = sqrt(3) - 2 and the factor -6 r of D
-    std::vector<double> gs(2);
+    double *gs = reinterpret_cast<double *>(slice(c->L.gs_g));
     gs[0] = sqrt(3.0) - 2.0;
     gs[1] = -6.0 * gs[0];
-    const size_t nxb = (size_t)p->nx * sizeof(double);
     auto cleanup_fail = [&](int rc) {
         delete c;
         return rc;
     };
     int rc = VLASOV_OK;
-    const struct {
-        size_t off;
-        const void *src;
-        size_t bytes;
-    } ups[] = {{c->L.drift_m, c->h_dm.data(), ntab * sizeof(int32_t)},
-               {c->L.drift_w, c->h_dw.data(), ntab * sizeof(double4)},
-               {c->L.kd_base, c->h_kd_base.data(), c->h_kd_base.size() * sizeof(int32_t)},
-               {c->L.kd_rel, c->h_kd_rel.data(), c->h_kd_rel.size() * sizeof(int32_t)},
-               {c->L.cs, cs.data(), nxb},
-               {c->L.sn, sn.data(), nxb},
-               {c->L.ringK, K.data(), nxb},
-               {c->L.ringV, V.data(), nxb},
-               {c->L.gs_g, gs.data(), gs.size() * sizeof(double)}};
-    for (const auto &u : ups) {
-        hipError_t e = hipMemcpyAsync(c->ws + u.off, u.src, u.bytes, hipMemcpyHostToDevice, c->stream);
-        if (e != hipSuccess) return cleanup_fail(fail(VLASOV_E_HIP, std::string("table upload: ") + hipGetErrorString(e)));
-    }
-    if (hipMemsetAsync(c->ws + c->L.Fext, 0, nxb, c->stream) != hipSuccess ||
-        hipMemsetAsync(c->ws + c->L.hcount, 0, sizeof(int64_t), c->stream) != hipSuccess ||
-        hipMemsetAsync(c->ws + c->L.mxmy, 0, 2 * sizeof(double), c->stream) != hipSuccess)
-        return cleanup_fail(fail(VLASOV_E_HIP, "workspace clear failed"));
+    const hipError_t e = hipMemcpyAsync(c->ws, image.data(), image_bytes, hipMemcpyHostToDevice, c->stream);
+    if (e != hipSuccess) return cleanup_fail(fail(VLASOV_E_HIP, std::string("table upload: ") + hipGetErrorString(e)));
     if (f0_host) {
         if ((rc = upload_f(c, f0_host)) != VLASOV_OK) return cleanup_fail(rc);
-    } else if (hipStreamSynchronize(c->stream) != hipSuccess) {  // the host tables above are locals
+    } else if (hipStreamSynchronize(c->stream) != hipSuccess) {  // the image is a local
         return cleanup_fail(fail(VLASOV_E_HIP, "table upload failed"));
     }
     *out = c;
@@ -663,64 +732,8 @@ int vlasov_kick(vlasov_ctx *c)
 int vlasov_moments(vlasov_ctx *c, vlasov_moments_t *out)
 {
     if (!c || !out) return fail(VLASOV_E_INVAL, "NULL argument");
-    const vlasov_params &P = c->P;
-    const int nx = (int)P.nx;
-    double *scratch = (double *)c->fnext();  // the idle buffer of the pair
-    double *col = c->at<double>(c->L.mom_col);
-    double *phi = c->at<double>(c->L.mom_phi);
-    double *res = c->at<double>(c->L.mom_out);
-    const dim3 grid((unsigned)((nx + 255) / 256), (unsigned)c->nblk), cgrid((unsigned)((nx + 15) / 16));
-    const int nblk = (int)c->nblk;
-#define MOM_BLOCKS(SETS)                                                                                                 \
-    if (P.storage == VLASOV_F32)                                                                                        \
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks<float, SETS>, grid, dim3(256), (const float *)c->fcur(), scratch, \
-               nx, (int)P.np, nblk, P.pmin, c->dp);                                                                     \
-    else                                                                                                                \
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_blocks<double, SETS>, grid, dim3(256), (const double *)c->fcur(),        \
-               scratch, nx, (int)P.np, nblk, P.pmin, c->dp)
-    // six planes of block sums in one pass where the idle buffer holds them
-    // (always but for FP32 grids of 17 to 23 and 33 to 35 rows), else four
-    // and two
-    if (6 * (size_t)nblk * sizeof(double) <= (size_t)P.np * c->s) {
-        MOM_BLOCKS(3);
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<6>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 0);
-    } else {
-        MOM_BLOCKS(1);
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<4>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 0);
-        MOM_BLOCKS(2);
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_cols<2>, cgrid, dim3(1024), scratch, col, nx, nblk, c->dp, 4);
-    }
-#undef MOM_BLOCKS
-    double wcoef = 0.0;
-    if (P.model == VLASOV_MODEL_RING) {
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_phi<true>, dim3((unsigned)((nx + 3) / 4)), dim3(256), col,
-               c->at<double>(c->L.ringV), phi, nx);
-        wcoef = (0.5 * c->dx) * c->dx;
-    } else if (P.model == VLASOV_MODEL_SHEET) {
-        launch(c, VLASOV_K_MOMENTS, vk::k_mom_phi<false>, dim3((unsigned)((nx + 3) / 4)), dim3(256), col,
-               (const double *)nullptr, phi, nx);
-        wcoef = (((M_PI * P.sheet_G) * c->dx) * c->dx) * c->dx;
-    }
-    launch(c, VLASOV_K_MOMENTS, vk::k_mom_final, dim3(1), dim3(576), col, phi, c->at<double>(c->L.cs),
-           c->at<double>(c->L.sn), res, nx, c->dx, (int)P.model, wcoef);
-    int rc = check_launch("moments");
-    if (rc) return rc;
-    double h[10];
-    HIP_TRY(hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    out->mass = h[0];
-    out->momentum = h[1];
-    out->kinetic = h[2];
-    out->potential = h[3];
-    out->energy = h[4];
-    out->mx = h[5];
-    out->my = h[6];
-    out->l2 = h[7];
-    out->entropy = h[8];
-    out->neg_mass = h[9];
-    for (double v : h)
-        if (!isfinite(v)) return fail(VLASOV_E_NONFINITE, "non-finite diagnostic");
-    return VLASOV_OK;
+    const int rc = enqueue_moments(c);
+    return rc == VLASOV_OK ? fetch_moments(c, out) : rc;
 }
 
 int vlasov_mag_history(vlasov_ctx *c, double *mx, double *my, int64_t cap, int64_t *count)
@@ -748,12 +761,10 @@ int vlasov_mag_history(vlasov_ctx *c, double *mx, double *my, int64_t cap, int64
 int vlasov_read_f(vlasov_ctx *c, double *f_host)
 {
     if (!c || !f_host) return fail(VLASOV_E_INVAL, "NULL argument");
-    const size_t bytes = (size_t)c->P.nx * (size_t)c->P.np * c->s;
-    std::vector<char> tmp(bytes);
-    HIP_TRY(hipMemcpyAsync(tmp.data(), c->fcur(), bytes, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    to_host_f(c, tmp.data(), f_host);
-    return VLASOV_OK;
+    std::unique_ptr<char[]> raw;
+    const int rc = read_raw(c, raw);
+    if (rc == VLASOV_OK) widen(raw.get(), c->P, f_host);
+    return rc;
 }
 
 int vlasov_write_f(vlasov_ctx *c, const double *f_host)

@@ -14,6 +14,7 @@
 #include <condition_variable>
 #include <deque>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <thread>
 #include <unordered_map>
@@ -417,7 +418,9 @@ struct vlasov_server {
     struct Entry {
         bool done = false;
         vlasov_result res{};
-        std::vector<double> f;
+        // final f as it is stored; the poll that takes it widens it
+        std::unique_ptr<char[]> f;
+        vlasov_params p{};
     };
     struct Active {
         uint64_t ticket;
@@ -427,6 +430,7 @@ struct vlasov_server {
         bool keep_f;
         double t_submit, t_admit;
         int32_t failed = VLASOV_OK;  // error of the chunk this request was in
+        int moments = VLASOV_OK;     // enqueueing its diagnostics
         int64_t closed_before = 0;   // steps finished before the current chunk
         int64_t fin_chunk = -1;      // the chunk that finishes it (-1: none yet)
         bool in_chunk = false;       // stepped by the chunk being enqueued
@@ -477,12 +481,13 @@ struct vlasov_server {
         }
     }
 
-    void finish(uint64_t ticket, const vlasov_result &r, std::vector<double> &&f)
+    void finish(uint64_t ticket, const vlasov_result &r, const vlasov_params &p, std::unique_ptr<char[]> &&f)
     {
         std::lock_guard<std::mutex> lk(mu);
         Entry &e = entries[ticket];
         e.done = true;
         e.res = r;
+        e.p = p;
         e.f = std::move(f);
     }
 
@@ -532,7 +537,7 @@ void admit(vlasov_server *s)
                 s->release(off, bytes);
                 --s->n_running;
             }
-            s->finish(p.ticket, r, {});
+            s->finish(p.ticket, r, p.req.p, nullptr);
             continue;
         }
         vlasov_server::Active a;
@@ -554,28 +559,35 @@ void admit(vlasov_server *s)
 void retire(vlasov_server *s)
 {
     std::vector<vlasov_server::Active> keep;
+    auto finished = [&](const vlasov_server::Active &a) { return a.m.done() && a.fin_chunk <= s->completed; };
+    // the diagnostics of all of them are enqueued before the first is waited for
+    for (auto &a : s->active)
+        if (finished(a)) {
+            a.ctx->stream = s->ret;
+            if (a.failed == VLASOV_OK) a.moments = enqueue_moments(a.ctx);
+        }
     for (auto &a : s->active) {
-        if (!a.m.done() || a.fin_chunk > s->completed) {
+        if (!finished(a)) {
             keep.push_back(a);
             continue;
         }
-        a.ctx->stream = s->ret;
         vlasov_result r{};
-        std::vector<double> f;
+        std::unique_ptr<char[]> f;
         if (a.failed != VLASOV_OK) {
             // the chunk's kernels may not have run (planning already moved the
             // context to its output buffer): no diagnostics, no f
             r.status = a.failed;
             r.steps_done = a.closed_before;
         } else {
-            r.status = vlasov_moments(a.ctx, &r.m);
+            r.status = a.moments == VLASOV_OK ? fetch_moments(a.ctx, &r.m) : a.moments;
             r.steps_done = a.m.closed;
         }
         if (a.keep_f && a.failed == VLASOV_OK) {
-            f.resize((size_t)a.ctx->P.nx * (size_t)a.ctx->P.np);
-            int rc = vlasov_read_f(a.ctx, f.data());
+            const int rc = read_raw(a.ctx, f);
+            if (rc != VLASOV_OK) f.reset();
             if (rc != VLASOV_OK && r.status == VLASOV_OK) r.status = rc;
         }
+        const vlasov_params params = a.ctx->P;
         r.t_submit = a.t_submit;
         r.t_admit = a.t_admit;
         r.t_done = seconds_since(s->t0);
@@ -585,7 +597,7 @@ void retire(vlasov_server *s)
             s->release(a.off, a.bytes);
             --s->n_running;
         }
-        s->finish(a.ticket, r, std::move(f));
+        s->finish(a.ticket, r, params, std::move(f));
     }
     s->active.swap(keep);
 }
@@ -818,13 +830,18 @@ int vlasov_submit(vlasov_server *s, const vlasov_request *r, const double *f0_ho
 int vlasov_poll(vlasov_server *s, uint64_t ticket, vlasov_result *out, double *f_host)
 {
     if (!s || !out) return fail(VLASOV_E_INVAL, "NULL argument");
-    std::lock_guard<std::mutex> lk(s->mu);
-    auto it = s->entries.find(ticket);
-    if (it == s->entries.end()) return fail(VLASOV_E_NOTFOUND, "unknown ticket");
-    if (!it->second.done) return VLASOV_PENDING;
-    *out = it->second.res;
-    if (f_host && !it->second.f.empty()) memcpy(f_host, it->second.f.data(), it->second.f.size() * sizeof(double));
-    s->entries.erase(it);
+    vlasov_server::Entry e;
+    {
+        std::lock_guard<std::mutex> lk(s->mu);
+        auto it = s->entries.find(ticket);
+        if (it == s->entries.end()) return fail(VLASOV_E_NOTFOUND, "unknown ticket");
+        if (!it->second.done) return VLASOV_PENDING;
+        e = std::move(it->second);
+        s->entries.erase(it);
+    }
+    // not under the lock, which the scheduler takes for every admission and result
+    *out = e.res;
+    if (f_host && e.f) widen(e.f.get(), e.p, f_host);
     return VLASOV_OK;
 }
 

@@ -8,6 +8,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -58,8 +59,8 @@ int split_weights(int scheme, double *w);
 // kick-drift tables one per pair of consecutive substeps (kd_base nblk
 // entries, kd_rel np entries each).
 struct Layout {
-    size_t drift_m, drift_w, kd_base, kd_rel, part, rho, F, Fext, cs, sn, ringK, ringV, mxmy, hist, hcount, mom_out,
-        mom_col, mom_phi, gs_g;
+    size_t drift_m, drift_w, kd_base, kd_rel, Fext, cs, sn, ringK, ringV, mxmy, hcount, gs_g;  // written at init
+    size_t part, rho, F, hist, mom_out, mom_col, mom_phi;
     size_t total;
 };
 
@@ -96,9 +97,7 @@ struct vlasov_ctx {
     hipStream_t cap_stream = nullptr;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int gcur_end[2] = {0, 0};  // current buffer after a replay
-    // host copies kept alive for asynchronous uploads
-    std::vector<int32_t> h_dm;
-    std::vector<double4> h_dw;
+    // host copies kept for the tables of other tile heights
     std::vector<int64_t> h_mfull;  // drift foot offset per row, as the fused tables need it
     std::vector<int32_t> h_kd_base, h_kd_rel;
     // substeps of a step (splitting) and steps taken since init (filter schedule)
@@ -172,6 +171,13 @@ inline int check_launch(const char *what)
     if (e != hipSuccess) return fail(VLASOV_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
     return VLASOV_OK;
 }
+
+// The current f as it is stored (synchronises), and its values as doubles.
+int read_raw(vlasov_ctx *c, std::unique_ptr<char[]> &raw);
+void widen(const char *raw, const vlasov_params &P, double *dst);
+// Diagnostics in two parts: the kernels, and their result (synchronises).
+int enqueue_moments(vlasov_ctx *c);
+int fetch_moments(vlasov_ctx *c, vlasov_moments_t *out);
 
 // Launchers (one translation unit per kernel family).  Each enqueues its
 // kernel on the context's stream and, on success, makes the output buffer
