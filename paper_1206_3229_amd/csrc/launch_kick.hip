@@ -1,5 +1,7 @@
 // Kernel launchers of the library, one translation unit per kernel family
 // (compiled in parallel); declared in vlasov_internal.hpp.
+#include <algorithm>
+
 #include "vlasov_internal.hpp"
 
 namespace vlasov_detail {
@@ -80,35 +82,42 @@ int launch_kick_filter(vlasov_ctx *c, double h)
     return rc;
 }
 
-// The kick followed by the filter: one pass with the local spline, the
-// transposed kick and then the filter with the global spline.
-
 // ---------------------------------------------------------------------------
-// Global spline (eq. tridiagsys): one workgroup per line; the kick runs on the
-// rows of the transpose.
+// Global spline (eq. tridiagsys): half drifts of the rows in LDS, the kick down
+// the columns.
 // ---------------------------------------------------------------------------
 template <typename T>
-int gs_drift_t(vlasov_ctx *c, int table, bool partials)
+int gs_drift_t(vlasov_ctx *c, int ta, int tb, bool partials)
 {
     const vlasov_params &P = c->P;
     const T *fin = (const T *)c->fcur();
     T *fout = (T *)c->fnext();
-    const int32_t *dm = c->dm(table);
-    const double4 *dw = c->dw(table);
+    const int32_t *dm1 = c->dm(ta), *dm2 = c->dm(tb >= 0 ? tb : ta);
+    const double4 *dw1 = c->dw(ta), *dw2 = c->dw(tb >= 0 ? tb : ta);
     const double *g = c->at<double>(c->L.gs_g);
-    const double *nof = nullptr;
-    if (P.bc_x == VLASOV_BC_PERIODIC)
-        launch(c, VLASOV_K_DRIFT, vk::k_gs_line<T, vk::BC_PERIODIC, false>, dim3((unsigned)P.np), dim3(vk::GS_NT), fin,
-               fout, (int)P.nx, dm, dw, nof, 0.0, 0.0, g);
-    else
-        launch(c, VLASOV_K_DRIFT, vk::k_gs_line<T, vk::BC_ZERO, false>, dim3((unsigned)P.np), dim3(vk::GS_NT), fin,
-               fout, (int)P.nx, dm, dw, nof, 0.0, 0.0, g);
+    const int n = (int)P.nx, np = (int)P.np;
+    // whole rows per workgroup: 128 threads of short rows (as far as 40 KB of
+    // LDS hold them), one long row
+    const int tpl = vk::gs_threads(n, P.bc_x);
+    const size_t row = (size_t)vk::gs_row(n, P.bc_x) * sizeof(T);
+    const int lpw = std::max(1, std::min(128 / tpl, (int)(40960 / row)));
+    const dim3 grid((unsigned)((np + lpw - 1) / lpw)), block((unsigned)((tpl * lpw + 63) / 64 * 64));
+    const int kid = tb >= 0 ? VLASOV_K_DRIFT2 : VLASOV_K_DRIFT;
+#define GS_ROWS(BC, NPASS)                                                                                          \
+    launch_lds(c, kid, vk::k_gs_rows<T, BC, NPASS>, grid, block, row * (size_t)lpw, fin, fout, n, np, tpl, lpw, dm1, \
+               dw1, dm2, dw2, g)
+    if (P.bc_x == VLASOV_BC_PERIODIC) {
+        if (tb >= 0) GS_ROWS(vk::BC_PERIODIC, 2); else GS_ROWS(vk::BC_PERIODIC, 1);
+    } else {
+        if (tb >= 0) GS_ROWS(vk::BC_ZERO, 2); else GS_ROWS(vk::BC_ZERO, 1);
+    }
+#undef GS_ROWS
     int rc = check_launch("global-spline drift");
     if (rc) return rc;
     c->cur ^= 1;
     if (partials) {
-        launch(c, VLASOV_K_DRIFT, vk::k_partials<T>, dim3((unsigned)((P.nx + 255) / 256), (unsigned)c->nblk),
-               dim3(256), (const T *)c->fcur(), c->at<double>(c->L.part), (int)P.nx, (int)P.np);
+        launch(c, kid, vk::k_partials<T>, dim3((unsigned)((P.nx + 255) / 256), (unsigned)c->nblk), dim3(256),
+               (const T *)c->fcur(), c->at<double>(c->L.part), n, np);
         rc = check_launch("partial sums");
     }
     return rc;
@@ -119,24 +128,21 @@ int gs_kick_t(vlasov_ctx *c, double h)
 {
     const vlasov_params &P = c->P;
     const int nx = (int)P.nx, np = (int)P.np;
-    T *A = (T *)c->fcur(), *B = (T *)c->fnext();
-    const unsigned t1 = (unsigned)(((nx + 63) / 64) * ((np + 63) / 64));
-    launch(c, VLASOV_K_KICK, vk::k_transpose<T>, dim3(t1), dim3(256), (const T *)A, B, np, nx);  // B = A^T
-    const int32_t *nodm = nullptr;
-    const double4 *nodw = nullptr;
+    const int ntx = (nx + 63) / 64, nty = (np + 4 * vk::GS_RK - 1) / (4 * vk::GS_RK);
+    const dim3 grid((unsigned)vk::xcd_grid(ntx, nty));
+    const T *fin = (const T *)c->fcur();
+    T *fout = (T *)c->fnext();
     const double *g = c->at<double>(c->L.gs_g);
     if (P.bc_p == VLASOV_BC_PERIODIC)
-        launch(c, VLASOV_K_KICK, vk::k_gs_line<T, vk::BC_PERIODIC, true>, dim3((unsigned)nx), dim3(vk::GS_NT),
-               (const T *)B, A, np, nodm, nodw, force_ptr(c), h, c->dp, g);
+        launch(c, VLASOV_K_KICK, vk::k_gs_cols<T, vk::BC_PERIODIC>, grid, dim3(256), fin, fout, nx, np, force_ptr(c), h,
+               c->dp, g, ntx, nty);
     else
-        launch(c, VLASOV_K_KICK, vk::k_gs_line<T, vk::BC_ZERO, true>, dim3((unsigned)nx), dim3(vk::GS_NT),
-               (const T *)B, A, np, nodm, nodw, force_ptr(c), h, c->dp, g);
-    launch(c, VLASOV_K_KICK, vk::k_transpose<T>, dim3(t1), dim3(256), (const T *)A, B, nx, np);  // B = A^T
+        launch(c, VLASOV_K_KICK, vk::k_gs_cols<T, vk::BC_ZERO>, grid, dim3(256), fin, fout, nx, np, force_ptr(c), h, c->dp,
+               g, ntx, nty);
     int rc = check_launch("global-spline kick");
     if (rc == VLASOV_OK) c->cur ^= 1;
     return rc;
 }
-
 
 template int launch_kick<float>(vlasov_ctx *, double);
 template int launch_kick<double>(vlasov_ctx *, double);
@@ -144,8 +150,8 @@ template int launch_filter<float>(vlasov_ctx *);
 template int launch_filter<double>(vlasov_ctx *);
 template int launch_kick_filter<float>(vlasov_ctx *, double);
 template int launch_kick_filter<double>(vlasov_ctx *, double);
-template int gs_drift_t<float>(vlasov_ctx *, int, bool);
-template int gs_drift_t<double>(vlasov_ctx *, int, bool);
+template int gs_drift_t<float>(vlasov_ctx *, int, int, bool);
+template int gs_drift_t<double>(vlasov_ctx *, int, int, bool);
 template int gs_kick_t<float>(vlasov_ctx *, double);
 template int gs_kick_t<double>(vlasov_ctx *, double);
 

@@ -150,17 +150,13 @@ std::string validate(const vlasov_params *p)
 
 namespace {
 
-int gs_drift(vlasov_ctx *c, int table, bool partials);
+int gs_drift(vlasov_ctx *c, int ta, int tb, bool partials);
 int gs_kick(vlasov_ctx *c, double h);
 
 // The half drift of table ta, then (tb >= 0) that of table tb, in one pass.
 int drift(vlasov_ctx *c, int ta, int tb, bool partials)
 {
-    if (c->P.spline == VLASOV_SPLINE_GS) {  // two half drifts are two passes
-        int rc = gs_drift(c, ta, partials && tb < 0);
-        if (rc == VLASOV_OK && tb >= 0) rc = gs_drift(c, tb, partials);
-        return rc;
-    }
+    if (c->P.spline == VLASOV_SPLINE_GS) return gs_drift(c, ta, tb, partials);
     return c->P.storage == VLASOV_F32 ? launch_drift<float>(c, ta, tb, partials)
                                       : launch_drift<double>(c, ta, tb, partials);
 }
@@ -228,13 +224,9 @@ int kick_filter(vlasov_ctx *c, double h)
     return c->P.storage == VLASOV_F32 ? launch_kick_filter<float>(c, h) : launch_kick_filter<double>(c, h);
 }
 
-// ---------------------------------------------------------------------------
-// Global spline (eq. tridiagsys): one workgroup per line; the kick runs on the
-// rows of the transpose.
-// ---------------------------------------------------------------------------
-int gs_drift(vlasov_ctx *c, int table, bool partials)
+int gs_drift(vlasov_ctx *c, int ta, int tb, bool partials)
 {
-    return c->P.storage == VLASOV_F32 ? gs_drift_t<float>(c, table, partials) : gs_drift_t<double>(c, table, partials);
+    return c->P.storage == VLASOV_F32 ? gs_drift_t<float>(c, ta, tb, partials) : gs_drift_t<double>(c, ta, tb, partials);
 }
 
 int gs_kick(vlasov_ctx *c, double h)
@@ -530,13 +522,14 @@ int vlasov_init(const vlasov_params *p, const double *f0_host, void *f_dev, void
     int32_t *dm = reinterpret_cast<int32_t *>(slice(c->L.drift_m));
     double4 *dw = reinterpret_cast<double4 *>(slice(c->L.drift_w));
     c->h_mfull.resize(ntab);
+    const int margin = p->spline == VLASOV_SPLINE_GS ? vk::FOOT_MARGIN_GS : vk::FOOT_MARGIN;
     for (int k = 0; k < c->nsub; ++k) {
         const double tau = 0.5 * (c->wsub[k] * p->dt);
         for (int64_t j = 0; j < p->np; ++j) {
             const size_t e = (size_t)k * (size_t)p->np + (size_t)j;
             const double pj = p->pmin + (double)j * c->dp;
             const vk::Foot ft = vk::foot_of_shift((pj * tau) / c->dx);
-            dm[e] = vk::reduce_offset(ft.m, p->nx, p->bc_x);
+            dm[e] = vk::reduce_offset(ft.m, p->nx, p->bc_x, margin);
             dw[e] = make_double4(ft.a, ft.b, ft.g, ft.d);
             // offsets as the drift uses them: the exact foot on a periodic axis
             // (the windows of a tile are then one contiguous range mod nx), the

@@ -152,17 +152,23 @@ inline hipEvent_t take_event(vlasov_ctx *c)
 // launch carries its own start/stop events (recorded by the dispatch itself,
 // so no extra packets sit between consecutive kernels).
 template <typename... KArgs, typename... Args>
-void launch(vlasov_ctx *c, int kid, void (*kernel)(KArgs...), dim3 grid, dim3 block, Args... args)
+void launch_lds(vlasov_ctx *c, int kid, void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, Args... args)
 {
     if (c->prof) {
         hipEvent_t a = take_event(c), b = take_event(c);
         if (a && b) {
-            hipExtLaunchKernelGGL(kernel, grid, block, 0, c->stream, a, b, 0, static_cast<KArgs>(args)...);
+            hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, c->stream, a, b, 0, static_cast<KArgs>(args)...);
             c->recs.push_back({kid, a, b});
             return;
         }
     }
-    kernel<<<grid, block, 0, c->stream>>>(static_cast<KArgs>(args)...);
+    kernel<<<grid, block, lds, c->stream>>>(static_cast<KArgs>(args)...);
+}
+
+template <typename... KArgs, typename... Args>
+void launch(vlasov_ctx *c, int kid, void (*kernel)(KArgs...), dim3 grid, dim3 block, Args... args)
+{
+    launch_lds(c, kid, kernel, grid, block, 0, args...);
 }
 
 inline int check_launch(const char *what)
@@ -190,8 +196,9 @@ template <typename T> int launch_kick(vlasov_ctx *c, double h);
 // The filter along p; the kick of step size h followed by the filter.
 template <typename T> int launch_filter(vlasov_ctx *c);
 template <typename T> int launch_kick_filter(vlasov_ctx *c, double h);
-// Global spline: half drift of table `table` (and its partial sums); kick.
-template <typename T> int gs_drift_t(vlasov_ctx *c, int table, bool partials);
+// Global spline: half drift of table ta, then (tb >= 0) that of table tb, in one
+// pass, and the partial sums of the result; kick.
+template <typename T> int gs_drift_t(vlasov_ctx *c, int ta, int tb, bool partials);
 template <typename T> int gs_kick_t(vlasov_ctx *c, double h);
 // Kick of substep ta (step size h) fused with the half drifts of tables ta and
 // ta + 1 mod nsub (pair), or with that of table ta alone; `spread` (at most

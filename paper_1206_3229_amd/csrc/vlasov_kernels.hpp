@@ -101,15 +101,18 @@ __host__ __device__ inline Foot foot_of_shift(double shift)
 }
 
 // Foot offset as used by the kernels: reduced to [0, n) on a periodic axis;
-// clamped to +-(n + 16) with zero extension (beyond that every sample is 0).
-__host__ __device__ inline int32_t reduce_offset(int64_t m, int64_t n, int bc)
+// clamped to +-(n + margin) with zero extension (beyond that every sample is 0;
+// with the global spline, whose second derivatives reach 31 cells outside, at a
+// larger margin).
+constexpr int FOOT_MARGIN = 16, FOOT_MARGIN_GS = 64;
+__host__ __device__ inline int32_t reduce_offset(int64_t m, int64_t n, int bc, int margin = FOOT_MARGIN)
 {
     if (bc == BC_PERIODIC) {
         int64_t r = m % n;
         if (r < 0) r += n;
         return (int32_t)r;
     }
-    int64_t lim = n + 16;
+    int64_t lim = n + margin;
     return (int32_t)(m > lim ? lim : (m < -lim ? -lim : m));
 }
 
@@ -129,11 +132,11 @@ __device__ __forceinline__ int wrap_near(int q, int n)
 }
 
 // reduce_offset() of a foot, whose m fits 32 bits (|xi| < 2^31).
-template <int BC>
+template <int BC, int MARGIN = FOOT_MARGIN>
 __device__ __forceinline__ int foot_offset(const Foot &ft, int n)
 {
     const int m = (int)ft.m;
-    return BC == BC_PERIODIC ? wrap_near(m, n) : min(max(m, -(n + 16)), n + 16);
+    return BC == BC_PERIODIC ? wrap_near(m, n) : min(max(m, -(n + MARGIN)), n + MARGIN);
 }
 
 // One sample of a line of n values (stride between samples `stride`) under
@@ -948,157 +951,187 @@ void k_drift(
 // E the shift to the next node and r = sqrt(3) - 2 its root inside the unit
 // circle, so D = -6 r x with y_i = S_i + r y_{i-1} (causal) and x_i = y_i +
 // r x_{i+1} (anticausal): the convolution of S with sqrt(3) r^|k|.  Each
-// thread runs both recursions over a chunk of GS_CH nodes, started GS_K nodes
-// outside its chunk from 0 (|r|^GS_K is below FP64 resolution), so the
-// chunks need no sequential pass.  On a periodic line the recursions wrap;
-// with zero extension they run over the line continued by GS_E zeros at each
-// end, where D decays by |r| per cell (farther feet read D = 0).  One
-// workgroup of 256 threads moves one line of n <= GS_MAX_N samples through
-// LDS (the samples, and S, y and D in turn in a second array), then
-// evaluates the spline of eq. (splinegen) at the feet.  Lines are the rows
-// of f (the drift) or of its transpose (the kick, shift from the force of
-// the column).
+// thread runs both recursions over GS_R cells of a line in its registers,
+// started GS_K nodes outside of them from 0 (|r|^GS_K is below FP64
+// resolution), so a thread needs the samples from GS_K + 1 before its cells to
+// GS_K + 1 after them and nothing from other threads.
 // ---------------------------------------------------------------------------
-constexpr int GS_K = 30, GS_E = GS_K + 2, GS_MAX_N = 4096, GS_NT = 256;
-constexpr int GS_LDS = GS_MAX_N + 2 * GS_E;
-constexpr int GS_CH = (GS_LDS + GS_NT - 1) / GS_NT;  // nodes per thread
+constexpr int GS_K = 30, GS_R = 33, GS_MAX_N = 4096;
 
-template <typename T, int BC, bool KICK>
-static __global__ __launch_bounds__(GS_NT) void k_gs_line(const T *__restrict__ fin, T *__restrict__ fout, int n,
-                                                   const int32_t *__restrict__ dm,
-                                                   const double4 *__restrict__ dw,
-                                                   const double *__restrict__ F, double dt, double dh,
-                                                   const double *__restrict__ gcoef)
+// Values of RC cells from the samples at(0 .. RC + 2 GS_K + 1), 31 before the
+// first cell on (cell u lies between samples u + 31 and u + 32), left in y[0 ..
+// RC).  `again` reads the samples of the cells a second time, so that they are
+// not held in registers meanwhile.
+template <int RC, typename T, typename At, typename Again>
+__device__ __forceinline__ void gs_cells(At at, Again again, T r, T cD, T a, T b, T g, T d, T (&y)[RC + GS_K])
 {
-    __shared__ T fe[GS_LDS], Q[GS_LDS];
-    const int line = blockIdx.x, t = threadIdx.x;
-    const T *src = fin + (size_t)line * n;
-    const T r = (T)gcoef[0], cD = (T)gcoef[1];
-    // working line: the n nodes (periodic, indices mod n) or the extended
-    // line e = i + GS_E, i in [-GS_E, n + GS_E) (zero extension)
-    const int N = BC == BC_PERIODIC ? n : n + 2 * GS_E;
-    {
-        // all GS_CH loads of a thread in flight at once
-        T v[GS_CH];
+    T f0 = at(0), f1 = at(1), acc = T(0);
 #pragma unroll
-        for (int u = 0; u < GS_CH; ++u) {
-            const int e = t + u * GS_NT;
-            const int i = BC == BC_PERIODIC ? e : e - GS_E;
-            v[u] = src[min(max(i, 0), n - 1)];
-        }
-#pragma unroll
-        for (int u = 0; u < GS_CH; ++u) keep_issued(v[u]);
-#pragma unroll
-        for (int u = 0; u < GS_CH; ++u) {
-            const int e = t + u * GS_NT;
-            const int i = BC == BC_PERIODIC ? e : e - GS_E;
-            if (e < N) fe[e] = (i >= 0 && i < n) ? v[u] : T(0);
-        }
+    for (int e = 0; e < RC + 2 * GS_K; ++e) {  // node of sample e + 1
+        const T f2 = at(e + 2);
+        acc = vfma(r, acc, (f0 + f2) - T(2) * f1);
+        if (e >= GS_K) y[e - GS_K] = acc;
+        f0 = f1;
+        f1 = f2;
     }
-    __syncthreads();
-    // a[e] under the boundary rule of the working line; e lies in
-    // [-GS_K, N + GS_K + GS_CH), so two conditional steps wrap it once the
-    // line is longer than that excursion (shorter lines take the division)
-    const bool short_line = n < GS_K + GS_CH + 1;
-    auto at = [&](const T *a, int e) -> T {
-        if (BC == BC_PERIODIC) {
-            if (short_line) return a[wrap(e, n)];
-            const int q = e < 0 ? e + n : e;
-            return a[q >= n ? q - n : q];
-        }
-        return (e >= 0 && e < N) ? a[e] : T(0);
-    };
-    for (int e = t; e < N; e += GS_NT)
-        Q[e] = (BC != BC_PERIODIC && (e == 0 || e == N - 1)) ? T(0)
-                                                             : (at(fe, e - 1) + at(fe, e + 1)) - T(2) * fe[e];
-    __syncthreads();
-    const int c0 = t * GS_CH;  // this thread's chunk [c0, c0 + GS_CH)
-    const bool mine = c0 < N;
-    T w[GS_CH];
-    if (mine) {  // causal recursion y_e = S_e + r y_{e-1}
-        T acc = T(0);
-        for (int k = GS_K; k >= 1; --k) acc = vfma(r, acc, at(Q, c0 - k));
+    acc = T(0);
 #pragma unroll
-        for (int u = 0; u < GS_CH; ++u) {
-            acc = vfma(r, acc, at(Q, c0 + u));
-            w[u] = acc;
-        }
+    for (int e = RC + GS_K - 1; e >= 0; --e) {
+        acc = vfma(r, acc, y[e]);
+        if (e <= RC) y[e] = cD * acc;
     }
-    __syncthreads();
-    if (mine)
+    f0 = again(GS_K + 1);
 #pragma unroll
-        for (int u = 0; u < GS_CH; ++u)
-            if (c0 + u < N) Q[c0 + u] = w[u];
-    __syncthreads();
-    if (mine) {  // anticausal recursion x_e = y_e + r x_{e+1}, D = -6 r x
-        T acc = T(0);
-        for (int k = GS_K + GS_CH - 1; k >= GS_CH; --k) acc = vfma(r, acc, at(Q, c0 + k));
-#pragma unroll
-        for (int u = GS_CH - 1; u >= 0; --u) {
-            acc = vfma(r, acc, at(Q, c0 + u));
-            w[u] = cD * acc;
-        }
-    }
-    __syncthreads();
-    if (mine)
-#pragma unroll
-        for (int u = 0; u < GS_CH; ++u)
-            if (c0 + u < N) Q[c0 + u] = w[u];
-    __syncthreads();
-    // foot of the line's shift
-    int m;
-    T a, b, gg, d;
-    if (KICK) {
-        const Foot ft = foot_of_shift((F[line] * dt) / dh);
-        m = reduce_offset(ft.m, n, BC);
-        a = (T)ft.a;
-        b = (T)ft.b;
-        gg = (T)ft.g;
-        d = (T)ft.d;
-    } else {
-        m = dm[line];
-        const double4 wv = dw[line];
-        a = (T)wv.x;
-        b = (T)wv.y;
-        gg = (T)wv.z;
-        d = (T)wv.w;
-    }
-    T *dst = fout + (size_t)line * n;
-    for (int i = t; i < n; i += GS_NT) {
-        const int k = i + m;  // cell [k, k + 1]
-        T fk, fk1, Dk, Dk1;
-        if (BC == BC_PERIODIC) {
-            const int q = k >= n ? k - n : k, q1 = q + 1 == n ? 0 : q + 1;  // m in [0, n)
-            fk = fe[q];
-            fk1 = fe[q1];
-            Dk = Q[q];
-            Dk1 = Q[q1];
-        } else {
-            fk = (k >= 0 && k < n) ? fe[k + GS_E] : T(0);
-            fk1 = (k + 1 >= 0 && k + 1 < n) ? fe[k + 1 + GS_E] : T(0);
-            Dk = (k > -GS_E && k < n + GS_E - 1) ? Q[k + GS_E] : T(0);
-            Dk1 = (k + 1 > -GS_E && k + 1 < n + GS_E - 1) ? Q[k + 1 + GS_E] : T(0);
-        }
-        dst[i] = spline(a, b, gg, d, fk, fk1, Dk, Dk1);
+    for (int u = 0; u < RC; ++u) {
+        f1 = again(GS_K + 2 + u);
+        y[u] = spline(a, b, g, d, f0, f1, y[u], y[u + 1]);
+        f0 = f1;
     }
 }
 
-// Transpose of an rows x cols array through 64 x 64 LDS tiles (the kick of
-// the global spline runs on the rows of the transpose).
-template <typename T>
-static __global__ __launch_bounds__(256) void k_transpose(const T *__restrict__ in, T *__restrict__ out, int rows,
-                                                   int cols)
+// Threads per row of the drift (with zero extension 32 more cells on each
+// side, where D decays to nothing) and samples of a row in LDS (GS_R of halo
+// before the first cell and after the last one).  GS_R is odd, so that the
+// threads of a row, GS_R cells apart, read distinct banks, and a zero-extended
+// row of 2048 takes exactly one wavefront.
+__host__ __device__ inline int gs_threads(int n, int bc) { return (n + (bc == BC_PERIODIC ? 0 : 64) + GS_R - 1) / GS_R; }
+__host__ __device__ inline int gs_row(int n, int bc) { return GS_R * (gs_threads(n, bc) + 2); }
+
+// The half drift of table 1 and (NPASS = 2) that of table 2, lpw rows per
+// workgroup, the rows in LDS between the two.  A row is shifted by whole cells
+// only when it is stored; in between, cells keep their place (place c of the
+// second pass is column c - m1).  2048^2 FP64: 16 us, 21 for two half drifts
+// (34 and 68 with both recursions through LDS, six barriers, and two workgroups
+// per compute unit); the rows' traffic alone takes 11.
+template <typename T, int BC, int NPASS>
+static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fin, T *__restrict__ fout, int n, int lines,
+                                                 int tpl, int lpw, const int32_t *__restrict__ dm1,
+                                                 const double4 *__restrict__ dw1, const int32_t *__restrict__ dm2,
+                                                 const double4 *__restrict__ dw2, const double *__restrict__ gcoef)
 {
-    __shared__ T tile[64][65];
-    const int tcols = (cols + 63) / 64;
-    const int bx = blockIdx.x % tcols, by = blockIdx.x / tcols;
-    const int c0 = bx * 64, r0 = by * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int r = ty; r < 64; r += 4)
-        if (r0 + r < rows && c0 + tx < cols) tile[r][tx] = in[(size_t)(r0 + r) * cols + c0 + tx];
+    extern __shared__ __attribute__((aligned(16))) char gs_lds[];
+    constexpr int Z = BC == BC_PERIODIC ? 0 : 32;  // cells before column 0
+    constexpr int H = GS_R;                        // sample e of the row is column e - H - Z
+    const int l = threadIdx.x / tpl, tt = threadIdx.x - l * tpl;
+    const int line = blockIdx.x * lpw + l;
+    const bool mine = l < lpw && line < lines;
+    T *row = reinterpret_cast<T *>(gs_lds) + (size_t)min(l, lpw - 1) * gs_row(n, BC);
+    const int NL = GS_R * (tpl + 2);
+    if (mine) {
+        const T *src = fin + (size_t)line * n;
+        constexpr int NB = 18;
+        for (int e0 = tt; e0 < NL; e0 += NB * tpl) {
+            T v[NB];
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int c = e0 + u * tpl - H - Z;
+                v[u] = BC == BC_PERIODIC ? src[wrap_near(c, n)] : src[min(max(c, 0), n - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) keep_issued(v[u]);
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int e = e0 + u * tpl, c = e - H - Z;
+                if (e < NL) row[e] = BC == BC_PERIODIC || (c >= 0 && c < n) ? v[u] : T(0);
+            }
+        }
+    }
     __syncthreads();
-    for (int c = ty; c < 64; c += 4)
-        if (c0 + c < cols && r0 + tx < rows) out[(size_t)(c0 + c) * rows + r0 + tx] = tile[tx][c];
+    const T r = (T)gcoef[0], cD = (T)gcoef[1];
+    T *mid = row + GS_R * tt + H;  // first cell of this thread
+    int shift = 0;
+#pragma unroll
+    for (int pass = 0; pass < NPASS; ++pass) {
+        T y[GS_R + GS_K];
+        const int m = mine ? (pass == 0 ? dm1 : dm2)[line] : 0;
+        if (mine) {
+            const double4 w = (pass == 0 ? dw1 : dw2)[line];
+            int o = 0;
+            __asm__ __volatile__("" : "+v"(o));  // the second reads are reads
+            gs_cells<GS_R>([&](int s) { return mid[s - GS_K - 1]; }, [&](int s) { return mid[o + s - GS_K - 1]; }, r, cD,
+                           (T)w.x, (T)w.y, (T)w.z, (T)w.w, y);
+        }
+        shift += m;
+        __syncthreads();
+        if (mine) {
+#pragma unroll
+            for (int u = 0; u < GS_R; ++u) {
+                T v = y[u];
+                if (BC == BC_ZERO && pass + 1 < NPASS) {  // values outside the grid are zeros
+                    const int i = GS_R * tt + u - Z - m;
+                    v = i >= 0 && i < n ? v : T(0);
+                }
+                mid[u] = v;
+            }
+        }
+        __syncthreads();
+        if (BC == BC_PERIODIC && pass + 1 < NPASS) {  // the halos again
+            if (mine)
+                for (int e = tt; e < NL - n; e += tpl) {
+                    const int h = e < H ? e : e + n;
+                    row[h] = row[wrap(h - H, n) + H];
+                }
+            __syncthreads();
+        }
+    }
+    if (mine) {
+        T *dst = fout + (size_t)line * n;
+        if (BC == BC_PERIODIC) shift = wrap(shift, n);
+        for (int i = tt; i < n; i += tpl) {
+            int c = i + shift;
+            if (BC == BC_PERIODIC) {
+                c = c >= n ? c - n : c;
+                dst[i] = row[c + H];
+            } else {
+                dst[i] = c >= -Z && c < GS_R * tpl - Z ? row[c + Z + H] : T(0);
+            }
+        }
+    }
+}
+
+// The kick: one thread per column and GS_RK rows, the samples read down the
+// column (the lanes of a wavefront read adjacent columns of the same rows, and
+// the rows that two chunks share come from the caches).  2048^2 FP64: 24 us (70
+// with two transposes around a sweep of rows); 16 rows a thread 29, and three
+// waves per SIMD, which spill, 40.
+constexpr int GS_RK = 32;
+template <typename T, int BC>
+static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void k_gs_cols(const T *__restrict__ fin, T *__restrict__ fout, int nx, int np, const double *__restrict__ F, double dt,
+               double dp, const double *__restrict__ gcoef, int ntx, int nty)
+{
+    int tx, ty;
+    if (!xcd_tile(ntx, nty, tx, ty)) return;
+    const int i = min(tx * 64 + ((int)threadIdx.x & 63), nx - 1);  // lanes past the last column repeat it
+    const int j0 = (ty * 4 + ((int)threadIdx.x >> 6)) * GS_RK;
+    if (j0 >= np) return;
+    const Foot ft = foot_of_shift((F[i] * dt) / dp);
+    const int m = foot_offset<BC, FOOT_MARGIN_GS>(ft, np);
+    const size_t ld = (size_t)nx;
+    int q0 = j0 + m - GS_K - 1;  // row of sample 0
+    if (BC == BC_PERIODIC) q0 = wrap_near(q0, np);
+    const T r = (T)gcoef[0], cD = (T)gcoef[1], a = (T)ft.a, b = (T)ft.b, g = (T)ft.g, d = (T)ft.d;
+    T y[GS_RK + GS_K];
+    int o = 0;
+    __asm__ __volatile__("" : "+v"(o));  // the second reads are reads
+    if (__builtin_amdgcn_readfirstlane((int)__all(q0 >= 0 && q0 + GS_RK + 2 * GS_K + 2 <= np))) {
+        // no sample of the wave needs the boundary rule
+        const T *col = fin + (size_t)q0 * ld + i;
+        gs_cells<GS_RK>([&](int s) { return col[(size_t)s * ld]; }, [&](int s) { return col[(size_t)s * ld + o]; }, r, cD,
+                        a, b, g, d, y);
+    } else {
+        const T *col = fin + i;
+        auto at = [&](int s) {
+            int q = q0 + s;
+            if (BC == BC_PERIODIC) return col[(size_t)wrap_near(q, np) * ld];
+            const T v = col[(size_t)min(max(q, 0), np - 1) * ld];
+            return q >= 0 && q < np ? v : T(0);
+        };
+        gs_cells<GS_RK>(at, [&](int s) { return at(s + o); }, r, cD, a, b, g, d, y);
+    }
+#pragma unroll
+    for (int u = 0; u < GS_RK; ++u)
+        if (j0 + u < np) fout[(size_t)(j0 + u) * ld + i] = y[u];
 }
 
 // Density partial sums of f (serial over the rows of each 16-row block, in
