@@ -178,8 +178,8 @@ int density_force(vlasov_ctx *c)
     const double *cs = c->at<double>(c->L.cs), *sn = c->at<double>(c->L.sn);
     switch (P.model) {
     case VLASOV_MODEL_HMF:
-        launch(c, VLASOV_K_FORCE, vk::k_force_hmf, dim3(1), dim3(1024), rho, cs, sn, F, nx, c->dx, mxmy, hist, hcount,
-               P.hist_cap);
+        launch(c, VLASOV_K_FORCE, nx > 1024 ? vk::k_force_hmf<true> : vk::k_force_hmf<false>, dim3(1),
+               dim3(1024), rho, cs, sn, F, nx, c->dx, mxmy, hist, hcount, P.hist_cap);
         break;
     case VLASOV_MODEL_RING: {
         const int per = vk::ring_outputs_per_wg(nx);

@@ -1400,13 +1400,25 @@ __device__ __forceinline__ void force_hmf_block(const double *__restrict__ rho, 
 
 // The single-grid form: wavefront 0 forms (M_x, M_y) from the arrays in
 // memory (the same chains as magnetization()), then every thread writes its
-// forces; no staging of the three arrays.
+// forces; no staging of the three arrays.  One wavefront's chain bounds it.
+// AHEAD (more columns than threads): the factors of a thread's first forces
+// are requested before that chain, not after it (4096 columns 5.4 -> 4.4 us;
+// with fewer columns the requests delay the chain: 128, a step 11.5 -> 11.6).
+template <bool AHEAD>
 static __global__ __launch_bounds__(1024) void k_force_hmf(const double *__restrict__ rho, const double *__restrict__ cs,
                                                     const double *__restrict__ sn, double *__restrict__ F, int n,
                                                     double dx, double *mxmy, double *hist, int64_t *hcount,
                                                     int64_t hcap)
 {
     __shared__ double M[2];
+    constexpr int U = AHEAD ? 4 : 0;
+    double cv[U + 1], sv[U + 1];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = min((int)(threadIdx.x + u * blockDim.x), n - 1);
+        cv[u] = cs[i];
+        sv[u] = sn[i];
+    }
     if (threadIdx.x < 64) {
         double mx, my;
         magnetization(rho, cs, sn, n, dx, mx, my);
@@ -1418,7 +1430,11 @@ static __global__ __launch_bounds__(1024) void k_force_hmf(const double *__restr
     }
     __syncthreads();
     const double mx = M[0], my = M[1];
-    for (int i = threadIdx.x; i < n; i += blockDim.x) F[i] = fma(my, cs[i], -(mx * sn[i]));
+    int i = threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < U; ++u, i += blockDim.x)
+        if (i < n) F[i] = fma(my, cv[u], -(mx * sv[u]));
+    for (; i < n; i += blockDim.x) F[i] = fma(my, cs[i], -(mx * sn[i]));
 }
 
 // Magnetization only (ring model, batched force phase).  One workgroup,
@@ -1562,30 +1578,43 @@ static __global__ __launch_bounds__(256) void k_force_ring(const double *__restr
 // Sheet force, eq. (sheetpot) with V = 2 pi G |x|: F_i = K (S - 2 P_i - rho_i),
 // K = 2 pi G dx, P_i the exclusive prefix sum of rho and S its total.
 // Wavefront 0 scans: lane l owns the contiguous chunk [l c, (l+1) c),
-// c = ceil(n/64); chunk totals by an inclusive Hillis-Steele scan
-// d = 1, 2, ..., 32.  When staged, rho is held in LDS chunk-transposed
-// (element l c + k at k 65 + l) so that the 64 lanes walking their chunks read
-// adjacent words; F is written back in place and stored coalesced.
+// c = ceil(n/64), and replaces each sample by the sum of those before it in
+// the chunk; chunk totals by an inclusive Hillis-Steele scan d = 1, 2, ..., 32.
+// P_i is the sum before the chunk (X[l], of X[65]; X[64] is S) plus that
+// before i in it, and all threads form the forces.  When staged, the samples
+// are held in LDS chunk-transposed (element l c + k at k 65 + l) so that the
+// 64 lanes walking their chunks use adjacent words; else in F.  Bound by the
+// one wavefront's chain of additions: with the forces in a second walk of that
+// wavefront 4096 columns took 4.9 us, 4.2 now.
 constexpr int SHEET_LDS_MAX = 16384;
 constexpr int SHEET_LDS_WORDS = (SHEET_LDS_MAX / 64) * 65;
 
 template <bool STAGED>
 __device__ __forceinline__ void force_sheet_block(const double *__restrict__ rho, double *__restrict__ F, int n,
-                                                  double K, double *L)
+                                                  double K, double *L, double *X)
 {
     const int c = (n + 63) / 64;
+    const int bd = blockDim.x;
+    // i / c: for n <= SHEET_LDS_MAX (c <= 256) the float product is off by less
+    // than 1e-4 where its distance from a whole number is at least 1 / (2 c)
+    const float rc = 1.0f / (float)c;
+    auto chunk = [&](int i) { return STAGED ? (int)(((float)i + 0.5f) * rc) : i / c; };
+    constexpr int U = 4;  // samples of a thread requested together
+    double own[U];        // the first ones stay in registers for the result
     if (STAGED) {
-        const int bd = blockDim.x;
-        for (int i0 = threadIdx.x; i0 < n; i0 += 4 * bd) {
-            double v[4];
+        for (int i0 = threadIdx.x; i0 < n; i0 += U * bd) {
+            double v[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = rho[min(i0 + u * bd, n - 1)];
+            for (int u = 0; u < U; ++u) v[u] = rho[min(i0 + u * bd, n - 1)];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) keep_issued(v[u]);
+            for (int u = 0; u < U; ++u) keep_issued(v[u]);
+            if (i0 == (int)threadIdx.x)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = i0 + u * bd;
-                if (i < n) L[(i % c) * 65 + i / c] = v[u];
+                for (int u = 0; u < U; ++u) own[u] = v[u];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * bd, l = chunk(i);
+                if (i < n) L[(i - l * c) * 65 + l] = v[u];
             }
         }
         __syncthreads();
@@ -1594,48 +1623,54 @@ __device__ __forceinline__ void force_sheet_block(const double *__restrict__ rho
         const int l = threadIdx.x;
         const int len = min(c, n - l * c);  // <= 0 past the end
         double tot = 0.0;
+        // (past the chunk: any value in bounds, not used)
+        auto at = [&](int k) { return STAGED ? L[min(k, c - 1) * 65 + l] : rho[min(l * c + k, n - 1)]; };
+        auto one = [&](int k, double r) {
+            if (STAGED)
+                L[k * 65 + l] = tot;
+            else
+                F[l * c + k] = tot;
+            tot = tot + r;
+        };
+        // eight samples ahead, summed in order
+        constexpr int B = 8;
+        double v[B], w[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) v[u] = at(u);
         int k = 0;
-        // sixteen samples requested at once, summed in order
-        for (; k + 16 <= len; k += 16) {
-            double v[16];
+        for (; k + B <= len; k += B) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = STAGED ? L[(k + u) * 65 + l] : rho[l * c + k + u];
+            for (int u = 0; u < B; ++u) w[u] = at(k + B + u);
 #pragma unroll
-            for (int u = 0; u < 16; ++u) tot = tot + v[u];
+            for (int u = 0; u < B; ++u) one(k + u, v[u]);
+#pragma unroll
+            for (int u = 0; u < B; ++u) v[u] = w[u];
         }
-        for (; k < len; ++k) tot = tot + (STAGED ? L[k * 65 + l] : rho[l * c + k]);
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k + u < len) one(k + u, v[u]);
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
-            const double v = __shfl_up(tot, d, 64);
-            if (l >= d) tot = v + tot;
+            const double up = __shfl_up(tot, d, 64);
+            if (l >= d) tot = up + tot;
         }
-        double excl = __shfl_up(tot, 1, 64);
-        if (l == 0) excl = 0.0;
-        const double S = __shfl(tot, 63, 64);
-        double acc = 0.0;
-        auto one = [&](int kk, double r) {
-            const double Pi = excl + acc;
-            const double f = K * (fma(-2.0, Pi, S) - r);
-            if (STAGED)
-                L[kk * 65 + l] = f;
-            else
-                F[l * c + kk] = f;
-            acc = acc + r;
-        };
-        k = 0;
-        for (; k + 16 <= len; k += 16) {
-            double v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = STAGED ? L[(k + u) * 65 + l] : rho[l * c + k + u];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) one(k + u, v[u]);
-        }
-        for (; k < len; ++k) one(k, STAGED ? L[k * 65 + l] : rho[l * c + k]);
+        X[l + 1] = tot;
+        if (l == 0) X[0] = 0.0;
     }
+    __syncthreads();
+    const double S = X[64];
+    auto force = [&](int i, double r) {
+        const int l = chunk(i);
+        const double Pi = X[l] + (STAGED ? L[(i - l * c) * 65 + l] : F[i]);
+        F[i] = K * (fma(-2.0, Pi, S) - r);
+    };
+    int i = threadIdx.x;
     if (STAGED) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < n; i += blockDim.x) F[i] = L[(i % c) * 65 + i / c];
+#pragma unroll
+        for (int u = 0; u < U; ++u, i += bd)
+            if (i < n) force(i, own[u]);
     }
+    for (; i < n; i += bd) force(i, rho[i]);
 }
 
 template <bool STAGED>
@@ -1643,7 +1678,8 @@ static __global__ __launch_bounds__(1024) void k_force_sheet(const double *__res
                                                       double K)
 {
     __shared__ double L[STAGED ? SHEET_LDS_WORDS : 1];
-    force_sheet_block<STAGED>(rho, F, n, K, L);
+    __shared__ double X[65];
+    force_sheet_block<STAGED>(rho, F, n, K, L, X);
 }
 
 // ---------------------------------------------------------------------------
@@ -1958,7 +1994,7 @@ constexpr int BATCH_FORCE_LDS = BATCH_SHEET_WORDS > 3 * BATCH_FORCE_STAGE ? BATC
 static __global__ __launch_bounds__(256) void kb_force(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int members, int items)
 {
     __shared__ double L[BATCH_FORCE_LDS];
-    __shared__ double M[2];
+    __shared__ double M[65];
     const int n = items >= 0 ? members : cy->n;
     const int total = items >= 0 ? items : cy->off_force[n];
     for (int e = blockIdx.x; e < total; e += gridDim.x) {
@@ -1974,9 +2010,9 @@ static __global__ __launch_bounds__(256) void kb_force(const GridDesc *__restric
                 force_hmf_block<false>(g.rho, g.cs, g.sn, g.F, g.nx, g.dx, g.mxmy, g.hist, g.hcount, g.hcap, L, M);
         } else if (g.model == 2) {
             if (g.nx <= BATCH_FORCE_STAGE)
-                force_sheet_block<true>(g.rho, g.F, g.nx, g.sheetK, L);
+                force_sheet_block<true>(g.rho, g.F, g.nx, g.sheetK, L, M);
             else
-                force_sheet_block<false>(g.rho, g.F, g.nx, g.sheetK, L);
+                force_sheet_block<false>(g.rho, g.F, g.nx, g.sheetK, L, M);
         } else if (g.model == 1) {
             const int nb = (g.nx + 15) / 16;
             if (li < nb) {
