@@ -415,7 +415,7 @@ enum {
     VLASOV_K_DRIFT = 0,    /* one half drift + density partial sums */
     VLASOV_K_DRIFT2 = 1,   /* two fused half drifts + density partial sums */
     VLASOV_K_DENSITY = 2,  /* density from the partial sums */
-    VLASOV_K_FORCE = 3,    /* model force (and magnetization) */
+    VLASOV_K_FORCE = 3,    /* model force (and magnetization); with the density on small grids */
     VLASOV_K_KICK = 4,     /* momentum advection, alone, or fused with the half drift after
                               the last kick of a call, or with two on 182-column tiles */
     VLASOV_K_MOMENTS = 5,  /* diagnostics */

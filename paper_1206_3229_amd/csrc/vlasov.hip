@@ -168,14 +168,25 @@ int density_force(vlasov_ctx *c)
     const int nx = (int)P.nx;
     double *rho = c->at<double>(c->L.rho);
     double *F = c->at<double>(c->L.F);
-    launch(c, VLASOV_K_DENSITY, vk::k_density, dim3((unsigned)((nx + 15) / 16)), dim3(1024),
-           c->at<double>(c->L.part), rho, nx, (int)c->nblk, c->dp);
-    int rc = check_launch("density");
-    if (rc) return rc;
+    const double *part = c->at<double>(c->L.part);
     double *hist = c->at<double>(c->L.hist);
     int64_t *hcount = c->at<int64_t>(c->L.hcount);
     double *mxmy = c->at<double>(c->L.mxmy);
     const double *cs = c->at<double>(c->L.cs), *sn = c->at<double>(c->L.sn);
+    const double sheetK = ((2.0 * M_PI) * P.sheet_G) * c->dx;
+    const bool hmf = P.model == VLASOV_MODEL_HMF;
+    if ((hmf || P.model == VLASOV_MODEL_SHEET) && vk::small_grid(nx, c->nblk)) {
+        launch(c, VLASOV_K_FORCE, hmf ? vk::k_density_force<0> : vk::k_density_force<2>, dim3(1),
+               dim3((unsigned)((nx + 63) / 64 * 64)), part, rho, F, nx, (int)c->nblk, c->dp, cs, sn, c->dx, mxmy, hist,
+               hcount, P.hist_cap, sheetK);
+        const int rc = check_launch("density+force");
+        if (rc == VLASOV_OK) c->have_force = true;
+        return rc;
+    }
+    launch(c, VLASOV_K_DENSITY, vk::k_density, dim3((unsigned)((nx + 15) / 16)), dim3(1024), part, rho, nx,
+           (int)c->nblk, c->dp);
+    int rc = check_launch("density");
+    if (rc) return rc;
     switch (P.model) {
     case VLASOV_MODEL_HMF:
         launch(c, VLASOV_K_FORCE, nx > 1024 ? vk::k_force_hmf<true> : vk::k_force_hmf<false>, dim3(1),
@@ -188,12 +199,10 @@ int density_force(vlasov_ctx *c)
                cs, sn, mxmy, hist, hcount, P.hist_cap);
         break;
     }
-    case VLASOV_MODEL_SHEET: {
-        const double K = ((2.0 * M_PI) * P.sheet_G) * c->dx;
+    case VLASOV_MODEL_SHEET:
         launch(c, VLASOV_K_FORCE, nx <= vk::SHEET_LDS_MAX ? vk::k_force_sheet<true> : vk::k_force_sheet<false>,
-               dim3(1), dim3(1024), rho, F, nx, K);
+               dim3(1), dim3(1024), rho, F, nx, sheetK);
         break;
-    }
     default:
         break;  // EXTERNAL: the kick reads the caller's force table
     }

@@ -1589,36 +1589,11 @@ static __global__ __launch_bounds__(256) void k_force_ring(const double *__restr
 constexpr int SHEET_LDS_MAX = 16384;
 constexpr int SHEET_LDS_WORDS = (SHEET_LDS_MAX / 64) * 65;
 
+// The scan: samples replaced by the sums before them in their chunks, X as above.
 template <bool STAGED>
-__device__ __forceinline__ void force_sheet_block(const double *__restrict__ rho, double *__restrict__ F, int n,
-                                                  double K, double *L, double *X)
+__device__ __forceinline__ void sheet_scan(const double *__restrict__ rho, double *__restrict__ F, int n, int c,
+                                           double *L, double *X)
 {
-    const int c = (n + 63) / 64;
-    const int bd = blockDim.x;
-    // i / c: for n <= SHEET_LDS_MAX (c <= 256) the float product is off by less
-    // than 1e-4 where its distance from a whole number is at least 1 / (2 c)
-    const float rc = 1.0f / (float)c;
-    auto chunk = [&](int i) { return STAGED ? (int)(((float)i + 0.5f) * rc) : i / c; };
-    constexpr int U = 4;  // samples of a thread requested together
-    double own[U];        // the first ones stay in registers for the result
-    if (STAGED) {
-        for (int i0 = threadIdx.x; i0 < n; i0 += U * bd) {
-            double v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = rho[min(i0 + u * bd, n - 1)];
-#pragma unroll
-            for (int u = 0; u < U; ++u) keep_issued(v[u]);
-            if (i0 == (int)threadIdx.x)
-#pragma unroll
-                for (int u = 0; u < U; ++u) own[u] = v[u];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = i0 + u * bd, l = chunk(i);
-                if (i < n) L[(i - l * c) * 65 + l] = v[u];
-            }
-        }
-        __syncthreads();
-    }
     if (threadIdx.x < 64) {
         const int l = threadIdx.x;
         const int len = min(c, n - l * c);  // <= 0 past the end
@@ -1658,6 +1633,39 @@ __device__ __forceinline__ void force_sheet_block(const double *__restrict__ rho
         if (l == 0) X[0] = 0.0;
     }
     __syncthreads();
+}
+
+template <bool STAGED>
+__device__ __forceinline__ void force_sheet_block(const double *__restrict__ rho, double *__restrict__ F, int n,
+                                                  double K, double *L, double *X)
+{
+    const int c = (n + 63) / 64;
+    const int bd = blockDim.x;
+    // i / c: for n <= SHEET_LDS_MAX (c <= 256) the float product is off by less
+    // than 1e-4 where its distance from a whole number is at least 1 / (2 c)
+    const float rc = 1.0f / (float)c;
+    auto chunk = [&](int i) { return STAGED ? (int)(((float)i + 0.5f) * rc) : i / c; };
+    constexpr int U = 4;  // samples of a thread requested together
+    double own[U];        // the first ones stay in registers for the result
+    if (STAGED) {
+        for (int i0 = threadIdx.x; i0 < n; i0 += U * bd) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = rho[min(i0 + u * bd, n - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) keep_issued(v[u]);
+            if (i0 == (int)threadIdx.x)
+#pragma unroll
+                for (int u = 0; u < U; ++u) own[u] = v[u];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * bd, l = chunk(i);
+                if (i < n) L[(i - l * c) * 65 + l] = v[u];
+            }
+        }
+        __syncthreads();
+    }
+    sheet_scan<STAGED>(rho, F, n, c, L, X);
     const double S = X[64];
     auto force = [&](int i, double r) {
         const int l = chunk(i);
@@ -1680,6 +1688,82 @@ static __global__ __launch_bounds__(1024) void k_force_sheet(const double *__res
     __shared__ double L[STAGED ? SHEET_LDS_WORDS : 1];
     __shared__ double X[65];
     force_sheet_block<STAGED>(rho, F, n, K, L, X);
+}
+
+// Density and force of a small grid by one workgroup in one launch, a thread
+// per column: HMF (model 0) or sheet (model 2).  The two kernels take a launch
+// and a few dependent memory latencies each, whatever the size: apart 3.9 us at
+// 64^2, 4.4 at 128^2, 4.7 at 256^2 and 512^2 (HMF), together 2.0, 2.1, 2.5 and
+// 4.1.  At 512^2 reading the partial sums through one CU (64 KB in 1 us) takes
+// up most of what the launch saves; hence SMALL_PART.  A column's classes are
+// of one block each (at most 32), summed by the butterfly's tree in the
+// thread's registers; classes past the last block are 0.
+constexpr int SMALL_NX = 1024, SMALL_BLK = 32, SMALL_PART = 16384;
+__host__ __device__ constexpr bool small_grid(int64_t nx, int64_t nblk)
+{
+    return nx <= SMALL_NX && nblk <= SMALL_BLK && nx * nblk <= SMALL_PART;
+}
+
+template <int NB>
+__device__ __forceinline__ double column_sum(const double *__restrict__ part, int i, int nx, int nblk)
+{
+    double v[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) v[b] = part[(size_t)min(b, nblk - 1) * nx + i];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) keep_issued(v[b]);
+    // 0 + x: the classes' sums start from 0
+#pragma unroll
+    for (int b = 0; b < NB; ++b) v[b] = b < nblk ? 0.0 + v[b] : 0.0;
+#pragma unroll
+    for (int d = NB / 2; d >= 1; d >>= 1)
+#pragma unroll
+        for (int b = 0; b < d; ++b) v[b] = v[b] + v[b + d];
+    return v[0];
+}
+
+template <int MODEL>
+static __global__ __launch_bounds__(SMALL_NX) void k_density_force(
+    const double *__restrict__ part, double *__restrict__ rho, double *__restrict__ F, int n, int nblk, double dp,
+    const double *__restrict__ cs, const double *__restrict__ sn, double dx, double *mxmy, double *hist,
+    int64_t *hcount, int64_t hcap, double K)
+{
+    __shared__ double L[3 * SMALL_NX];
+    __shared__ double X[65];
+    const int i = threadIdx.x, ic = min(i, n - 1);
+    double cv = 0.0, sv = 0.0;
+    if (MODEL == 0) {
+        cv = cs[ic];
+        sv = sn[ic];
+    }
+    const double r = dp * (nblk <= 8    ? column_sum<8>(part, ic, n, nblk)
+                           : nblk <= 16 ? column_sum<16>(part, ic, n, nblk)
+                                        : column_sum<SMALL_BLK>(part, ic, n, nblk));
+    if (i < n) rho[i] = r;
+    if (MODEL == 0) {
+        L[i] = r;
+        L[SMALL_NX + i] = cv;
+        L[2 * SMALL_NX + i] = sv;
+        __syncthreads();
+        if (i < 64) {
+            double mx, my;
+            magnetization(L, L + SMALL_NX, L + 2 * SMALL_NX, n, dx, mx, my);
+            if (i == 0) {
+                X[0] = mx;
+                X[1] = my;
+                record_history(mxmy, hist, hcount, hcap, mx, my);
+            }
+        }
+        __syncthreads();
+        if (i < n) F[i] = fma(X[1], cv, -(X[0] * sv));
+    } else {
+        const int c = (n + 63) / 64;
+        const int l = ic / c, slot = (ic - l * c) * 65 + l;
+        if (i < n) L[slot] = r;
+        __syncthreads();
+        sheet_scan<true>(rho, F, n, c, L, X);
+        if (i < n) F[i] = K * (fma(-2.0, X[l] + L[slot], X[64]) - r);
+    }
 }
 
 // ---------------------------------------------------------------------------
