@@ -4,8 +4,8 @@
 
 namespace vlasov_detail {
 
-template <typename T>
-int launch_drift(vlasov_ctx *c, int ta, int tb, bool partials)
+template <typename T, bool THROUGH>
+int launch_drift_by(vlasov_ctx *c, int ta, int tb, bool partials)
 {
     using G = vk::KDGeom<vk::DR_TW>;
     const vlasov_params &P = c->P;
@@ -19,7 +19,7 @@ int launch_drift(vlasov_ctx *c, int ta, int tb, bool partials)
     double *part = partials ? c->at<double>(c->L.part) : nullptr;
     const int nx = (int)P.nx, np = (int)P.np;
 #define DRIFT_LAUNCH(KID, BX, NPASS, NT)                                                                                \
-    launch(c, KID, vk::k_drift<T, BX, NPASS>, grid, dim3(NT), fin, fout, dm1, dm2, dw1, dw2, part, nx, np, nb, ntx, nty)
+    launch(c, KID, vk::k_drift<T, BX, NPASS, THROUGH>, grid, dim3(NT), fin, fout, dm1, dm2, dw1, dw2, part, nx, np, nb, ntx, nty)
     if (P.bc_x == VLASOV_BC_PERIODIC) {
         if (tb >= 0) DRIFT_LAUNCH(VLASOV_K_DRIFT2, vk::BC_PERIODIC, 2, G::NT); else DRIFT_LAUNCH(VLASOV_K_DRIFT, vk::BC_PERIODIC, 1, G::NT1);
     } else {
@@ -29,6 +29,13 @@ int launch_drift(vlasov_ctx *c, int ta, int tb, bool partials)
     int rc = check_launch("drift");
     if (rc == VLASOV_OK) c->cur ^= 1;
     return rc;
+}
+
+template <typename T>
+int launch_drift(vlasov_ctx *c, int ta, int tb, bool partials)
+{
+    return write_through<T>(c->P) ? launch_drift_by<T, true>(c, ta, tb, partials)
+                            : launch_drift_by<T, false>(c, ta, tb, partials);
 }
 
 template int launch_drift<float>(vlasov_ctx *, int, int, bool);

@@ -45,6 +45,19 @@ inline int default_kd_blocks(int64_t nx, int64_t nblk)
 {
     return ((nx + KD_TW - 1) / KD_TW) * ((nblk + KD_RB - 1) / KD_RB) >= KD_RB_MIN_TILES ? KD_RB : 1;
 }
+// Size of f from which the drifts write their results through the L2s: a
+// kernel ends, and the next one starts, only once the lines its XCDs hold
+// dirty are written back.  The fused kernel alone, written back -> through:
+// FP64 128^2 6.5 -> 6.4 us, 256^2 6.6 -> 6.4, 512^2 6.7 -> 6.5, 1024^2 9.5 ->
+// 8.9, 2048^2 22.5 -> 21, 4096^2 64.7 -> 64.2; FP32 (8 bytes a store) 256^2 6.0
+// -> 6.1, 724^2 6.28 -> 6.26, 1024^2 7.3 -> 7.15, 2048^2 14.7 -> 13.7, 4096^2
+// 40.7 -> 40.5.  The density after it starts sooner as well (2048^2 ring 277 ->
+// 264 us for 10 steps).
+template <typename T> constexpr int64_t through_bytes() { return sizeof(T) == 8 ? int64_t(512) << 10 : int64_t(2) << 20; }
+template <typename T> bool write_through(const vlasov_params &P)
+{
+    return P.nx * P.np * (int64_t)sizeof(T) >= through_bytes<T>();
+}
 template <typename T> constexpr int kd_pf() { return sizeof(T) == 8 ? 4 : 2; }
 // rows per thread of the filter along p
 constexpr int FILTER_R = 16;

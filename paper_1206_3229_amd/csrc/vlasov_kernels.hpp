@@ -529,6 +529,24 @@ __device__ __forceinline__ void store2(T *p, T v0, T v1)
     *reinterpret_cast<pair_t *>(p) = v;
 }
 
+// store2() at `off` bytes into a row, written through the L2 of the XCD (no
+// dirty lines for the end of the kernel to write back).
+template <typename T>
+__device__ __forceinline__ void store2_through(char *row, uint32_t off, T v0, T v1)
+{
+    constexpr int SC1 = 16;  // cache policy: device scope
+    typedef T pair_t __attribute__((ext_vector_type(2)));
+    typedef uint32_t words_t __attribute__((ext_vector_type(sizeof(T) / 2)));
+    pair_t v;
+    v.x = v0;
+    v.y = v1;
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(row, 0, 0xffffffffu, 0x00027000);
+    if constexpr (sizeof(T) == 8)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(words_t, v), r, off, 0, SC1);
+    else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(words_t, v), r, off, 0, SC1);
+}
+
 template <typename T>
 struct KDTile {
     const T *fin;
@@ -805,8 +823,9 @@ __device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
     __syncthreads();
 }
 
-// The waves of the half drift whose result is stored: wave w2 of W2.
-template <typename T, int BCX, int TW, int SPR, int SRC, int NPASS>
+// The waves of the half drift whose result is stored: wave w2 of W2.  THROUGH:
+// pairs are written through the L2 (single values and odd last rows are not).
+template <typename T, int BCX, int TW, int SPR, int SRC, int NPASS, bool THROUGH>
 __device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
 {
     using G = KDGeom<TW, SPR>;
@@ -856,11 +875,17 @@ __device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
             swap_halves(o[0], o[2]);
             swap_halves(o[1], o[3]);
             T *outa = reinterpret_cast<T *>(out + io), *outb = reinterpret_cast<T *>(out + ldb + io);
+            char *const row0 = out;
             out += 2 * ldb;
             if (row + 1 < nr) {
                 if (two) {
-                    store2(outa, o[0], o[1]);
-                    store2(outb, o[2], o[3]);
+                    if constexpr (THROUGH) {
+                        store2_through<T>(row0, io, o[0], o[1]);
+                        store2_through<T>(row0 + ldb, io, o[2], o[3]);
+                    } else {
+                        store2(outa, o[0], o[1]);
+                        store2(outb, o[2], o[3]);
+                    }
                 }
                 if (anyone)
                     if (one) {
@@ -882,8 +907,14 @@ __device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
             __syncthreads();
         }
         if (sums) {
-            double *srow = reinterpret_cast<double *>(reinterpret_cast<char *>(a.part + (size_t)(a.ty * a.nb + blk) * ld) + ios);
-            if (two) store2(srow, acc0, acc1);
+            char *const sums0 = reinterpret_cast<char *>(a.part + (size_t)(a.ty * a.nb + blk) * ld);
+            double *srow = reinterpret_cast<double *>(sums0 + ios);
+            if (two) {
+                if constexpr (THROUGH)
+                    store2_through<double>(sums0, ios, acc0, acc1);
+                else
+                    store2(srow, acc0, acc1);
+            }
             if (one) srow[0] = acc0;
         }
     }
@@ -901,7 +932,7 @@ __device__ __forceinline__ void kd_no_part(const KDTile<T> &a)
 // One tile, by a workgroup of KDGeom::NT threads (or NT1 with one half drift).
 // SRC KD_KICK: the rows kicked, KD_LOAD: the rows of f (BCP, PF unused); then
 // NPASS half drifts.  rot: number of the workgroup.
-template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int SRC, int NPASS>
+template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int SRC, int NPASS, bool THROUGH = false>
 __device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot)
 {
     using G = KDGeom<TW, SPR>;
@@ -924,7 +955,7 @@ __device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot)
             a.wtab[4 * k + 3] = (T)w.w;
         }
         if (p >= G::WK + G::W1)
-            kd_second_part<T, BCX, TW, SPR, SRC, NPASS>(a, p - G::WK - G::W1);
+            kd_second_part<T, BCX, TW, SPR, SRC, NPASS, THROUGH>(a, p - G::WK - G::W1);
         else if (NPASS == 2)
             kd_first_part<T, BCX, TW, SPR, SRC>(a, p - G::WK);
         else
@@ -932,7 +963,7 @@ __device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot)
     }
 }
 
-template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int NPASS>
+template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int NPASS, bool THROUGH>
 static __global__ __launch_bounds__((NPASS == 2 ? KDGeom<TW, SPR>::NT : KDGeom<TW, SPR>::NT1))
 __attribute__((amdgpu_waves_per_eu(8)))
 void k_kick_drift(
@@ -948,7 +979,7 @@ void k_kick_drift(
     int tx, ty;
     if (!xcd_tile(ntx, nty, tx, ty)) return;
     const KDTile<T> a{fin, fout, F, dt, dp, dm1, dm2, dw1, dw2, kbase, krel, part, nx, np, nb, tx, ty, kbuf, mbuf, wtab};
-    kick_drift_tile<T, BCX, BCP, TW, SPR, PF, KD_KICK, NPASS>(a, (int)blockIdx.x);
+    kick_drift_tile<T, BCX, BCP, TW, SPR, PF, KD_KICK, NPASS, THROUGH>(a, (int)blockIdx.x);
 }
 
 // Steps 1 and 4 (eqs. step1, step4) without a kick before them: drift along x,
@@ -959,7 +990,7 @@ void k_kick_drift(
 // near the copy rate on large ones (4096^2 FP64 48.4 us, 50.6 before; FP32
 // 27.6, 25.7 before).
 constexpr int DR_TW = 230;
-template <typename T, int BCX, int NPASS>
+template <typename T, int BCX, int NPASS, bool THROUGH>
 static __global__ __launch_bounds__((NPASS == 2 ? KDGeom<DR_TW>::NT : KDGeom<DR_TW>::NT1))
 __attribute__((amdgpu_waves_per_eu(8)))
 void k_drift(
@@ -975,7 +1006,7 @@ void k_drift(
     if (!xcd_tile(ntx, nty, tx, ty)) return;
     const KDTile<T> a{fin, fout, nullptr, 0.0, 0.0, dm1, dm2, dw1, dw2, nullptr, nullptr, part, nx, np, nb, tx, ty, kbuf,
                       mbuf, wtab};
-    kick_drift_tile<T, BCX, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, NPASS>(a, (int)blockIdx.x);
+    kick_drift_tile<T, BCX, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, NPASS, THROUGH>(a, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
