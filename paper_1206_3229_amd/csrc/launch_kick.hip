@@ -86,8 +86,8 @@ int launch_kick_filter(vlasov_ctx *c, double h)
 // Global spline (eq. tridiagsys): half drifts of the rows in LDS, the kick down
 // the columns.
 // ---------------------------------------------------------------------------
-template <typename T>
-int gs_drift_t(vlasov_ctx *c, int ta, int tb, bool partials)
+template <typename T, bool THROUGH>
+int gs_drift_by(vlasov_ctx *c, int ta, int tb, bool partials)
 {
     const vlasov_params &P = c->P;
     const T *fin = (const T *)c->fcur();
@@ -104,7 +104,7 @@ int gs_drift_t(vlasov_ctx *c, int ta, int tb, bool partials)
     const dim3 grid((unsigned)((np + lpw - 1) / lpw)), block((unsigned)((tpl * lpw + 63) / 64 * 64));
     const int kid = tb >= 0 ? VLASOV_K_DRIFT2 : VLASOV_K_DRIFT;
 #define GS_ROWS(BC, NPASS)                                                                                          \
-    launch_lds(c, kid, vk::k_gs_rows<T, BC, NPASS>, grid, block, row * (size_t)lpw, fin, fout, n, np, tpl, lpw, dm1, \
+    launch_lds(c, kid, vk::k_gs_rows<T, BC, NPASS, THROUGH>, grid, block, row * (size_t)lpw, fin, fout, n, np, tpl, lpw, dm1, \
                dw1, dm2, dw2, g)
     if (P.bc_x == VLASOV_BC_PERIODIC) {
         if (tb >= 0) GS_ROWS(vk::BC_PERIODIC, 2); else GS_ROWS(vk::BC_PERIODIC, 1);
@@ -123,8 +123,8 @@ int gs_drift_t(vlasov_ctx *c, int ta, int tb, bool partials)
     return rc;
 }
 
-template <typename T>
-int gs_kick_t(vlasov_ctx *c, double h)
+template <typename T, bool THROUGH>
+int gs_kick_by(vlasov_ctx *c, double h)
 {
     const vlasov_params &P = c->P;
     const int nx = (int)P.nx, np = (int)P.np;
@@ -134,14 +134,26 @@ int gs_kick_t(vlasov_ctx *c, double h)
     T *fout = (T *)c->fnext();
     const double *g = c->at<double>(c->L.gs_g);
     if (P.bc_p == VLASOV_BC_PERIODIC)
-        launch(c, VLASOV_K_KICK, vk::k_gs_cols<T, vk::BC_PERIODIC>, grid, dim3(256), fin, fout, nx, np, force_ptr(c), h,
+        launch(c, VLASOV_K_KICK, vk::k_gs_cols<T, vk::BC_PERIODIC, THROUGH>, grid, dim3(256), fin, fout, nx, np, force_ptr(c), h,
                c->dp, g, ntx, nty);
     else
-        launch(c, VLASOV_K_KICK, vk::k_gs_cols<T, vk::BC_ZERO>, grid, dim3(256), fin, fout, nx, np, force_ptr(c), h, c->dp,
+        launch(c, VLASOV_K_KICK, vk::k_gs_cols<T, vk::BC_ZERO, THROUGH>, grid, dim3(256), fin, fout, nx, np, force_ptr(c), h, c->dp,
                g, ntx, nty);
     int rc = check_launch("global-spline kick");
     if (rc == VLASOV_OK) c->cur ^= 1;
     return rc;
+}
+
+template <typename T>
+int gs_drift_t(vlasov_ctx *c, int ta, int tb, bool partials)
+{
+    return write_through<T>(c->P) ? gs_drift_by<T, true>(c, ta, tb, partials) : gs_drift_by<T, false>(c, ta, tb, partials);
+}
+
+template <typename T>
+int gs_kick_t(vlasov_ctx *c, double h)
+{
+    return write_through<T>(c->P) ? gs_kick_by<T, true>(c, h) : gs_kick_by<T, false>(c, h);
 }
 
 template int launch_kick<float>(vlasov_ctx *, double);

@@ -547,6 +547,16 @@ __device__ __forceinline__ void store2_through(char *row, uint32_t off, T v0, T 
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(words_t, v), r, off, 0, SC1);
 }
 
+// One value, through the L2 or not.
+template <bool THROUGH, typename T>
+__device__ __forceinline__ void store1(T *p, T v)
+{
+    if constexpr (THROUGH)
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        *p = v;
+}
+
 template <typename T>
 struct KDTile {
     const T *fin;
@@ -1069,7 +1079,7 @@ __host__ __device__ inline int gs_row(int n, int bc) { return GS_R * (gs_threads
 // second pass is column c - m1).  2048^2 FP64: 16 us, 21 for two half drifts
 // (34 and 68 with both recursions through LDS, six barriers, and two workgroups
 // per compute unit); the rows' traffic alone takes 11.
-template <typename T, int BC, int NPASS>
+template <typename T, int BC, int NPASS, bool THROUGH>
 static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fin, T *__restrict__ fout, int n, int lines,
                                                  int tpl, int lpw, const int32_t *__restrict__ dm1,
                                                  const double4 *__restrict__ dw1, const int32_t *__restrict__ dm2,
@@ -1147,9 +1157,9 @@ static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fi
             int c = i + shift;
             if (BC == BC_PERIODIC) {
                 c = c >= n ? c - n : c;
-                dst[i] = row[c + H];
+                store1<THROUGH>(dst + i, row[c + H]);
             } else {
-                dst[i] = c >= -Z && c < GS_R * tpl - Z ? row[c + Z + H] : T(0);
+                store1<THROUGH>(dst + i, c >= -Z && c < GS_R * tpl - Z ? row[c + Z + H] : T(0));
             }
         }
     }
@@ -1161,7 +1171,7 @@ static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fi
 // with two transposes around a sweep of rows); 16 rows a thread 29, and three
 // waves per SIMD, which spill, 40.
 constexpr int GS_RK = 32;
-template <typename T, int BC>
+template <typename T, int BC, bool THROUGH>
 static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void k_gs_cols(const T *__restrict__ fin, T *__restrict__ fout, int nx, int np, const double *__restrict__ F, double dt,
                double dp, const double *__restrict__ gcoef, int ntx, int nty)
@@ -1197,7 +1207,7 @@ void k_gs_cols(const T *__restrict__ fin, T *__restrict__ fout, int nx, int np, 
     }
 #pragma unroll
     for (int u = 0; u < GS_RK; ++u)
-        if (j0 + u < np) fout[(size_t)(j0 + u) * ld + i] = y[u];
+        if (j0 + u < np) store1<THROUGH>(fout + (size_t)(j0 + u) * ld + i, y[u]);
 }
 
 // Density partial sums of f (serial over the rows of each 16-row block, in

@@ -57,3 +57,16 @@ def test_large_results_match_the_oracle(oracle, name):
     want = oracle.sweep_x(p, oracle.sweep_x(p, want, 0.5 * p.dt), 0.5 * p.dt)
     assert np.array_equal(s.read_f(), want), (name, "two half drifts")
     s.close()
+
+
+@pytest.mark.parametrize("storage", [D, S])
+@pytest.mark.parametrize("zero", [False, True])
+def test_large_global_spline(oracle, storage, zero):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import test_gpu_global_spline_edges as E
+    from paper_1206_3229_amd import vlasov as V
+    V.load()
+    nx, np_ = (515, 131) if storage == D else (1027, 517)
+    E.test_sweeps(V, oracle, nx, np_, 0.05, zero, storage)
