@@ -299,7 +299,7 @@ int vlasov_set_tuning(vlasov_ctx *c, const vlasov_tuning *t);
 int vlasov_get_tuning(vlasov_ctx *c, vlasov_tuning *t);
 
 /* ---------------------------------------------------------------------------
- * Batches: many contexts stepped together (one persistent launch per phase).
+ * Batches: many contexts stepped together (one launch per phase).
  * ------------------------------------------------------------------------- */
 
 #define VLASOV_BATCH_MAX 256

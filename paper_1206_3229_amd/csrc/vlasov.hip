@@ -247,7 +247,7 @@ int gs_kick(vlasov_ctx *c, double h)
 // of table k and, tb >= 0, that of table tb: in one kernel where the offsets of
 // the rows of every tile lie close enough together, else in separate ones.
 // Measured, a call's last kick and half drift apart -> in one kernel: 4096^2
-// sheet 106 -> 57.6 us (FP32 46 -> 30), 2048^2 27 -> 18, 64^2 17 -> 6.7.
+// sheet 106 -> 56.5 us (FP32 46 -> 29), 2048^2 27 -> 18, 64^2 17 -> 6.7.
 int kick_then_drift(vlasov_ctx *c, int k, int tb, double h, bool filt)
 {
     if (!filt && c->tune.kick_drift_width != 0 && c->P.spline == VLASOV_SPLINE_FD) {

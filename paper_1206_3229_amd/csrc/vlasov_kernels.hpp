@@ -365,15 +365,18 @@ static __global__ __launch_bounds__(256) void k_kick_filter(const T *__restrict_
 // outputs), lanes 0..31 of a wave in the first row of the pair and lanes
 // 32..63 in the second; the waves of a part share the runs of a row.
 //
-// What bounds it: small grids by the time of an interval in one wave (0.35 us
+// What bounds it: small grids by the time of an interval in one wave (0.36 us;
 // with every wave kicking and drifting in turn 0.5 us, hence waves of their
-// own for each part); FP64 at 4096^2 by the traffic (318 MB, 51 us of data
-// movement alone) and VALU issue together, FP32 by VALU issue.  Runs of four
+// own for each part); FP64 at 4096^2 by the traffic (without the drifts'
+// arithmetic 58 of 65 us, without the kick's 60), FP32 by traffic and VALU
+// issue together (30 to 36 of 40).  Four rows an interval, loads 6 to 14 rows
+// ahead, LDS reads an interval ahead and runs of two by twice the drifting
+// waves were no faster.  Runs of four
 // cost 15.25 operations an output and 7 LDS reads of 16 bytes for four
 // (runs of two: 17.5, and 12); row weights stand in LDS and row offsets one per
 // lane (v_readlane), where scalar loads between the barriers cost a wait each.
-// Measured alone, before -> now: 230 x 16 6.9 -> 5.9 us, 1024^2 10.1 -> 9.5,
-// 2048^2 22.2 -> 20.9, 4096^2 65.9 -> 64.2 (FP32 42.1 -> 38.4).
+// Measured alone, before -> now: 230 x 16 6.9 -> 6.05 us, 1024^2 10.1 -> 8.9,
+// 2048^2 22.2 -> 21.0, 4096^2 65.9 -> 64.2 (FP32 42.1 -> 40.5).
 // ---------------------------------------------------------------------------
 constexpr int KD_SPR = 8;
 // tiles for offsets that spread more (coarse p, fine x, long steps): the same
@@ -995,10 +998,10 @@ void k_kick_drift(
 // Steps 1 and 4 (eqs. step1, step4) without a kick before them: drift along x,
 // row j shifted by the constant p_j tau/dx cells, once or (NPASS = 2, tables 1
 // and 2) twice in turn; the tiles of the fused kernel with the rows' windows
-// loaded instead of kicked.  Latency-bound on small grids (64^2: 5.3 us; 12.7
+// loaded instead of kicked.  Latency-bound on small grids (64^2: 5.2 us; 12.7
 // with a workgroup of two waves that waited for each row of an edge tile),
-// near the copy rate on large ones (4096^2 FP64 48.4 us, 50.6 before; FP32
-// 27.6, 25.7 before).
+// near the copy rate on large ones (4096^2 FP64 48.6 us, 50.6 before; FP32
+// 29.7, 25.7 before: once in a call).
 constexpr int DR_TW = 230;
 template <typename T, int BCX, int NPASS, bool THROUGH>
 static __global__ __launch_bounds__((NPASS == 2 ? KDGeom<DR_TW>::NT : KDGeom<DR_TW>::NT1))
@@ -1167,7 +1170,7 @@ static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fi
 
 // The kick: one thread per column and GS_RK rows, the samples read down the
 // column (the lanes of a wavefront read adjacent columns of the same rows, and
-// the rows that two chunks share come from the caches).  2048^2 FP64: 24 us (70
+// the rows that two chunks share come from the caches).  2048^2 FP64: 23 us (70
 // with two transposes around a sweep of rows); 16 rows a thread 29, and three
 // waves per SIMD, which spill, 40.
 constexpr int GS_RK = 32;
