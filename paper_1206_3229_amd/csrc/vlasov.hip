@@ -175,10 +175,16 @@ int density_force(vlasov_ctx *c)
     const double *cs = c->at<double>(c->L.cs), *sn = c->at<double>(c->L.sn);
     const double sheetK = ((2.0 * M_PI) * P.sheet_G) * c->dx;
     const bool hmf = P.model == VLASOV_MODEL_HMF;
-    if ((hmf || P.model == VLASOV_MODEL_SHEET) && vk::small_grid(nx, c->nblk)) {
-        launch(c, VLASOV_K_FORCE, hmf ? vk::k_density_force<0> : vk::k_density_force<2>, dim3(1),
-               dim3((unsigned)((nx + 63) / 64 * 64)), part, rho, F, nx, (int)c->nblk, c->dp, cs, sn, c->dx, mxmy, hist,
-               hcount, P.hist_cap, sheetK);
+    const bool ring = P.model == VLASOV_MODEL_RING;
+    if ((hmf || ring || P.model == VLASOV_MODEL_SHEET) && vk::small_grid(nx, c->nblk)) {
+        if (ring)
+            launch(c, VLASOV_K_FORCE, vk::k_density_force_ring, dim3((unsigned)(1 + (nx + vk::RING_OUT_WG - 1) / vk::RING_OUT_WG)),
+                   dim3(256), part, rho, c->at<double>(c->L.ringK), F, nx, (int)c->nblk, c->dp, c->dx, cs, sn, mxmy, hist,
+                   hcount, P.hist_cap);
+        else
+            launch(c, VLASOV_K_FORCE, hmf ? vk::k_density_force<0> : vk::k_density_force<2>, dim3(1),
+                   dim3((unsigned)((nx + 63) / 64 * 64)), part, rho, F, nx, (int)c->nblk, c->dp, cs, sn, c->dx, mxmy,
+                   hist, hcount, P.hist_cap, sheetK);
         const int rc = check_launch("density+force");
         if (rc == VLASOV_OK) c->have_force = true;
         return rc;

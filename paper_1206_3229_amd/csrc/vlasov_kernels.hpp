@@ -1734,8 +1734,8 @@ static __global__ __launch_bounds__(1024) void k_force_sheet(const double *__res
     force_sheet_block<STAGED>(rho, F, n, K, L, X);
 }
 
-// Density and force of a small grid by one workgroup in one launch, a thread
-// per column: HMF (model 0) or sheet (model 2).  The two kernels take a launch
+// Density and force of a small grid in one launch, for HMF (model 0) and sheet
+// (model 2) by one workgroup, a thread per column.  The two kernels take a launch
 // and a few dependent memory latencies each, whatever the size: apart 3.9 us at
 // 64^2, 4.4 at 128^2, 4.7 at 256^2 and 512^2 (HMF), together 2.0, 2.1, 2.5 and
 // 4.1.  At 512^2 reading the partial sums through one CU (64 KB in 1 us) takes
@@ -1766,6 +1766,60 @@ __device__ __forceinline__ double column_sum(const double *__restrict__ part, in
     return v[0];
 }
 
+__device__ __forceinline__ double column_density(const double *__restrict__ part, int i, int nx, int nblk, double dp)
+{
+    return dp * (nblk <= 8    ? column_sum<8>(part, i, nx, nblk)
+                 : nblk <= 16 ? column_sum<16>(part, i, nx, nblk)
+                              : column_sum<SMALL_BLK>(part, i, nx, nblk));
+}
+
+// The ring's form: the workgroups of k_force_ring<true>, each of which sums all
+// columns for itself (they are few, and come from the caches); workgroup 0
+// keeps the densities.  A step, in two launches -> one: 64^2 13.6 -> 9.7 us,
+// 256^2 14.6 -> 10.8, 512^2 14.3 -> 12.8, 1024 x 256 14.9 -> 13.4.
+static __global__ __launch_bounds__(256) void k_density_force_ring(
+    const double *__restrict__ part, double *__restrict__ rho, const double *__restrict__ K, double *__restrict__ F,
+    int n, int nblk, double dp, double dx, const double *__restrict__ cs, const double *__restrict__ sn, double *mxmy,
+    double *hist, int64_t *hcount, int64_t hcap)
+{
+    constexpr int U = SMALL_NX / 256;
+    __shared__ double L[3 * SMALL_NX];
+    const bool mag = blockIdx.x == 0;
+    const int t = threadIdx.x;
+    const double *a0 = mag ? cs : K;  // staged beside the densities
+    double v0[U], v1[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = min(t + 256 * u, n - 1);
+        v0[u] = a0[i];
+        v1[u] = sn[i];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = t + 256 * u;
+        if (256 * u >= n) break;  // uniform
+        const double r = column_density(part, min(i, n - 1), n, nblk, dp);
+        L[i] = r;
+        L[SMALL_NX + i] = v0[u];
+        L[2 * SMALL_NX + i] = v1[u];
+        if (mag && i < n) rho[i] = r;
+    }
+    __syncthreads();
+    if (mag) {
+        if (t < 64) {
+            double mx, my;
+            magnetization(L, L + SMALL_NX, L + 2 * SMALL_NX, n, dx, mx, my);
+            if (t == 0) record_history(mxmy, hist, hcount, hcap, mx, my);
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < RING_OUT_WG / 4; ++q) {
+        const int i = (blockIdx.x - 1) * RING_OUT_WG + (t >> 6) * (RING_OUT_WG / 4) + q;
+        if (i < n) force_ring_output(L, L + SMALL_NX, F, n, dx, i);
+    }
+}
+
 template <int MODEL>
 static __global__ __launch_bounds__(SMALL_NX) void k_density_force(
     const double *__restrict__ part, double *__restrict__ rho, double *__restrict__ F, int n, int nblk, double dp,
@@ -1780,9 +1834,7 @@ static __global__ __launch_bounds__(SMALL_NX) void k_density_force(
         cv = cs[ic];
         sv = sn[ic];
     }
-    const double r = dp * (nblk <= 8    ? column_sum<8>(part, ic, n, nblk)
-                           : nblk <= 16 ? column_sum<16>(part, ic, n, nblk)
-                                        : column_sum<SMALL_BLK>(part, ic, n, nblk));
+    const double r = column_density(part, ic, n, nblk, dp);
     if (i < n) rho[i] = r;
     if (MODEL == 0) {
         L[i] = r;

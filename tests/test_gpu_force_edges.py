@@ -21,7 +21,7 @@ SMALL = [(16, 16), (63, 17), (64, 128), (65, 129), (127, 256), (256, 257), (512,
 
 
 @pytest.mark.parametrize("model,nx,np_", [(I.MODEL_SHEET, n, 16) for n in SHEET] + [(I.MODEL_HMF, n, 16) for n in HMF] +
-                         [(m, *s) for m in (I.MODEL_SHEET, I.MODEL_HMF) for s in SMALL])
+                         [(m, *s) for m in (I.MODEL_SHEET, I.MODEL_HMF, I.MODEL_RING) for s in SMALL])
 def test_force(oracle, model, nx, np_):
     import torch
     if not torch.cuda.is_available():
