@@ -1040,18 +1040,27 @@ constexpr int GS_K = 30, GS_R = 33, GS_MAX_N = 4096;
 // Values of RC cells from the samples at(0 .. RC + 2 GS_K + 1), 31 before the
 // first cell on (cell u lies between samples u + 31 and u + 32), left in y[0 ..
 // RC).  `again` reads the samples of the cells a second time, so that they are
-// not held in registers meanwhile.
+// not held in registers meanwhile.  fetch(s) comes before the samples s, s + 1,
+// ..., s + RC, which are then asked for by their number and place in this group.
 template <int RC, typename T, typename At, typename Again>
 __device__ __forceinline__ void gs_cells(At at, Again again, T r, T cD, T a, T b, T g, T d, T (&y)[RC + GS_K])
 {
-    T f0 = at(0), f1 = at(1), acc = T(0);
+    constexpr int S = RC + 2 * GS_K + 2, NB = RC + 1;
+    T f0 = T(0), f1 = T(0), acc = T(0);
 #pragma unroll
-    for (int e = 0; e < RC + 2 * GS_K; ++e) {  // node of sample e + 1
-        const T f2 = at(e + 2);
-        acc = vfma(r, acc, (f0 + f2) - T(2) * f1);
-        if (e >= GS_K) y[e - GS_K] = acc;
-        f0 = f1;
-        f1 = f2;
+    for (int s0 = 0; s0 < S; s0 += NB) {
+        at.fetch(s0);
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int s = s0 + u, e = s - 2;  // node of sample e + 1
+            if (s < S) {
+                const T f2 = at(s, u);
+                if (e >= 0) acc = vfma(r, acc, (f0 + f2) - T(2) * f1);
+                if (e >= GS_K) y[e - GS_K] = acc;
+                f0 = f1;
+                f1 = f2;
+            }
+        }
     }
     acc = T(0);
 #pragma unroll
@@ -1059,14 +1068,51 @@ __device__ __forceinline__ void gs_cells(At at, Again again, T r, T cD, T a, T b
         acc = vfma(r, acc, y[e]);
         if (e <= RC) y[e] = cD * acc;
     }
-    f0 = again(GS_K + 1);
+    again.fetch(GS_K + 1);
+    f0 = again(GS_K + 1, 0);
 #pragma unroll
     for (int u = 0; u < RC; ++u) {
-        f1 = again(GS_K + 2 + u);
+        f1 = again(GS_K + 2 + u, u + 1);
         y[u] = spline(a, b, g, d, f0, f1, y[u], y[u + 1]);
         f0 = f1;
     }
 }
+
+// Samples where they are needed, from p on, `ld` apart.
+template <typename T>
+struct GsDirect {
+    const T *p;
+    size_t ld;
+    __device__ __forceinline__ void fetch(int) {}
+    __device__ __forceinline__ T operator()(int s, int) const { return p[(size_t)s * ld]; }
+};
+
+// Samples of a column near the ends of the grid, from row q0 (in [0, np) on a
+// periodic axis) on, NB at a time: with the boundary rule between two loads (a
+// division, or a branch for the zero) each load waited for the one before it.
+template <typename T, int BC, int NB>
+struct GsEdge {
+    const T *col;
+    size_t ld;
+    int q0, np;
+    T buf[NB];
+    __device__ __forceinline__ void fetch(int s)
+    {
+        int row = BC == BC_PERIODIC ? wrap_near(q0 + s, np) : 0;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            if (BC != BC_PERIODIC) row = min(max(q0 + s + u, 0), np - 1);
+            buf[u] = col[(size_t)(unsigned)row * ld];
+            if (BC == BC_PERIODIC) row = row + 1 < np ? row + 1 : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) keep_issued(buf[u]);
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+            if (BC != BC_PERIODIC) buf[u] = (unsigned)(q0 + s + u) < (unsigned)np ? buf[u] : T(0);
+    }
+    __device__ __forceinline__ T operator()(int, int u) const { return buf[u]; }
+};
 
 // Threads per row of the drift (with zero extension 32 more cells on each
 // side, where D decays to nothing) and samples of a row in LDS (GS_R of halo
@@ -1127,8 +1173,8 @@ static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fi
             const double4 w = (pass == 0 ? dw1 : dw2)[line];
             int o = 0;
             __asm__ __volatile__("" : "+v"(o));  // the second reads are reads
-            gs_cells<GS_R>([&](int s) { return mid[s - GS_K - 1]; }, [&](int s) { return mid[o + s - GS_K - 1]; }, r, cD,
-                           (T)w.x, (T)w.y, (T)w.z, (T)w.w, y);
+            const T *x = mid - GS_K - 1;
+            gs_cells<GS_R>(GsDirect<T>{x, 1}, GsDirect<T>{x + o, 1}, r, cD, (T)w.x, (T)w.y, (T)w.z, (T)w.w, y);
         }
         shift += m;
         __syncthreads();
@@ -1170,9 +1216,13 @@ static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fi
 
 // The kick: one thread per column and GS_RK rows, the samples read down the
 // column (the lanes of a wavefront read adjacent columns of the same rows, and
-// the rows that two chunks share come from the caches).  2048^2 FP64: 23 us (70
-// with two transposes around a sweep of rows); 16 rows a thread 29, and three
-// waves per SIMD, which spill, 40.
+// the rows that two chunks share come from the caches).  Small grids take the
+// time of one wave, near the ends of the grid three groups of loads and their
+// arithmetic; large ones the reads of 94 and 33 rows for 32.  FP64, periodic /
+// zero p, with the boundary rule between the loads of an edge -> with them in
+// groups: 64^2 13 / 20 -> 7 / 7 us, 256^2 15 / 28 -> 8 / 8, 2048^2 21 / 44 -> 15
+// / 14, 4096^2 59 / 79 -> 51 / 49.  No register spilled (206 to 242 in FP64, two
+// waves per SIMD).  2048^2 with two transposes around a sweep of rows: 70 us.
 constexpr int GS_RK = 32;
 template <typename T, int BC, bool THROUGH>
 static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
@@ -1196,17 +1246,10 @@ void k_gs_cols(const T *__restrict__ fin, T *__restrict__ fout, int nx, int np, 
     if (__builtin_amdgcn_readfirstlane((int)__all(q0 >= 0 && q0 + GS_RK + 2 * GS_K + 2 <= np))) {
         // no sample of the wave needs the boundary rule
         const T *col = fin + (size_t)q0 * ld + i;
-        gs_cells<GS_RK>([&](int s) { return col[(size_t)s * ld]; }, [&](int s) { return col[(size_t)s * ld + o]; }, r, cD,
-                        a, b, g, d, y);
+        gs_cells<GS_RK>(GsDirect<T>{col, ld}, GsDirect<T>{col + o, ld}, r, cD, a, b, g, d, y);
     } else {
-        const T *col = fin + i;
-        auto at = [&](int s) {
-            int q = q0 + s;
-            if (BC == BC_PERIODIC) return col[(size_t)wrap_near(q, np) * ld];
-            const T v = col[(size_t)min(max(q, 0), np - 1) * ld];
-            return q >= 0 && q < np ? v : T(0);
-        };
-        gs_cells<GS_RK>(at, [&](int s) { return at(s + o); }, r, cD, a, b, g, d, y);
+        using Edge = GsEdge<T, BC, GS_RK + 1>;
+        gs_cells<GS_RK>(Edge{fin + i, ld, q0, np}, Edge{fin + i, ld, q0 + o, np}, r, cD, a, b, g, d, y);
     }
 #pragma unroll
     for (int u = 0; u < GS_RK; ++u)

@@ -1,0 +1,54 @@
+"""Kernel times of one form of a call beside another form's, measured in the same
+process: a form that falls behind does so by a cause of its own (loads that wait
+for each other, too few workgroups), not by the chip's."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_1206_3229_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def V():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1206_3229_amd import vlasov
+    vlasov.load()
+    return vlasov
+
+
+def _time(s, kernels, call):
+    """Least mean time (us) of a launch of `kernels` over 20 windows of ten calls."""
+    call()
+    best = math.inf
+    for _ in range(20):
+        s.profile(True)
+        for _ in range(10):
+            call()
+        t = s.profile_read()
+        s.profile(False)
+        best = min(best, sum(t[k][0] for k in kernels) * 1e3 / sum(t[k][1] for k in kernels))
+    return best
+
+
+@pytest.mark.parametrize("storage", [I.STORAGE_F64, I.STORAGE_F32])
+@pytest.mark.parametrize("n", [256, 1024])
+def test_global_spline_kick_with_zero_p(V, n, storage):
+    """The same kick on a zero-extended p axis as on a periodic one: the same samples and sums but for the
+    boundary rule.  1.8 to 2.3 times as long where each load near the ends waits for the one before it; the limit
+    is the geometric mean of that and 1."""
+    times = []
+    for bc in (I.BC_PERIODIC, I.BC_ZERO):
+        p = I.Params(I.MODEL_EXTERNAL, n, n, -10.0, 10.0, -4.0, 4.0, 0.02, bc_p=bc, storage=storage,
+                     spline=I.SPLINE_GS)
+        s = V.Solver(p, V.ic_waterbag(1.2, 0.9))
+        s.set_external_force(np.sin(2.0 * math.pi * np.arange(n) / n) * 5.0 * p.dp / p.dt)
+        s.force()
+        times.append(_time(s, ["kick"], s.kick))
+        s.close()
+    print(f"global spline kick {n}^2 storage {storage}: periodic {times[0]:.2f} us, zero {times[1]:.2f} us", flush=True)
+    assert times[1] <= 1.35 * times[0]
