@@ -86,6 +86,8 @@ int launch_kick_filter(vlasov_ctx *c, double h)
 // Global spline (eq. tridiagsys): half drifts of the rows in LDS, the kick down
 // the columns.
 // ---------------------------------------------------------------------------
+// workgroups of the half drift that few rows are spread over: the CUs
+constexpr int GS_MIN_WG = 256;
 template <typename T, bool THROUGH>
 int gs_drift_by(vlasov_ctx *c, int ta, int tb, bool partials)
 {
@@ -97,14 +99,16 @@ int gs_drift_by(vlasov_ctx *c, int ta, int tb, bool partials)
     const double *g = c->at<double>(c->L.gs_g);
     const int n = (int)P.nx, np = (int)P.np;
     // whole rows per workgroup: 128 threads of short rows (as far as 40 KB of
-    // LDS hold them), one long row
+    // LDS hold them, and as the rows give every CU a workgroup), one long row.
+    // Where rows are few, the threads without cells load and store (half drift
+    // and partial sums, FP64, packed -> spread: 64^2 18 -> 10 us, 512^2 16 -> 13)
     const int tpl = vk::gs_threads(n, P.bc_x);
     const size_t row = (size_t)vk::gs_row(n, P.bc_x) * sizeof(T);
-    const int lpw = std::max(1, std::min(128 / tpl, (int)(40960 / row)));
-    const dim3 grid((unsigned)((np + lpw - 1) / lpw)), block((unsigned)((tpl * lpw + 63) / 64 * 64));
+    const int lpw = std::max(1, std::min({128 / tpl, (int)(40960 / row), np / GS_MIN_WG})), grp = std::max(tpl, 128 / lpw);
+    const dim3 grid((unsigned)((np + lpw - 1) / lpw)), block((unsigned)((grp * lpw + 63) / 64 * 64));
     const int kid = tb >= 0 ? VLASOV_K_DRIFT2 : VLASOV_K_DRIFT;
 #define GS_ROWS(BC, NPASS)                                                                                          \
-    launch_lds(c, kid, vk::k_gs_rows<T, BC, NPASS, THROUGH>, grid, block, row * (size_t)lpw, fin, fout, n, np, tpl, lpw, dm1, \
+    launch_lds(c, kid, vk::k_gs_rows<T, BC, NPASS, THROUGH>, grid, block, row * (size_t)lpw, fin, fout, n, np, tpl, grp, lpw, dm1, \
                dw1, dm2, dw2, g)
     if (P.bc_x == VLASOV_BC_PERIODIC) {
         if (tb >= 0) GS_ROWS(vk::BC_PERIODIC, 2); else GS_ROWS(vk::BC_PERIODIC, 1);

@@ -14,6 +14,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace vk {
 
 enum { BC_PERIODIC = 0, BC_ZERO = 1 };
@@ -1127,49 +1129,57 @@ __host__ __device__ inline int gs_row(int n, int bc) { return GS_R * (gs_threads
 // only when it is stored; in between, cells keep their place (place c of the
 // second pass is column c - m1).  2048^2 FP64: 16 us, 21 for two half drifts
 // (34 and 68 with both recursions through LDS, six barriers, and two workgroups
-// per compute unit); the rows' traffic alone takes 11.
+// per compute unit); the rows' traffic alone takes 11.  A row's `grp` threads
+// load and store it, the first `tpl` of them have its cells: a short row has
+// only two to four, which took up to 66 samples each from memory and back.
 template <typename T, int BC, int NPASS, bool THROUGH>
 static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fin, T *__restrict__ fout, int n, int lines,
-                                                 int tpl, int lpw, const int32_t *__restrict__ dm1,
+                                                 int tpl, int grp, int lpw, const int32_t *__restrict__ dm1,
                                                  const double4 *__restrict__ dw1, const int32_t *__restrict__ dm2,
                                                  const double4 *__restrict__ dw2, const double *__restrict__ gcoef)
 {
     extern __shared__ __attribute__((aligned(16))) char gs_lds[];
     constexpr int Z = BC == BC_PERIODIC ? 0 : 32;  // cells before column 0
     constexpr int H = GS_R;                        // sample e of the row is column e - H - Z
-    const int l = threadIdx.x / tpl, tt = threadIdx.x - l * tpl;
+    const int l = threadIdx.x / grp, tt = threadIdx.x - l * grp;
     const int line = blockIdx.x * lpw + l;
-    const bool mine = l < lpw && line < lines;
+    const bool mine = l < lpw && line < lines, cells = mine && tt < tpl;
     T *row = reinterpret_cast<T *>(gs_lds) + (size_t)min(l, lpw - 1) * gs_row(n, BC);
     const int NL = GS_R * (tpl + 2);
     if (mine) {
         const T *src = fin + (size_t)line * n;
-        constexpr int NB = 18;
-        for (int e0 = tt; e0 < NL; e0 += NB * tpl) {
-            T v[NB];
+        auto load = [&](auto batch) {  // samples of the row, `batch` a thread in flight
+            constexpr int NB = decltype(batch)::value;
+            for (int e0 = tt; e0 < NL; e0 += NB * grp) {
+                T v[NB];
 #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int c = e0 + u * tpl - H - Z;
-                v[u] = BC == BC_PERIODIC ? src[wrap_near(c, n)] : src[min(max(c, 0), n - 1)];
+                for (int u = 0; u < NB; ++u) {
+                    const int c = min(e0 + u * grp, NL - 1) - H - Z;
+                    v[u] = BC == BC_PERIODIC ? src[wrap_near(c, n)] : src[min(max(c, 0), n - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < NB; ++u) keep_issued(v[u]);
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const int e = e0 + u * grp, c = e - H - Z;
+                    if (e < NL) row[e] = BC == BC_PERIODIC || (c >= 0 && c < n) ? v[u] : T(0);
+                }
             }
-#pragma unroll
-            for (int u = 0; u < NB; ++u) keep_issued(v[u]);
-#pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int e = e0 + u * tpl, c = e - H - Z;
-                if (e < NL) row[e] = BC == BC_PERIODIC || (c >= 0 && c < n) ? v[u] : T(0);
-            }
-        }
+        };
+        if (NL <= 4 * grp)
+            load(std::integral_constant<int, 4>{});
+        else
+            load(std::integral_constant<int, 18>{});
     }
     __syncthreads();
     const T r = (T)gcoef[0], cD = (T)gcoef[1];
-    T *mid = row + GS_R * tt + H;  // first cell of this thread
+    T *mid = row + GS_R * min(tt, tpl - 1) + H;  // first cell of this thread
     int shift = 0;
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
         T y[GS_R + GS_K];
         const int m = mine ? (pass == 0 ? dm1 : dm2)[line] : 0;
-        if (mine) {
+        if (cells) {
             const double4 w = (pass == 0 ? dw1 : dw2)[line];
             int o = 0;
             __asm__ __volatile__("" : "+v"(o));  // the second reads are reads
@@ -1178,7 +1188,7 @@ static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fi
         }
         shift += m;
         __syncthreads();
-        if (mine) {
+        if (cells) {
 #pragma unroll
             for (int u = 0; u < GS_R; ++u) {
                 T v = y[u];
@@ -1192,7 +1202,7 @@ static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fi
         __syncthreads();
         if (BC == BC_PERIODIC && pass + 1 < NPASS) {  // the halos again
             if (mine)
-                for (int e = tt; e < NL - n; e += tpl) {
+                for (int e = tt; e < NL - n; e += grp) {
                     const int h = e < H ? e : e + n;
                     row[h] = row[wrap(h - H, n) + H];
                 }
@@ -1202,7 +1212,7 @@ static __global__ __launch_bounds__(256) void k_gs_rows(const T *__restrict__ fi
     if (mine) {
         T *dst = fout + (size_t)line * n;
         if (BC == BC_PERIODIC) shift = wrap(shift, n);
-        for (int i = tt; i < n; i += tpl) {
+        for (int i = tt; i < n; i += grp) {
             int c = i + shift;
             if (BC == BC_PERIODIC) {
                 c = c >= n ? c - n : c;

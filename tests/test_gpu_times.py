@@ -52,3 +52,18 @@ def test_global_spline_kick_with_zero_p(V, n, storage):
         s.close()
     print(f"global spline kick {n}^2 storage {storage}: periodic {times[0]:.2f} us, zero {times[1]:.2f} us", flush=True)
     assert times[1] <= 1.35 * times[0]
+
+
+@pytest.mark.parametrize("storage", [I.STORAGE_F64, I.STORAGE_F32])
+def test_global_spline_drift_of_a_small_grid(V, storage):
+    """A half drift (with its density partial sums) of 64 rows of 64 takes no longer than one of 512 rows of 512,
+    which has 64 times the values: 1.15 to 1.2 times as long where two threads move a row of 64 and one workgroup
+    has all rows."""
+    times = []
+    for n in (64, 512):
+        p = I.Params(I.MODEL_HMF, n, n, -math.pi, math.pi, -2.5, 2.5, 0.02, storage=storage, spline=I.SPLINE_GS)
+        s = V.Solver(p, V.ic_waterbag(1.2, 0.9))
+        times.append(_time(s, ["drift"], lambda: s.drift(1)))
+        s.close()
+    print(f"global spline half drift storage {storage}: 64^2 {times[0]:.2f} us, 512^2 {times[1]:.2f} us", flush=True)
+    assert times[0] <= times[1]
