@@ -6,7 +6,7 @@
 
 namespace vlasov_detail {
 
-template <typename T, int TW, int SPR, int NPASS, bool THROUGH>
+template <typename T, int TW, int SPR, int NPASS, bool THROUGH, int PF>
 int launch_kick_drift_w(vlasov_ctx *c, int kid, int ta, double h)
 {
     using G = vk::KDGeom<TW, SPR>;
@@ -26,7 +26,7 @@ int launch_kick_drift_w(vlasov_ctx *c, int kid, int ta, double h)
     double *part = NPASS == 2 ? c->at<double>(c->L.part) : nullptr;
     const int nx = (int)P.nx, np = (int)P.np;
 #define KD_LAUNCH(BX, BP)                                                                                      \
-    launch(c, kid, vk::k_kick_drift<T, BX, BP, TW, SPR, kd_pf<T>(), NPASS, THROUGH>, grid, dim3(NT), fin, fout, F, h, c->dp, \
+    launch(c, kid, vk::k_kick_drift<T, BX, BP, TW, SPR, PF, NPASS, THROUGH>, grid, dim3(NT), fin, fout, F, h, c->dp, \
            dm1, dm2, dw1, dw2, kbase, krel, part, nx, np, nb, ntx, nty)
     if (P.bc_x == VLASOV_BC_PERIODIC) {
         if (P.bc_p == VLASOV_BC_PERIODIC) KD_LAUNCH(vk::BC_PERIODIC, vk::BC_PERIODIC); else KD_LAUNCH(vk::BC_PERIODIC, vk::BC_ZERO);
@@ -39,26 +39,27 @@ int launch_kick_drift_w(vlasov_ctx *c, int kid, int ta, double h)
     return rc;
 }
 
-template <typename T, bool THROUGH>
+template <typename T, bool THROUGH, int PF>
 int launch_kick_drift_by(vlasov_ctx *c, int ta, bool pair, int64_t spread, double h)
 {
     if (pair) {
         if (spread > vk::KD_SPR)
-            return launch_kick_drift_w<T, vk::KD_TW_WIDE, vk::KD_SPR_WIDE, 2, THROUGH>(c, VLASOV_K_KICK, ta, h);
+            return launch_kick_drift_w<T, vk::KD_TW_WIDE, vk::KD_SPR_WIDE, 2, THROUGH, PF>(c, VLASOV_K_KICK, ta, h);
         if (c->tune.kick_drift_width == 486)
-            return launch_kick_drift_w<T, 486, vk::KD_SPR, 2, THROUGH>(c, VLASOV_K_KICK_DRIFT2, ta, h);
-        return launch_kick_drift_w<T, KD_TW, vk::KD_SPR, 2, THROUGH>(c, VLASOV_K_KICK_DRIFT2, ta, h);
+            return launch_kick_drift_w<T, 486, vk::KD_SPR, 2, THROUGH, PF>(c, VLASOV_K_KICK_DRIFT2, ta, h);
+        return launch_kick_drift_w<T, KD_TW, vk::KD_SPR, 2, THROUGH, PF>(c, VLASOV_K_KICK_DRIFT2, ta, h);
     }
     if (spread > vk::KD_SPR)
-        return launch_kick_drift_w<T, vk::KD_TW_WIDE, vk::KD_SPR_WIDE, 1, THROUGH>(c, VLASOV_K_KICK, ta, h);
-    return launch_kick_drift_w<T, KD_TW, vk::KD_SPR, 1, THROUGH>(c, VLASOV_K_KICK, ta, h);
+        return launch_kick_drift_w<T, vk::KD_TW_WIDE, vk::KD_SPR_WIDE, 1, THROUGH, PF>(c, VLASOV_K_KICK, ta, h);
+    return launch_kick_drift_w<T, KD_TW, vk::KD_SPR, 1, THROUGH, PF>(c, VLASOV_K_KICK, ta, h);
 }
 
 template <typename T>
 int launch_kick_drift(vlasov_ctx *c, int ta, bool pair, int64_t spread, double h)
 {
-    return write_through<T>(c->P) ? launch_kick_drift_by<T, true>(c, ta, pair, spread, h)
-                            : launch_kick_drift_by<T, false>(c, ta, pair, spread, h);
+    if (far_grid<T>(c->P)) return launch_kick_drift_by<T, false, kd_pf<T>(true)>(c, ta, pair, spread, h);
+    return write_through<T>(c->P) ? launch_kick_drift_by<T, true, kd_pf<T>()>(c, ta, pair, spread, h)
+                                  : launch_kick_drift_by<T, false, kd_pf<T>()>(c, ta, pair, spread, h);
 }
 
 }  // namespace vlasov_detail

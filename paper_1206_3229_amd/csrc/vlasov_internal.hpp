@@ -34,9 +34,7 @@ inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 constexpr int DRIFT_NT = 128;
 // kick rows per thread (measured best on 4096^2: 16 for FP64, 32 for FP32)
 template <typename T> constexpr int kick_rows() { return sizeof(T) == 8 ? 16 : 32; }
-// fused kick and drift: default tile width and blocks; rows requested ahead by
-// the kick (4096^2: 64.2 us with four, 65.3 with two in FP64; no difference in
-// FP32)
+// fused kick and drift: default tile width and blocks
 constexpr int KD_TW = 230, KD_RB = 2;
 // 32-row tiles where the grid still gives at least this many of them, else
 // 16-row tiles (twice the workgroups, to fill the chip)
@@ -45,20 +43,33 @@ inline int default_kd_blocks(int64_t nx, int64_t nblk)
 {
     return ((nx + KD_TW - 1) / KD_TW) * ((nblk + KD_RB - 1) / KD_RB) >= KD_RB_MIN_TILES ? KD_RB : 1;
 }
-// Size of f from which the drifts write their results through the L2s: a
-// kernel ends, and the next one starts, only once the lines its XCDs hold
+// Sizes of f at which the drifts write their results through the L2s.
+// From through_bytes() on: a kernel ends, and the next one starts, only once the lines its XCDs hold
 // dirty are written back.  The fused kernel alone, written back -> through:
 // FP64 128^2 6.5 -> 6.4 us, 256^2 6.6 -> 6.4, 512^2 6.7 -> 6.5, 1024^2 9.5 ->
 // 8.9, 2048^2 22.5 -> 21, 4096^2 64.7 -> 64.2; FP32 (8 bytes a store) 256^2 6.0
 // -> 6.1, 724^2 6.28 -> 6.26, 1024^2 7.3 -> 7.15, 2048^2 14.7 -> 13.7, 4096^2
 // 40.7 -> 40.5.  The density after it starts sooner as well (2048^2 ring 277 ->
 // 264 us for 10 steps).
+// Up to far_bytes(): the pair of buffers of larger grids does not fit in the 256
+// MiB of the last-level cache, and the lines that two tiles share go to memory
+// in two parts, one from each, unless the L2s put them together first.  Eight
+// steps, written back / through, us: FP64 sheet 128 MiB of f 586 / 565, 136 MiB
+// 625 / 632, 192 MiB 905 / 946; FP32 HMF 112 MiB 507 / 508, 128 MiB 708 / 726,
+// 192 MiB 986 / 1071, 16384^2 4795 / 5516.
 template <typename T> constexpr int64_t through_bytes() { return sizeof(T) == 8 ? int64_t(512) << 10 : int64_t(2) << 20; }
+template <typename T> constexpr int64_t far_bytes() { return (sizeof(T) == 8 ? int64_t(132) : int64_t(120)) << 20; }
+template <typename T> int64_t bytes_of_f(const vlasov_params &P) { return P.nx * P.np * (int64_t)sizeof(T); }
+template <typename T> bool far_grid(const vlasov_params &P) { return bytes_of_f<T>(P) >= far_bytes<T>(); }
 template <typename T> bool write_through(const vlasov_params &P)
 {
-    return P.nx * P.np * (int64_t)sizeof(T) >= through_bytes<T>();
+    return bytes_of_f<T>(P) >= through_bytes<T>() && !far_grid<T>(P);
 }
-template <typename T> constexpr int kd_pf() { return sizeof(T) == 8 ? 4 : 2; }
+// Rows that the fused kernel's kick requests ahead.  FP64 four (4096^2 64.2 us,
+// 65.3 with two).  FP32 two, which is the faster by up to 5 % where f comes from
+// the last-level cache (1024^2 sheet, eight steps 124 us, 130 with four), and
+// four on far grids (16384^2 sheet 4771, 5447 with two).
+template <typename T> constexpr int kd_pf(bool far = false) { return sizeof(T) == 8 || far ? 4 : 2; }
 // rows per thread of the filter along p
 constexpr int FILTER_R = 16;
 // substeps of a step at most (the splittings of vlasov_splitting)

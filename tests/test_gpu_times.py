@@ -67,3 +67,34 @@ def test_global_spline_drift_of_a_small_grid(V, storage):
         s.close()
     print(f"global spline half drift storage {storage}: 64^2 {times[0]:.2f} us, 512^2 {times[1]:.2f} us", flush=True)
     assert times[0] <= times[1]
+
+
+def _copy_time(V, nbytes):
+    """Least mean time (us) of ten copies of nbytes from one device buffer to another and back."""
+    import torch
+    a = torch.rand(nbytes // 8, dtype=torch.float64, device="cuda")
+    b = torch.empty_like(a)
+    best = math.inf
+    for _ in range(20):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for k in range(10):
+            V.device_copy(*((b, a) if k % 2 else (a, b)), nbytes)
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1) * 100.0)
+    return best
+
+
+def test_fused_kernel_beyond_the_last_level_cache(V):
+    """The FP32 fused kernel on 256 MiB of f against a copy of that size, which reads and writes the same bytes:
+    1.8 times as long where it wrote through the L2s and requested two rows ahead, 1.4 times as it was before it
+    did either; the limit lies between."""
+    n = 8192
+    p = I.Params(I.MODEL_SHEET, n, n, -10.0, 10.0, -4.0, 4.0, 0.005, bc_x=I.BC_ZERO, storage=I.STORAGE_F32)
+    s = V.Solver(p, V.ic_waterbag(1.2, 0.9, 1e-4, 1))
+    fused = _time(s, ["kick_drift2"], lambda: s.step(3))
+    s.close()
+    copy = _copy_time(V, 4 * n * n)
+    print(f"fused kernel on 256 MiB {fused:.1f} us, copy {copy:.1f} us", flush=True)
+    assert fused <= 1.6 * copy
