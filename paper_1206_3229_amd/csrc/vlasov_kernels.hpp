@@ -389,8 +389,9 @@ constexpr int KD_TW_WIDE = 182, KD_SPR_WIDE = 56;
 constexpr int KD_RPI = 2;
 constexpr int KD_MAX_BLOCKS = 4;
 
-// Where the drifted rows come from: kicked from f, or f itself.
-enum { KD_KICK = 0, KD_LOAD = 1 };
+// Where the drifted rows come from: kicked from f, or f itself (one value or 16
+// bytes a lane).
+enum { KD_KICK = 0, KD_LOAD = 1, KD_LOAD_WIDE = 2 };
 
 // Geometry of a fused tile of TW columns whose rows' windows lie within SPR
 // columns of slack: WK waves kick the KW = TW + 18 + SPR columns the windows
@@ -418,10 +419,12 @@ struct KDGeom {
     // Part of wave w in workgroup `rot`: the kicking waves come first, so that
     // each SIMD gets kicking and drifting waves alike; the two drifts change
     // places from one workgroup to the next.  With one half drift the waves
-    // past the kicking ones run it (those of a larger workgroup idle).
-    template <int NPASS> static __device__ __forceinline__ int part(int w, int rot)
+    // past the kicking ones run it (those of a larger workgroup idle).  WL: the
+    // waves that do the kicking ones' part.
+    template <int NPASS, int WL> static __device__ __forceinline__ int part(int w, int rot)
     {
-        if (w < WK) return w;
+        if (w < WL) return w;
+        w += WK - WL;
         if (NPASS == 1) return w + W1 < WK + W1 + W2 ? w + W1 : WK;
         const int d = w - WK + (rot & 1) * W1;
         return WK + (d < W1 + W2 ? d : d - (W1 + W2));
@@ -788,6 +791,90 @@ __device__ __forceinline__ void kd_load_part(const KDTile<T> &a, int t)
     for (int k = 0; k < NPASS; ++k) __syncthreads();
 }
 
+// The same with 16 bytes a lane and load, for lines of at least KD_WIDE_MIN
+// columns: two rows at a time by KD_WIDE_WAVES waves, one a row in FP32, two in
+// FP64.  EDGE (windows that pass an end of the grid): a lane's samples are taken
+// from the nearest ones of the row and, on a periodic axis, from its first ones.
+constexpr int KD_WIDE_MIN = 512;
+template <typename T> constexpr int KD_WIDE_WAVES = 2 * 256 * (int)sizeof(T) / (64 * 16);
+template <typename T, int BCX, int TW, int SPR, int NPASS, bool EDGE>
+__device__ __forceinline__ void kd_load_rows(const KDTile<T> &a, int t, int b_v)
+{
+    using G = KDGeom<TW, SPR>;
+    constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NB = G::NBUF;
+    constexpr int VEC = 16 / (int)sizeof(T), LPR = G::NTK / VEC, NI = R / P, PF = 4;
+    static_assert(P * LPR == 64 * KD_WIDE_WAVES<T> && LPR % 64 == 0 && NI % PF == 0, "a row of the pair by whole waves");
+    static_assert(KD_WIDE_MIN >= G::NTK + VEC, "a window passes the end of a line once");
+    typedef T vec_t __attribute__((ext_vector_type(VEC)));
+    typedef T load_t __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));
+    const int nx = a.nx, np = a.np, j0 = a.ty * (R * a.nb);
+    const int nblk = (min(R * a.nb, np - j0) + R - 1) / R;
+    const int q = __builtin_amdgcn_readfirstlane(t / LPR), l = t - q * LPR;  // row of the pair, place in it
+    const size_t ld = (size_t)nx;
+    vec_t v[PF], head[EDGE && BCX == BC_PERIODIC ? PF : 1];
+    // first column of the lane's samples in row r, and the one they are loaded from
+    auto column = [&](int r) { return __builtin_amdgcn_readlane(b_v, r) + VEC * l; };
+    auto from = [&](int c) {
+        if (!EDGE) return c;
+        if (BCX == BC_PERIODIC) return c < nx ? min(c, nx - VEC) : c - nx;
+        return min(max(c, 0), nx - VEC);
+    };
+    auto request = [&](int r, int slot) {
+        const T *row = a.fin + (size_t)min(j0 + r, np - 1) * ld;
+        v[slot] = *reinterpret_cast<const load_t *>(row + (unsigned)from(column(r)));
+        if (EDGE && BCX == BC_PERIODIC) head[slot] = *reinterpret_cast<const load_t *>(row);
+    };
+    auto settle = [&](int r, int slot) {
+        vec_t y = v[slot];
+        if (EDGE) {
+            const int c = column(r), d = BCX == BC_PERIODIC && c >= nx ? 0 : c - from(c);
+            vec_t o;
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                T x = BCX == BC_PERIODIC ? y[k] : T(0);
+#pragma unroll
+                for (int e = BCX == BC_PERIODIC ? k + 1 : 0; e < (BCX == BC_PERIODIC ? k + VEC : VEC); ++e)
+                    x = k + d == e ? (e < VEC ? y[e % VEC] : head[BCX == BC_PERIODIC ? slot : 0][e % VEC]) : x;
+                o[k] = x;
+            }
+            y = o;
+        }
+        return y;
+    };
+#pragma unroll
+    for (int it = 0; it < PF; ++it) request(P * it + q, it);
+    // the lane's place in ring row 0: a group of four values in FP32, half a group in FP64
+    vec_t *dst = reinterpret_cast<vec_t *>(a.kbuf) + (VEC == 4 ? l : (l >> 1) + (l & 1) * G::NG);
+    // (the last block on its own: where its requests are left out by a branch in
+    // the loop, the compiler waits for all outstanding ones at the loop's head)
+    auto block = [&](int blk, auto last) {
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            const int r = R * blk + P * it + q;
+            dst[((P * it + q) & (NB - 1)) * (LD / VEC)] = settle(r, it % PF);
+            if (!last.value || it + PF < NI) request(r + P * PF, it % PF);
+            __syncthreads();
+        }
+    };
+    for (int blk = 0; blk + 1 < nblk; ++blk) block(blk, std::false_type{});
+    block(nblk - 1, std::true_type{});
+#pragma unroll
+    for (int k = 0; k < NPASS; ++k) __syncthreads();
+}
+
+template <typename T, int BCX, int TW, int SPR, int NPASS>
+__device__ __forceinline__ void kd_load_wide(const KDTile<T> &a, int t)
+{
+    constexpr int NTK = KDGeom<TW, SPR>::NTK;
+    const int jl = kd_row(a, t & 63);
+    int b_v = a.tx * TW + a.dm1[jl] + (NPASS == 2 ? a.dm2[jl] : 0) - 4 * NPASS;
+    if (BCX == BC_PERIODIC) b_v = wrap(b_v, a.nx);
+    if (__all(b_v >= 0 && b_v + NTK <= a.nx))
+        kd_load_rows<T, BCX, TW, SPR, NPASS, false>(a, t, b_v);
+    else
+        kd_load_rows<T, BCX, TW, SPR, NPASS, true>(a, t, b_v);
+}
+
 // The waves of the first half drift of a pair: wave w1 of W1.
 template <typename T, int BCX, int TW, int SPR, int SRC>
 __device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
@@ -944,7 +1031,8 @@ __device__ __forceinline__ void kd_no_part(const KDTile<T> &a)
     for (int k = 0; k < nblk * (R / KD_RPI) + NPASS; ++k) __syncthreads();
 }
 
-// One tile, by a workgroup of KDGeom::NT threads (or NT1 with one half drift).
+// One tile, by a workgroup of KDGeom::NT threads (or NT1 with one half drift;
+// with KD_LOAD_WIDE fewer: dr_threads).
 // SRC KD_KICK: the rows kicked, KD_LOAD: the rows of f (BCP, PF unused); then
 // NPASS half drifts.  rot: number of the workgroup.
 template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int SRC, int NPASS, bool THROUGH = false>
@@ -952,17 +1040,20 @@ __device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot)
 {
     using G = KDGeom<TW, SPR>;
     constexpr int R = ROWS_PER_BLOCK;
-    const int p = G::template part<NPASS>((int)threadIdx.x >> 6, rot);
+    constexpr int WL = SRC == KD_LOAD_WIDE ? KD_WIDE_WAVES<T> : G::WK;
+    const int p = G::template part<NPASS, WL>((int)threadIdx.x >> 6, rot);
     if (p < G::WK) {
-        if (SRC == KD_KICK)
+        if constexpr (SRC == KD_KICK)
             kd_kick_part<T, BCX, BCP, TW, SPR, PF, NPASS>(a, (int)threadIdx.x);
+        else if constexpr (SRC == KD_LOAD_WIDE)
+            kd_load_wide<T, BCX, TW, SPR, NPASS>(a, (int)threadIdx.x);
         else
             kd_load_part<T, BCX, TW, SPR, NPASS>(a, (int)threadIdx.x);
     } else {
         // row weights, both passes of a row adjacent
         const int j0 = a.ty * (R * a.nb);
         const int n = 2 * R * ((min(R * a.nb, a.np - j0) + R - 1) / R);
-        for (int k = threadIdx.x - G::NTK; k < n; k += blockDim.x - G::NTK) {
+        for (int k = threadIdx.x - 64 * WL; k < n; k += blockDim.x - 64 * WL) {
             const double4 w = (NPASS == 2 && (k & 1) ? a.dw2 : a.dw1)[min(j0 + (k >> 1), a.np - 1)];
             a.wtab[4 * k] = (T)w.x;
             a.wtab[4 * k + 1] = (T)w.y;
@@ -1000,20 +1091,34 @@ void k_kick_drift(
 // Steps 1 and 4 (eqs. step1, step4) without a kick before them: drift along x,
 // row j shifted by the constant p_j tau/dx cells, once or (NPASS = 2, tables 1
 // and 2) twice in turn; the tiles of the fused kernel with the rows' windows
-// loaded instead of kicked.  Latency-bound on small grids (64^2: 5.2 us; 12.7
-// with a workgroup of two waves that waited for each row of an edge tile),
-// near the copy rate on large ones (4096^2 FP64 48.6 us, 50.6 before; FP32
-// 29.7, 25.7 before: once in a call).
+// loaded instead of kicked.  Latency-bound on small grids (64^2 4.2 us; 11.5
+// with a workgroup of two waves that waited for each row of an edge tile), near
+// the copy rate on large ones.  It runs at the ends of a call, after every
+// filtered kick, and for both half drifts of grids that cannot fuse.  WIDE
+// (lines of KD_WIDE_MIN columns on): 16 bytes a load, and one half drift on
+// tiles of 224 columns by one block, whose stores fill whole 128-byte lines
+// where rows start on one.  One half drift, one value a load on tiles of 230 by
+// two blocks -> wide, us: FP32 4096^2 25.7 -> 22.5, 2048^2 7.9 -> 7.5, 512 x
+// 8192 10.2 -> 8.2; FP64 4096^2 48.0 -> 43.9, 2048^2 12.8 -> 11.7.  Two, on tiles of 230 by two blocks: FP32 4096^2 27.8 -> 26.2
+// (tiles of 224 27.1, by one block 30), FP64 no change.
 constexpr int DR_TW = 230;
-template <typename T, int BCX, int NPASS, bool THROUGH>
-static __global__ __launch_bounds__((NPASS == 2 ? KDGeom<DR_TW>::NT : KDGeom<DR_TW>::NT1))
+template <int NPASS, bool WIDE> constexpr int dr_width() { return NPASS == 1 && WIDE ? 224 : DR_TW; }
+template <typename T, int NPASS, bool WIDE>
+constexpr int dr_threads()
+{
+    using G = KDGeom<dr_width<NPASS, WIDE>()>;
+    return (NPASS == 2 ? G::NT : G::NT1) - (WIDE ? 64 * (G::WK - KD_WIDE_WAVES<T>) : 0);
+}
+template <typename T, int BCX, int NPASS, bool THROUGH, bool WIDE>
+static __global__ __launch_bounds__((dr_threads<T, NPASS, WIDE>()))
 __attribute__((amdgpu_waves_per_eu(8)))
 void k_drift(
     const T *__restrict__ fin, T *__restrict__ fout, const int32_t *__restrict__ dm1, const int32_t *__restrict__ dm2,
     const double4 *__restrict__ dw1, const double4 *__restrict__ dw2, double *__restrict__ part, int nx, int np, int nb,
     int ntx, int nty)
 {
-    using G = KDGeom<DR_TW>;
+    constexpr int TW = dr_width<NPASS, WIDE>();
+    using G = KDGeom<TW>;
     __shared__ __attribute__((aligned(16))) T kbuf[G::NBUF * G::ROWLD];
     __shared__ __attribute__((aligned(16))) T mbuf[NPASS == 2 ? G::NBUF * G::ROWLD : 4];
     __shared__ __attribute__((aligned(16))) T wtab[8 * ROWS_PER_BLOCK * KD_MAX_BLOCKS];
@@ -1021,7 +1126,7 @@ void k_drift(
     if (!xcd_tile(ntx, nty, tx, ty)) return;
     const KDTile<T> a{fin, fout, nullptr, 0.0, 0.0, dm1, dm2, dw1, dw2, nullptr, nullptr, part, nx, np, nb, tx, ty, kbuf,
                       mbuf, wtab};
-    kick_drift_tile<T, BCX, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, NPASS, THROUGH>(a, (int)blockIdx.x);
+    kick_drift_tile<T, BCX, BC_PERIODIC, TW, KD_SPR, 2, WIDE ? KD_LOAD_WIDE : KD_LOAD, NPASS, THROUGH>(a, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
