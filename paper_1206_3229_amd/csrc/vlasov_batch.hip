@@ -311,7 +311,7 @@ class Engine {
         if (e == hipSuccess) e = resident(vk::kb_force, KB_FORCE_NT, ncu, wg_force_);
         if (e == hipSuccess) e = resident(vk::kb_kick<T, kick_rows<T>()>, 256, ncu, wg_kick_);
         if (e == hipSuccess)
-            e = resident(vk::kb_kick_drift<T, kd_pf<T>()>, vk::KDGeom<vk::KB_KD_TW>::NT, ncu, wg_kd_);
+            e = resident(vk::kb_kick_drift<T>, vk::KDGeom<vk::KB_KD_TW>::NT, ncu, wg_kd_);
         return e;
     }
 
@@ -334,7 +334,7 @@ class Engine {
             if (dens) vk::kb_density<<<grid(wg_dens_, dens), 256, 0, st>>>(gd, cy + k, n, dens);
             if (force) vk::kb_force<<<grid(wg_force_, force), KB_FORCE_NT, 0, st>>>(gd, cy + k, n, force);
             if (kick) vk::kb_kick<T, kick_rows<T>()><<<grid(wg_kick_, kick), 256, 0, st>>>(gd, cy + k, n, kick);
-            if (kd) vk::kb_kick_drift<T, kd_pf<T>()><<<grid(wg_kd_, kd), NT, 0, st>>>(gd, cy + k, n, kd);
+            if (kd) vk::kb_kick_drift<T><<<grid(wg_kd_, kd), NT, 0, st>>>(gd, cy + k, n, kd);
         }
     }
 

@@ -877,13 +877,13 @@ __device__ __forceinline__ void kd_load_wide(const KDTile<T> &a, int t)
 
 // The waves of the first half drift of a pair: wave w1 of W1.
 template <typename T, int BCX, int TW, int SPR, int SRC>
-__device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
+__device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1, int t)
 {
     using G = KDGeom<TW, SPR>;
     constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NB = G::NBUF;
     const int nx = a.nx, np = a.np, i0 = a.tx * TW, j0 = a.ty * (R * a.nb);
     const int nblk = (min(R * a.nb, np - j0) + R - 1) / R;
-    const int lane = threadIdx.x & 63, l32 = lane & 31;
+    const int lane = t & 63, l32 = lane & 31;
     const bool hi = lane >= 32;
     const int jl = kd_row(a, lane);
     const int st_v = SRC == KD_KICK ? (a.krel[jl] + 3) >> 2 : 0;  // group where the row's window starts
@@ -928,7 +928,7 @@ __device__ __forceinline__ void kd_first_part(const KDTile<T> &a, int w1)
 // The waves of the half drift whose result is stored: wave w2 of W2.  THROUGH:
 // pairs are written through the L2 (single values and odd last rows are not).
 template <typename T, int BCX, int TW, int SPR, int SRC, int NPASS, bool THROUGH>
-__device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
+__device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2, int t)
 {
     using G = KDGeom<TW, SPR>;
     constexpr int R = ROWS_PER_BLOCK, LD = G::ROWLD, P = KD_RPI, NB = G::NBUF, NI = R / P;
@@ -936,7 +936,7 @@ __device__ __forceinline__ void kd_second_part(const KDTile<T> &a, int w2)
     constexpr bool ROWS = SRC == KD_KICK && NPASS == 1;  // windows start at their offset in the kicked range
     const int nx = a.nx, np = a.np, i0 = a.tx * TW, j0 = a.ty * (R * a.nb);
     const int nr = min(R * a.nb, np - j0), nblk = (nr + R - 1) / R;
-    const int lane = threadIdx.x & 63, l32 = lane & 31;
+    const int lane = t & 63, l32 = lane & 31;
     const bool hi = lane >= 32;
     int st_v = 0, cL;
     if (ROWS) {
@@ -1034,26 +1034,26 @@ __device__ __forceinline__ void kd_no_part(const KDTile<T> &a)
 // One tile, by a workgroup of KDGeom::NT threads (or NT1 with one half drift;
 // with KD_LOAD_WIDE fewer: dr_threads).
 // SRC KD_KICK: the rows kicked, KD_LOAD: the rows of f (BCP, PF unused); then
-// NPASS half drifts.  rot: number of the workgroup.
+// NPASS half drifts.  rot: number of the workgroup, t: of the thread in it.
 template <typename T, int BCX, int BCP, int TW, int SPR, int PF, int SRC, int NPASS, bool THROUGH = false>
-__device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot)
+__device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot, int t)
 {
     using G = KDGeom<TW, SPR>;
     constexpr int R = ROWS_PER_BLOCK;
     constexpr int WL = SRC == KD_LOAD_WIDE ? KD_WIDE_WAVES<T> : G::WK;
-    const int p = G::template part<NPASS, WL>((int)threadIdx.x >> 6, rot);
+    const int p = G::template part<NPASS, WL>(t >> 6, rot);
     if (p < G::WK) {
         if constexpr (SRC == KD_KICK)
-            kd_kick_part<T, BCX, BCP, TW, SPR, PF, NPASS>(a, (int)threadIdx.x);
+            kd_kick_part<T, BCX, BCP, TW, SPR, PF, NPASS>(a, t);
         else if constexpr (SRC == KD_LOAD_WIDE)
-            kd_load_wide<T, BCX, TW, SPR, NPASS>(a, (int)threadIdx.x);
+            kd_load_wide<T, BCX, TW, SPR, NPASS>(a, t);
         else
-            kd_load_part<T, BCX, TW, SPR, NPASS>(a, (int)threadIdx.x);
+            kd_load_part<T, BCX, TW, SPR, NPASS>(a, t);
     } else {
         // row weights, both passes of a row adjacent
         const int j0 = a.ty * (R * a.nb);
         const int n = 2 * R * ((min(R * a.nb, a.np - j0) + R - 1) / R);
-        for (int k = threadIdx.x - 64 * WL; k < n; k += blockDim.x - 64 * WL) {
+        for (int k = t - 64 * WL; k < n; k += blockDim.x - 64 * WL) {
             const double4 w = (NPASS == 2 && (k & 1) ? a.dw2 : a.dw1)[min(j0 + (k >> 1), a.np - 1)];
             a.wtab[4 * k] = (T)w.x;
             a.wtab[4 * k + 1] = (T)w.y;
@@ -1061,9 +1061,9 @@ __device__ __forceinline__ void kick_drift_tile(const KDTile<T> &a, int rot)
             a.wtab[4 * k + 3] = (T)w.w;
         }
         if (p >= G::WK + G::W1)
-            kd_second_part<T, BCX, TW, SPR, SRC, NPASS, THROUGH>(a, p - G::WK - G::W1);
+            kd_second_part<T, BCX, TW, SPR, SRC, NPASS, THROUGH>(a, p - G::WK - G::W1, t);
         else if (NPASS == 2)
-            kd_first_part<T, BCX, TW, SPR, SRC>(a, p - G::WK);
+            kd_first_part<T, BCX, TW, SPR, SRC>(a, p - G::WK, t);
         else
             kd_no_part<NPASS>(a);
     }
@@ -1085,7 +1085,7 @@ void k_kick_drift(
     int tx, ty;
     if (!xcd_tile(ntx, nty, tx, ty)) return;
     const KDTile<T> a{fin, fout, F, dt, dp, dm1, dm2, dw1, dw2, kbase, krel, part, nx, np, nb, tx, ty, kbuf, mbuf, wtab};
-    kick_drift_tile<T, BCX, BCP, TW, SPR, PF, KD_KICK, NPASS, THROUGH>(a, (int)blockIdx.x);
+    kick_drift_tile<T, BCX, BCP, TW, SPR, PF, KD_KICK, NPASS, THROUGH>(a, (int)blockIdx.x, (int)threadIdx.x);
 }
 
 // Steps 1 and 4 (eqs. step1, step4) without a kick before them: drift along x,
@@ -1126,7 +1126,8 @@ void k_drift(
     if (!xcd_tile(ntx, nty, tx, ty)) return;
     const KDTile<T> a{fin, fout, nullptr, 0.0, 0.0, dm1, dm2, dw1, dw2, nullptr, nullptr, part, nx, np, nb, tx, ty, kbuf,
                       mbuf, wtab};
-    kick_drift_tile<T, BCX, BC_PERIODIC, TW, KD_SPR, 2, WIDE ? KD_LOAD_WIDE : KD_LOAD, NPASS, THROUGH>(a, (int)blockIdx.x);
+    kick_drift_tile<T, BCX, BC_PERIODIC, TW, KD_SPR, 2, WIDE ? KD_LOAD_WIDE : KD_LOAD, NPASS, THROUGH>(
+        a, (int)blockIdx.x, (int)threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -2272,6 +2273,19 @@ __device__ __forceinline__ int find_member(const int32_t *__restrict__ off, int 
     return count - 1;
 }
 
+// threadIdx.x, in FP64 anew for every work item: what the tiles of all kinds
+// derive from it was computed before the loop over the items and spilled there
+// (18 registers of the fused kernel, 10 of the drift).  Spilled -> not, FP64: 32
+// grids of up to 1024 columns 3300 -> 2800 us, 8 of 2048^2 9420 -> 8450, one of
+// 256^2 1170 -> 1075.  FP32 fits without.
+template <typename T>
+__device__ __forceinline__ int thread_of_item()
+{
+    int t = (int)threadIdx.x;
+    if constexpr (sizeof(T) == 8) __asm__ __volatile__("" : "+v"(t));
+    return t;
+}
+
 template <typename T>
 static __global__ __launch_bounds__(KDGeom<DR_TW>::NT) __attribute__((amdgpu_waves_per_eu(8)))
 void kb_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int members, int items)
@@ -2289,19 +2303,20 @@ void kb_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int
         const int li = e - cy->off_drift[a];
         const int ntx = (g.nx + DR_TW - 1) / DR_TW;
         __syncthreads();  // the previous item's LDS rows are consumed
+        const int tid = thread_of_item<T>();
         const KDTile<T> t{(const T *)g.f[cur], (T *)g.f[cur ^ 1], nullptr, 0.0, 0.0, g.dm, g.dm, g.dw, g.dw, nullptr,
                           nullptr, kind == DRIFT_LAST ? nullptr : g.part, g.nx, g.np, 1, li % ntx, li / ntx, kbuf, mbuf,
                           wtab};
         if (g.bc_x == BC_PERIODIC) {
             if (kind == DRIFT_PAIR)
-                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 2>(t, e);
+                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 2>(t, e, tid);
             else
-                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 1>(t, e);
+                kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 1>(t, e, tid);
         } else {
             if (kind == DRIFT_PAIR)
-                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 2>(t, e);
+                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 2>(t, e, tid);
             else
-                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 1>(t, e);
+                kick_drift_tile<T, BC_ZERO, BC_PERIODIC, DR_TW, KD_SPR, 2, KD_LOAD, 1>(t, e, tid);
         }
     }
 }
@@ -2394,7 +2409,10 @@ static __global__ __launch_bounds__(256) void kb_kick(const GridDesc *__restrict
 // x, long steps), tiles of 182 columns with 56 of slack (the same 256 kicked
 // columns and four waves, more kicked columns per output).  Periodic p only.
 constexpr int KB_KD_TW = 230;
-template <typename T, int PF>
+// Rows requested ahead: with four, FP64 spills two registers (batches of up to
+// 256 columns 1 to 3 % slower, of 2048^2 1 % faster).
+constexpr int KB_PF = 2;
+template <typename T>
 static __global__ __launch_bounds__(KDGeom<KB_KD_TW>::NT) __attribute__((amdgpu_waves_per_eu(8)))
 void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy, int members, int items)
 {
@@ -2419,6 +2437,7 @@ void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy
         const T *fin = (const T *)g.f[kin];
         T *fout = (T *)g.f[kin ^ 1];
         __syncthreads();  // the previous item's LDS rows are consumed
+        const int tid = thread_of_item<T>();
         KDTile<T> t{fin, fout, g.Fkick, g.dt, g.dp, g.dm, g.dm, g.dw, g.dw, g.kbase, g.krel, g.part, g.nx, g.np, 1, tx, ty,
                           kbuf, mbuf, wtab};
         const bool px = g.bc_x == BC_PERIODIC;
@@ -2426,13 +2445,13 @@ void kb_kick_drift(const GridDesc *__restrict__ gd, const Cycle *__restrict__ cy
     if (cy->kick[a] == KICK_LAST) {                                                            \
         t.part = nullptr;                                                                      \
         if (px)                                                                                \
-            kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, TW, SPR, PF, KD_KICK, 1>(t, e);       \
+            kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, TW, SPR, KB_PF, KD_KICK, 1>(t, e, tid); \
         else                                                                                   \
-            kick_drift_tile<T, BC_ZERO, BC_PERIODIC, TW, SPR, PF, KD_KICK, 1>(t, e);           \
+            kick_drift_tile<T, BC_ZERO, BC_PERIODIC, TW, SPR, KB_PF, KD_KICK, 1>(t, e, tid);     \
     } else if (px) {                                                                           \
-        kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, TW, SPR, PF, KD_KICK, 2>(t, e);           \
+        kick_drift_tile<T, BC_PERIODIC, BC_PERIODIC, TW, SPR, KB_PF, KD_KICK, 2>(t, e, tid);     \
     } else {                                                                                   \
-        kick_drift_tile<T, BC_ZERO, BC_PERIODIC, TW, SPR, PF, KD_KICK, 2>(t, e);               \
+        kick_drift_tile<T, BC_ZERO, BC_PERIODIC, TW, SPR, KB_PF, KD_KICK, 2>(t, e, tid);         \
     }
         if (g.kd_wide) {
             KB_KD(KD_TW_WIDE, KD_SPR_WIDE)

@@ -46,3 +46,16 @@ def test_half_drifts_of_long_lines_load_16_bytes(code_objects):
                 loads = re.findall(r"global_load_dword\S*", text)
                 assert loads.count("global_load_dwordx4") >= 8, (name, loads)
     assert len(seen) == 16
+
+
+def test_batch_kernels_do_not_spill(code_objects):
+    """The batched drift and fused kernel hold eight tile kinds in one loop over the work items."""
+    seen = set()
+    for co in code_objects:
+        for name, meta in _kernels(co):
+            m = re.match(r"_ZN2vkL(?:8kb_drift|13kb_kick_drift)I([fd])", name)
+            if m:
+                seen.add(name)
+                for key in (".vgpr_spill_count", ".private_segment_fixed_size"):
+                    assert re.search(re.escape(key) + r":\s+0\b", meta), (name, key)
+    assert len(seen) == 4
