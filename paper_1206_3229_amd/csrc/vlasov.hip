@@ -813,8 +813,7 @@ int vlasov_tuning_candidates(vlasov_tuning *out, int32_t cap, int32_t *n)
             if (k < cap) out[k] = vlasov_tuning{a, r, 0, 1};
             ++k;
         }
-    // fused kick and drift (the drift and kick shapes serve the first and last
-    // half drift of a call and grids that cannot fuse)
+    // fused kick and drift (the kick shape serves grids that cannot fuse)
     for (int w : kdw)
         for (int b : kdb) {
             if (k < cap) out[k] = vlasov_tuning{DRIFT_NT, kick_rows<double>(), w, b};
