@@ -769,6 +769,12 @@ int vlasov_mag_history(vlasov_ctx *c, double *mx, double *my, int64_t cap, int64
 int vlasov_read_f(vlasov_ctx *c, double *f_host)
 {
     if (!c || !f_host) return fail(VLASOV_E_INVAL, "NULL argument");
+    if (c->P.storage == VLASOV_F64) {  // as it is stored: no copy on the way
+        HIP_TRY(hipMemcpyAsync(f_host, c->fcur(), (size_t)c->P.nx * (size_t)c->P.np * sizeof(double),
+                               hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        return VLASOV_OK;
+    }
     std::unique_ptr<char[]> raw;
     const int rc = read_raw(c, raw);
     if (rc == VLASOV_OK) widen(raw.get(), c->P, f_host);

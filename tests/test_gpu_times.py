@@ -98,3 +98,29 @@ def test_fused_kernel_beyond_the_last_level_cache(V):
     copy = _copy_time(V, 4 * n * n)
     print(f"fused kernel on 256 MiB {fused:.1f} us, copy {copy:.1f} us", flush=True)
     assert fused <= 1.6 * copy
+
+
+def test_read_f_against_a_plain_copy(V):
+    """32 MiB of f in FP64 into a buffer that has been written before, against torch's copy from the device into it:
+    5 times as long by way of fresh memory of the same size; the limit is the geometric mean of that and 1."""
+    import time
+
+    import torch
+    n = 2048
+    s = V.Solver(I.Params(I.MODEL_HMF, n, n, -math.pi, math.pi, -2.5, 2.5, 0.02), V.ic_waterbag(1.2, 0.9))
+    out = np.ones((n, n))
+    src = torch.rand(n, n, dtype=torch.float64, device="cuda")
+    best = []
+    for call in (lambda: V.check(V.load().vlasov_read_f(s._ctx, V._dptr(out))), lambda: torch.from_numpy(out).copy_(src)):
+        call()
+        times = []
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            call()
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        best.append(min(times) * 1e6)
+    s.close()
+    print(f"read_f of 32 MiB {best[0]:.0f} us, torch copy {best[1]:.0f} us", flush=True)
+    assert best[0] <= 2.3 * best[1]
