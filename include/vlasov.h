@@ -275,7 +275,7 @@ const char *vlasov_last_error(void);
 
 typedef struct {
     int32_t drift_threads;     /* 64, 128 or 256: accepted and kept, without effect (the drift
-                                  kernel has one shape, tiles of 230 columns) */
+                                  kernel's shape follows from the grid) */
     int32_t kick_rows;         /* rows per thread of the kick: 8, 16 or 32 */
     int32_t kick_drift_width;  /* 0: the kick (step 3) and the half drifts after it (step 4 and
                                   the next step 1; step 4 alone after the last kick of a call)

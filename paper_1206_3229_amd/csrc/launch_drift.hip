@@ -18,8 +18,9 @@ int launch_drift_by(vlasov_ctx *c, int ta, int tb, bool partials)
     const double4 *dw1 = c->dw(ta), *dw2 = c->dw(tb >= 0 ? tb : ta);
     double *part = partials ? c->at<double>(c->L.part) : nullptr;
     const int nx = (int)P.nx, np = (int)P.np;
-#define DRIFT_LAUNCH(KID, BX, NPASS)                                                                                    \
-    launch(c, KID, vk::k_drift<T, BX, NPASS, THROUGH, WIDE>, grid, dim3(vk::dr_threads<T, NPASS, WIDE>()), fin, fout, dm1, dm2, dw1, dw2, part, nx, np, nb, ntx, nty)
+#define DRIFT_LAUNCH(KID, BX, NPASS)                                                                                   \
+    launch(c, KID, vk::k_drift<T, BX, NPASS, THROUGH, WIDE>, grid, dim3(vk::dr_threads<T, NPASS, WIDE>()), fin, fout, \
+           dm1, dm2, dw1, dw2, part, nx, np, nb, ntx, nty)
     if (P.bc_x == VLASOV_BC_PERIODIC) {
         if (tb >= 0) DRIFT_LAUNCH(VLASOV_K_DRIFT2, vk::BC_PERIODIC, 2); else DRIFT_LAUNCH(VLASOV_K_DRIFT, vk::BC_PERIODIC, 1);
     } else {

@@ -39,8 +39,6 @@ int launch_kick(vlasov_ctx *c, double h)
     }
 }
 
-// Kick of step size h (w_k dt) with the last force.
-
 template <typename T>
 int launch_filter(vlasov_ctx *c)
 {
@@ -60,7 +58,6 @@ int launch_filter(vlasov_ctx *c)
     if (rc == VLASOV_OK) c->cur ^= 1;
     return rc;
 }
-
 
 template <typename T>
 int launch_kick_filter(vlasov_ctx *c, double h)

@@ -25,7 +25,7 @@ using namespace vlasov_detail;
 
 namespace {
 
-// Persistent launch widths (workgroups) of the four batched phases.
+// Threads per workgroup of the batched force.
 constexpr int KB_FORCE_NT = 256;
 
 size_t set_bytes(int K) { return align_up(sizeof(vk::GridDesc) * vk::BATCH_MAX + sizeof(vk::Cycle) * (size_t)K); }

@@ -45,12 +45,12 @@ inline int default_kd_blocks(int64_t nx, int64_t nblk)
 }
 // Sizes of f at which the drifts write their results through the L2s.
 // From through_bytes() on: a kernel ends, and the next one starts, only once the lines its XCDs hold
-// dirty are written back.  The fused kernel alone, written back -> through:
-// FP64 128^2 6.5 -> 6.4 us, 256^2 6.6 -> 6.4, 512^2 6.7 -> 6.5, 1024^2 9.5 ->
-// 8.9, 2048^2 22.5 -> 21, 4096^2 64.7 -> 64.2; FP32 (8 bytes a store) 256^2 6.0
-// -> 6.1, 724^2 6.28 -> 6.26, 1024^2 7.3 -> 7.15, 2048^2 14.7 -> 13.7, 4096^2
-// 40.7 -> 40.5.  The density after it starts sooner as well (2048^2 ring 277 ->
-// 264 us for 10 steps).
+// dirty are written back.  The fused kernel in steps of the sheet grid, written
+// back -> through: FP64 128^2 6.5 -> 6.5 us, 512^2 6.8 -> 6.5, 1024^2 9.7 -> 9.1,
+// 2048^2 18.4 -> 17.0, 4096^2 58.1 -> 55.8; FP32 (8 bytes a store) 256^2 5.8 ->
+// 5.9, 512^2 5.9 -> 6.2, 724^2 6.3 -> 6.4, 1024^2 7.4 -> 7.4, 2048^2 13.6 -> 13.0,
+// 4096^2 31.1 -> 30.8.  The density after it starts sooner as well (2048^2 ring
+// 277 -> 264 us for 10 steps).
 // Up to far_bytes(): the pair of buffers of larger grids does not fit in the 256
 // MiB of the last-level cache, and the lines that two tiles share go to memory
 // in two parts, one from each, unless the L2s put them together first.  Eight
@@ -65,8 +65,8 @@ template <typename T> bool write_through(const vlasov_params &P)
 {
     return bytes_of_f<T>(P) >= through_bytes<T>() && !far_grid<T>(P);
 }
-// Rows that the fused kernel's kick requests ahead.  FP64 four (4096^2 64.2 us,
-// 65.3 with two).  FP32 two, which is the faster by up to 5 % where f comes from
+// Rows that the fused kernel's kick requests ahead.  FP64 four (4096^2 sheet,
+// eight steps 568 us, 587 with two).  FP32 two, which is the faster by up to 5 % where f comes from
 // the last-level cache (1024^2 sheet, eight steps 124 us, 130 with four), and
 // four on far grids (16384^2 sheet 4771, 5447 with two).
 template <typename T> constexpr int kd_pf(bool far = false) { return sizeof(T) == 8 || far ? 4 : 2; }

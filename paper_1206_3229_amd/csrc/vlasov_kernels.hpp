@@ -367,18 +367,23 @@ static __global__ __launch_bounds__(256) void k_kick_filter(const T *__restrict_
 // outputs), lanes 0..31 of a wave in the first row of the pair and lanes
 // 32..63 in the second; the waves of a part share the runs of a row.
 //
+// All times here are of the launch in steps of the sheet grid (dt 0.01, calls of
+// 20 steps), by its own events.
 // What bounds it: small grids by the time of an interval in one wave (0.36 us;
-// with every wave kicking and drifting in turn 0.5 us, hence waves of their
-// own for each part); FP64 at 4096^2 by the traffic (without the drifts'
-// arithmetic 58 of 65 us, without the kick's 60), FP32 by traffic and VALU
-// issue together (30 to 36 of 40).  Four rows an interval, loads 6 to 14 rows
-// ahead, LDS reads an interval ahead and runs of two by twice the drifting
-// waves were no faster.  Runs of four
-// cost 15.25 operations an output and 7 LDS reads of 16 bytes for four
-// (runs of two: 17.5, and 12); row weights stand in LDS and row offsets one per
-// lane (v_readlane), where scalar loads between the barriers cost a wait each.
-// Measured alone, before -> now: 230 x 16 6.9 -> 6.05 us, 1024^2 10.1 -> 8.9,
-// 2048^2 22.2 -> 21.0, 4096^2 65.9 -> 64.2 (FP32 42.1 -> 40.5).
+// with every wave kicking and drifting in turn 0.5 us, hence waves of their own
+// for each part); 4096^2 by its loads, stores and the pipeline around them: FP64
+// 56 us, without the drifts' arithmetic 52, without the kick's 52, with neither
+// 49.5; FP32 30.5, 27.3, 28.5 and 25.2.  Four rows an interval, loads 6 to 14
+// rows ahead, LDS reads an interval ahead and runs of two by twice the drifting
+// waves were no faster.  Runs of four cost 15.25 operations an output and 7 LDS
+// reads of 16 bytes for four (runs of two: 17.5, and 12); row weights stand in
+// LDS and row offsets one per lane (v_readlane), where scalar loads between the
+// barriers cost a wait each.  Every wave kicking and drifting -> parts, runs of
+// four and stores through the L2s: 64^2 7.5 -> 6.3 us, 512^2 8.2 -> 6.5, 1024^2
+// 10.4 -> 9.2, 2048^2 19.1 -> 16.8, 4096^2 60.1 -> 55.9; FP32 7.2 -> 5.5, 7.5 ->
+// 5.9, 8.2 -> 7.2, 13.8 -> 13.0, 32.8 -> 30.5.
+// Registers: FP64 57 to 64, two spilled with periodic x and zero p; FP32 36 with
+// periodic p, 54 to 58 with zero p; eight waves per SIMD in all.
 // ---------------------------------------------------------------------------
 constexpr int KD_SPR = 8;
 // tiles for offsets that spread more (coarse p, fine x, long steps): the same
