@@ -371,17 +371,19 @@ static __global__ __launch_bounds__(256) void k_kick_filter(const T *__restrict_
 // 20 steps), by its own events.
 // What bounds it: small grids by the time of an interval in one wave (0.36 us;
 // with every wave kicking and drifting in turn 0.5 us, hence waves of their own
-// for each part); 4096^2 by its loads, stores and the pipeline around them: FP64
-// 56 us, without the drifts' arithmetic 52, without the kick's 52, with neither
-// 49.5; FP32 30.5, 27.3, 28.5 and 25.2.  Four rows an interval, loads 6 to 14
-// rows ahead, LDS reads an interval ahead and runs of two by twice the drifting
-// waves were no faster.  Runs of four cost 15.25 operations an output and 7 LDS
-// reads of 16 bytes for four (runs of two: 17.5, and 12); row weights stand in
-// LDS and row offsets one per lane (v_readlane), where scalar loads between the
-// barriers cost a wait each.  Every wave kicking and drifting -> parts, runs of
-// four and stores through the L2s: 64^2 7.5 -> 6.3 us, 512^2 8.2 -> 6.5, 1024^2
-// 10.4 -> 9.2, 2048^2 19.1 -> 16.8, 4096^2 60.1 -> 55.9; FP32 7.2 -> 5.5, 7.5 ->
-// 5.9, 8.2 -> 7.2, 13.8 -> 13.0, 32.8 -> 30.5.
+// for each part); FP64 at 4096^2 by its loads and stores (56 us, without the
+// drifts' arithmetic 52, without the kick's 52, with neither 49.5); FP32 there by
+// VALU issue, 17.8 M wave-instructions of four cycles on 1024 SIMDs being all of
+// its 70 000 cycles (30.5 us, 27.3, 28.5, and with no arithmetic 25.2).  Four
+// rows an interval, loads 6 to 14 rows ahead, LDS reads an interval ahead and
+// runs of two by twice the drifting waves were no faster.  Runs of four cost
+// 15.25 operations an output and 7 LDS reads of 16 bytes for four (runs of two:
+// 17.5, and 12); row weights stand in LDS and row offsets one per lane
+// (v_readlane), where scalar loads between the barriers cost a wait each.  Every
+// wave kicking and drifting -> parts, runs of four and stores through the L2s:
+// 64^2 7.5 -> 6.3 us, 512^2 8.2 -> 6.5, 1024^2 10.4 -> 9.2, 2048^2 19.1 -> 16.8,
+// 4096^2 60.1 -> 55.9; FP32 7.2 -> 5.5, 7.5 -> 5.9, 8.2 -> 7.2, 13.8 -> 13.0, 32.8
+// -> 30.5.
 // Registers: FP64 57 to 64, two spilled with periodic x and zero p; FP32 36 with
 // periodic p, 54 to 58 with zero p; eight waves per SIMD in all.
 // ---------------------------------------------------------------------------
